@@ -1,6 +1,7 @@
 """Build libmts.so (hipcc, gfx950) in-tree."""
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -16,7 +17,9 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Wall"]
 # per-source extra flags: the step kernel's floating point never sees a NaN
 # (freeness keys are finite or -inf), so its maxima need no NaN quieting
-EXTRA = {"mts_kernels.hip": ["-fno-honor-nans"]}
+EXTRA = {"mts_kernels.hip": ["-fno-honor-nans", "-Wno-unused-function", "-Wno-unneeded-internal-declaration"]}
+# the step kernel's instantiations, compiled as this many units of their own
+STEP_PARTS = 8
 
 
 def _run(cmd):
@@ -31,12 +34,19 @@ def build(verbose=False):
     os.makedirs(os.path.dirname(LIB), exist_ok=True)
     objdir = os.path.join(os.path.dirname(LIB), "obj")
     os.makedirs(objdir, exist_ok=True)
-    outs, objs = [], []
+    cmds, objs = [], []
     for src in SOURCES:
-        obj = os.path.join(objdir, os.path.basename(src) + ".o")
-        outs.append(_run([HIPCC] + FLAGS + EXTRA.get(os.path.basename(src), []) +
-                         ["-I", os.path.join(ROOT, "include"), "-c", "-o", obj, src]))
-        objs.append(obj)
+        name = os.path.basename(src)
+        units = [(name + ".o", [])]
+        if name == "mts_kernels.hip":
+            units = [("%s.part%d.o" % (name, k), ["-DMTS_STEP_PART=%d" % k]) for k in reversed(range(STEP_PARTS))] + units
+        for out, defs in units:
+            obj = os.path.join(objdir, out)
+            cmds.append([HIPCC] + FLAGS + EXTRA.get(name, []) + defs +
+                        ["-I", os.path.join(ROOT, "include"), "-c", "-o", obj, src])
+            objs.append(obj)
+    with ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+        outs = list(pool.map(_run, cmds))
     tmp = LIB + ".tmp"
     outs.append(_run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs))
     out = "\n".join(o for o in outs if o.strip())

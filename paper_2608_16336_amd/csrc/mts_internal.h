@@ -66,13 +66,21 @@ struct Layout {
     size_t next_seq, stats, digest;                                     // [R], [R][NSTAT], [R]
     size_t arr_cnt, arr_rec;                                            // [R][chunk], [R][chunk][cap]
     size_t wheel;                                                       // [R][wsz][wcap]
-    size_t qx;                                                          // [R][I][kQxDepth] uint4 (I > 64 only)
+    size_t qx;                                                          // [R][I][qx_depth] uint4 (I > 64 only)
     size_t total;
 };
 
 // The kernels for more than 64 instances keep, behind each instance's queue
-// cache in LDS, up to this many further waiting requests in order in HBM.
-constexpr uint32_t kQxDepth = 64;
+// cache in LDS, further waiting requests in order in HBM: as many as the
+// instance has slots, so that a burst's whole pile stays in order, unless
+// that takes more than kQxBudget bytes in all (then kQxLeast, one rescan's
+// selection).
+constexpr uint32_t kQxLeast = 64;
+constexpr size_t kQxBudget = size_t(8) << 30;
+inline uint32_t qx_depth(size_t R, size_t I, size_t S)
+{
+    return R * I * S * 16 <= kQxBudget ? uint32_t(S) : kQxLeast;
+}
 
 // Everything a kernel launch needs, passed by value.
 struct Params {
@@ -120,7 +128,8 @@ struct Params {
     uint32_t* arr_cnt;
     unsigned long long* arr_rec;
     uint32_t* wheel;
-    uint4* qx;                     // [R][I][kQxDepth] queue cache extension (I > 64; null otherwise)
+    uint4* qx;                     // [R][I][qxd] queue cache extension (I > 64; null otherwise)
+    uint32_t qxd;                  // its entries per instance
 };
 
 // LDS bytes of one wave (one replica) of the step kernel

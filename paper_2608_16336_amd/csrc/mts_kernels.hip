@@ -158,10 +158,11 @@ struct Ctx {
     uint4* qt;                 // [I][td] a ring: entry k at (qh + k) mod td
     int* qn;                   // [I] cached entries
     int* qh;                   // [I] ring position of the first entry
-    // kernels for 128+ instances (null otherwise): behind the ring, up to
-    // kQxDepth further waiting requests of the instance in order, in HBM
-    int* xn;                   // [I] head << 16 | count
-    uint4* qx;                 // [I][kQxDepth] this replica's extensions
+    // kernels for 128+ instances (null otherwise): behind the ring, further
+    // waiting requests of the instance in order, a ring of xd entries in HBM
+    int* xn;                   // [I] first entry << 16 | count
+    uint4* qx;                 // [I][xd] this replica's extensions
+    int xd;
     int td;
     uint32_t blind;            // 1: tiers order nothing (tier-blind scheduling)
     // adaptive headroom and promotion (null when both are off): the LDS
@@ -212,7 +213,7 @@ __device__ __forceinline__ unsigned long long* ext_hsnap(const Params& P)
     return reinterpret_cast<unsigned long long*>(reinterpret_cast<const unsigned long long*>(P.ext + kXHsnap)[0]);
 }
 
-template <int IM, bool INF, bool EXT>
+template <int IM, bool INF, bool EXT, bool QC>
 __device__ inline Ctx carve(char* base, const Params& P)
 {
     const LdsLayout Y = lds_layout(IM, P.I, P.W, P.RB, P.wsz, P.policy, P.qdepth, EXT);
@@ -253,13 +254,14 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.nvic = reinterpret_cast<int*>(C.vic + kVic);
     C.wc = reinterpret_cast<unsigned*>(base + Y.wc);
     C.wov = reinterpret_cast<unsigned*>(base + Y.wov);
-    C.td = int(P.qdepth);
+    C.td = QC ? int(P.qdepth) : 0;
     C.blind = P.blind;
     C.qt = reinterpret_cast<uint4*>(base + Y.qt);
     C.qn = reinterpret_cast<int*>(base + Y.qn);
     C.qh = C.qn + IM;
     C.xn = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.xn) : nullptr;
     C.qx = nullptr;  // per replica, set with the slot records
+    C.xd = int(P.qxd);
     if (INF) {
         C.fsum = reinterpret_cast<unsigned long long*>(base + Y.inf);
         C.svc = reinterpret_cast<long long*>(base + Y.inf + IM * 8);
@@ -515,6 +517,13 @@ __device__ __forceinline__ void qx_clear(const Ctx& C, int i)
     if (C.xn) C.xn[i] = 0;
 }
 __device__ __forceinline__ int qx_count(const Ctx& C, int i) { return C.xn ? (C.xn[i] & 0xFFFF) : 0; }
+// entry k of instance i's extension whose first entry is at xh (k <= xd)
+__device__ __forceinline__ uint4* qx_at(const Ctx& C, int i, int xh, int k)
+{
+    const int x = xh + k;
+    return C.qx + size_t(i) * C.xd + (x >= C.xd ? x - C.xd : x);
+}
+
 
 __device__ __forceinline__ void clear_hol(const Ctx& C, int i)
 {
@@ -536,7 +545,11 @@ __device__ __forceinline__ void set_hol(const Ctx& C, int i, int slot, unsigned 
 // instance i) and keep it: popping the head promotes the first cached entry
 // (or leaves the head unknown, to be found by a rescan), a new waiting
 // request becomes the head or enters the cache at its place when it is
-// smaller than the last cached entry.
+// smaller than the last cached entry (or follows it, when every waiting
+// request is listed).  Arrivals enter it too (qc_arrive and the dispatch's
+// run): dropping the cache of every instance that takes an ordinary arrival
+// cost the overloaded gauss10 workload 1.57 rescans per tick where 0.22
+// remain, 24.6 ms per 1000 ticks against 18.9 (4096 replicas).
 // the rank a tier gives in every ordering (queue, preemption, migration
 // candidate): the tier itself, or 0 for all when scheduling is tier-blind
 __device__ __forceinline__ unsigned long long rank_of(const Ctx& C, uint32_t tier)
@@ -562,7 +575,18 @@ __device__ __forceinline__ int qc_at(const Ctx& C, int i, int k)
 __device__ inline void qc_insert_at(const Ctx& C, int i, int p, uint4 e)
 {
     const int n = C.qn[i];
-    if (n >= C.td) qx_clear(C, i);  // the last entry drops out: the extension no longer follows
+    if (C.xn && n >= C.td) {
+        // the last entry drops out of the ring, to the front of the extension
+        // (it is the smallest request behind the ring)
+        const int xv = C.xn[i], xc = xv & 0xFFFF, xh = xv >> 16;
+        if (xc < C.xd) {
+            const int h = xc == 0 ? 0 : xh == 0 ? C.xd - 1 : xh - 1;
+            *qx_at(C, i, h, 0) = C.qt[qc_at(C, i, n - 1)];
+            C.xn[i] = (h << 16) | (xc + 1);
+        } else {
+            C.xn[i] = 0;
+        }
+    }
     if (p == 0) {
         // in front: the ring start moves back (over the last entry when full)
         const int h = C.qh[i];
@@ -586,10 +610,11 @@ __device__ inline void hol_pop(const Ctx& C, int i)
         if ((xv & 0xFFFF) == 0) { C.hols[i] = kHolUnknown; return; }
         // the extension's first entry becomes the head of line
         const int xh = xv >> 16;
-        const uint4 e = C.qx[size_t(i) * kQxDepth + xh];
+        const uint4 e = *qx_at(C, i, xh, 0);
         const uint32_t tier = (e.w >> 12) & 15u;
         set_hol(C, i, int(e.w & 0xFFFu), qc_key(C, e), e.y, kWaiting | (tier << 2) | (((e.w >> 16) & 1u) << 6), e.z);
-        C.xn[i] = ((xh + 1) << 16) | ((xv & 0xFFFF) - 1);
+        // (an empty extension starts at its first entry again)
+        C.xn[i] = (xv & 0xFFFF) == 1 ? 0 : ((xh + 1 == C.xd ? 0 : xh + 1) << 16) | ((xv & 0xFFFF) - 1);
         return;
     }
     const uint4 e = C.qt[qc_at(C, i, 0)];
@@ -599,24 +624,104 @@ __device__ inline void hol_pop(const Ctx& C, int i)
     C.qh[i] = h == C.td ? 0 : h;
     C.qn[i] = n - 1;
 }
-// a new waiting request of i (nwait already counts it)
-__device__ inline void hol_insert(const Ctx& C, int i, unsigned long long key, int slot, uint32_t word, uint32_t meta,
+// what the dispatch knows of an instance's queue cache (kept in order[] while
+// its arrivals enter): nothing to do, the head of line and the cache are the
+// smallest of the waiting requests, or all of them; with the flags that the
+// head of line is one of this batch's arrivals, and that the batch's other
+// arrivals follow the cached entries as one run
+constexpr int kQcSkip = 0, kQcPart = 1, kQcAll = 2, kQcHead = 4, kQcRun = 8;
+__device__ __forceinline__ unsigned long long arr_key(const Ctx& C, int tier, uint32_t seq)
+{
+    return (rank_of(C, uint32_t(tier)) << 32) | seq;
+}
+// arrival e of instance i, larger than its head of line, enters the cache: at
+// its place among the cached entries (looked for from the end, where a new
+// arrival of a low tier belongs), behind them when they list every waiting
+// request and there is room, else not at all (it is larger than the cached
+// prefix).  One that falls behind the ring drops the extension, which it may
+// fall into.
+__device__ inline void qc_arrive(const Ctx& C, int i, uint4 e)
+{
+    const unsigned long long key = qc_key(C, e);
+    const int n = C.qn[i];
+    int p = n;
+    while (p > 0 && key < qc_key(C, C.qt[qc_at(C, i, p - 1)])) --p;
+    if (p < n) { qc_insert_at(C, i, p, e); return; }
+    if (qx_count(C, i) > 0) { qx_clear(C, i); C.order[i] = kQcPart; return; }
+    if (n < C.td && (C.order[i] & 3) == kQcAll) { C.qt[qc_at(C, i, n)] = e; C.qn[i] = n + 1; }
+}
+// a new waiting request of i (nwait already counts it); returns true when it
+// falls behind the ring of an instance with an extension: the caller's wave
+// then puts it in its place there (qx_insert)
+__device__ inline bool hol_insert(const Ctx& C, int i, unsigned long long key, int slot, uint32_t word, uint32_t meta,
                                   uint32_t tarr)
 {
     const int h = C.hols[i];
-    if (h == kHolUnknown) return;
-    if (h == kNoHol) { set_hol(C, i, slot, key, word, meta, tarr); if (C.td) C.qn[i] = 0; qx_clear(C, i); return; }
+    if (h == kHolUnknown) return false;
+    if (h == kNoHol) { set_hol(C, i, slot, key, word, meta, tarr); if (C.td) C.qn[i] = 0; qx_clear(C, i); return false; }
     if (key < C.holk[i]) {
         if (C.td) qc_insert_at(C, i, 0, qc_pack(C.holk[i], h, C.hwd[i], C.hmt[i], C.hta[i]));
         set_hol(C, i, slot, key, word, meta, tarr);
-        return;
+        return false;
     }
-    if (!C.td) return;
+    if (!C.td) return false;
     const int n = C.qn[i];
     int p = 0;
     while (p < n && qc_key(C, C.qt[qc_at(C, i, p)]) < key) ++p;
     if (p < n) qc_insert_at(C, i, p, qc_pack(key, slot, word, meta, tarr));
-    else qx_clear(C, i);  // beyond the cached run: it may fall inside the extension
+    else if (qx_count(C, i) > 0) return true;
+    else if (n < C.td && C.nwait[i] == n + 2) {
+        // the head and the cache listed every other waiting request: it is the last
+        C.qt[qc_at(C, i, n)] = qc_pack(key, slot, word, meta, tarr);
+        C.qn[i] = n + 1;
+    }
+    return false;
+}
+
+// Puts waiting request e at its place in the extension of instance i (which
+// has one): the entries after it move up by one, read and written from the
+// end 256 at a time, so the place in a queue of 2000 costs a few memory round
+// trips instead of the rescans that a dropped extension brings (3.2 rescans of
+// 2048 slots per tick on the wide workload, 0.65 with it; 23.6 ms per 300
+// ticks against 21.5).  When nothing lies behind it, it is the last known
+// request only if every other waiting one is listed; else it stays out.
+// Uniform.
+__device__ inline void qx_insert(const Ctx& C, int i, uint4 e, int lane)
+{
+    constexpr int GX = 4;
+    const int xv = C.xn[i], xc = xv & 0xFFFF, xh = xv >> 16;
+    const unsigned long long key = qc_key(C, e);
+    if (xc >= C.xd) { wave_sync(); if (lane == 0) C.xn[i] = 0; wave_sync(); return; }
+    int p = xc;  // the place of e: everything from p on is larger
+    for (int hi = xc; hi > 0; hi -= 64 * GX) {
+        uint4 v[GX];
+        bool up[GX];
+#pragma unroll
+        for (int g = 0; g < GX; ++g) {
+            const int k = hi - 1 - g * 64 - lane;
+            v[g] = k >= 0 ? *qx_at(C, i, xh, k) : make_uint4(0u, 0u, 0u, 0u);
+        }
+        int moved = 0;
+#pragma unroll
+        for (int g = 0; g < GX; ++g) {
+            const int k = hi - 1 - g * 64 - lane;
+            up[g] = k >= 0 && qc_key(C, v[g]) > key;
+            moved += __popcll(ballot(up[g]));
+        }
+#pragma unroll
+        for (int g = 0; g < GX; ++g)
+            if (up[g]) *qx_at(C, i, xh, hi - g * 64 - lane) = v[g];
+        wave_sync();
+        p -= moved;
+        if (moved < 64 * GX) break;
+    }
+    const bool all = C.nwait[i] == 2 + C.qn[i] + xc;  // head, ring, extension, e
+    wave_sync();
+    if (lane == 0 && (p < xc || all)) {
+        *qx_at(C, i, xh, p) = e;
+        C.xn[i] = (xh << 16) | (xc + 1);
+    }
+    wave_sync();
 }
 
 // file a running request under its finish tick
@@ -743,6 +848,7 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
             fr += vb;
             G -= vg;
             aborted = aborted || vm;
+            bool deep = false;
             if (lane == 0) {
                 C.held[i] -= vb;
                 C.B[i] -= 1;
@@ -758,10 +864,12 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
                 stat(C, vt * 8 + kPreempted, 1);
                 if (vm) C.flags[i] |= kFlagAbort;
                 const unsigned long long key = (rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx);
-                hol_insert(C, i, key, vs, vw, vmeta, vta);
+                deep = hol_insert(C, i, key, vs, vw, vmeta, vta);
                 if (C.ext) wlb(C)[i] = vta < wlb(C)[i] ? vta : wlb(C)[i];
             }
             wave_sync();
+            if (C.xn && ballot(deep))
+                qx_insert(C, i, qc_pack((rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx), vs, vw, vmeta, vta), lane);
             if (unknown) { scan = G > fr; break; }  // the winner's next key is unknown: read again
         }
     }
@@ -961,12 +1069,13 @@ __device__ __forceinline__ void tier_stat3(const Ctx& C, int tier, bool f0, int 
 // smallest keys of a longer queue; when all w of those fit, the head of line
 // is unknown afterwards (the next rescan finds it).
 // xn0 >= 0: the list is the head of line, the xn0 cached entries and the
-// extension from its head xh0 on (admit_cached): the new extension is then
-// a suffix of the stored one (the cache never holds more than qdepth), so
-// only its head moves.
+// extension (xc0 entries from xh0 on) as far as it fits the wave
+// (admit_cached): the new extension is then a suffix of the stored one (the
+// cache never holds more than qdepth), so only its head moves; when the whole
+// list is admitted, its first entry becomes the head of line.
 __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, int w, unsigned long long key,
                                     uint32_t word, uint32_t meta, uint32_t ta, int slot, bool complete = true,
-                                    int xn0 = -1, int xh0 = 0)
+                                    int xn0 = -1, int xh0 = 0, int xc0 = 0)
 {
     const size_t b = size_t(i) * C.S;
     const int dem = lane < w ? blocks_of(wlo(word), C.shift) : 0;
@@ -1010,8 +1119,17 @@ __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, i
         }
         if (C.td && na < w) { C.qn[i] = min(w - na - 1, C.td); C.qh[i] = 0; }
         if (C.xn) {
-            const int xc = C.td && na < w && w - na - 1 > C.td ? w - na - 1 - C.td : 0;
-            C.xn[i] = xc && xn0 >= 0 ? ((xh0 + na + C.td - xn0) << 16) | xc : xc;
+            if (xn0 < 0) {
+                C.xn[i] = C.td && na < w && w - na - 1 > C.td ? w - na - 1 - C.td : 0;
+            } else {
+                // entries before the new extension: the admitted ones and the new ring's
+                // (behind the new head of line, or, when all were admitted, none)
+                const int used = na + (na < w ? min(w - na - 1, C.td) : -1) - xn0;
+                const int xc = xc0 - used;
+                const int xh = xh0 + used;
+                C.xn[i] = xc > 0 ? ((xh >= C.xd ? xh - C.xd : xh) << 16) | xc : 0;
+                if (na == w && xc > 0) hol_pop(C, i);
+            }
         }
     }
     // the ranked list holds the smallest keys: the ones after the new head fill
@@ -1019,7 +1137,7 @@ __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, i
     if (C.td && lane > na && lane < w && lane - na - 1 < C.td)
         C.qt[i * C.td + lane - na - 1] = qc_pack(key, slot, word, meta, ta);
     if (C.xn && C.td && xn0 < 0 && lane > na + C.td && lane < w)
-        C.qx[size_t(i) * kQxDepth + (lane - na - 1 - C.td)] = qc_pack(key, slot, word, meta, ta);
+        *qx_at(C, i, 0, lane - na - 1 - C.td) = qc_pack(key, slot, word, meta, ta);
     wave_sync();
 }
 
@@ -1326,15 +1444,16 @@ __device__ inline void admit_batch(const Ctx& C, int i, uint32_t t, int lane)
 __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
 {
     const int n = C.qn[i];
-    // (kernels for 128+ instances) the extension follows the ring: n + xc <= 63
+    // (kernels for 128+ instances) the extension follows the ring
     const int xv = C.xn ? C.xn[i] : 0, xc = xv & 0xFFFF, xh = xv >> 16;
+    const int w = min(64, n + xc + 1);
     unsigned long long key = kNone;
     uint32_t word = 0, meta = 0, ta = 0;
     int slot = 0;
     if (lane == 0) {
         key = C.holk[i]; word = C.hwd[i]; meta = C.hmt[i]; ta = C.hta[i]; slot = C.hols[i];
-    } else if (lane <= n + xc) {
-        const uint4 e = lane <= n ? C.qt[qc_at(C, i, lane - 1)] : C.qx[size_t(i) * kQxDepth + xh + lane - n - 1];
+    } else if (lane < w) {
+        const uint4 e = lane <= n ? C.qt[qc_at(C, i, lane - 1)] : *qx_at(C, i, xh, lane - n - 1);
         const uint32_t tier = (e.w >> 12) & 15u;
         key = qc_key(C, e);
         word = e.y;
@@ -1342,8 +1461,8 @@ __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
         ta = e.z;
         slot = int(e.w & 0xFFFu);
     }
-    const bool complete = C.nwait[i] == n + xc + 1;
-    admit_ranked(C, i, t, lane, n + xc + 1, key, word, meta, ta, slot, complete, C.xn ? n : -1, xh);
+    const bool complete = C.nwait[i] == w;
+    admit_ranked(C, i, t, lane, w, key, word, meta, ta, slot, complete, C.xn ? n : -1, xh, xc);
 }
 
 // Admission of instance i whose waiting requests all arrived in the previous
@@ -1371,6 +1490,70 @@ __device__ inline void admit_fresh(const Ctx& C, int i, uint32_t t, int lane)
         key = (rank_of(C, tier) << 32) | C.lsq[idx];
     }
     admit_ranked(C, i, t, lane, w, key, word, meta, ta, slot);
+}
+
+// Admission of every instance whose waiting requests all arrived in the
+// previous tick and whose head of line fits (one-wave kernels).  The dispatch's
+// list in LDS holds those requests in (tier, seq) order, one per lane; each
+// instance admits the longest prefix of its own requests whose summed demand
+// fits, and its next request becomes the head of line.  One pass over the list
+// serves all instances, whatever their number: a lane writes its own request,
+// and an instance's totals are combined by LDS atomics.  (A pass per instance
+// and a lane-parallel round for the instances with one request took the sweep
+// 10.85 ms per 1000 ticks, this one 10.2.)
+__device__ inline void admit_fresh_all(const Ctx& C, uint32_t t, int lane)
+{
+    const bool in = lane < *C.lastn;
+    const uint32_t e = in ? C.lsl[lane] : 0u;
+    const uint32_t word = in ? C.lw[lane] : 0u, seq = in ? C.lsq[lane] : 0u;
+    const int i = int(e >> 16), slot = int(e & 0xFFFu), tier = int((e >> 12) & 15u);
+    const int fr = C.freeb[i];
+    const bool act = in && C.frs[i] && C.hols[i] >= 0 && C.hold[i] <= fr;
+    const int dem = act ? blocks_of(wlo(word), C.shift) : 0;
+    // per instance: the running sum of the demands and the lanes of its requests
+    int pre = 0;
+    unsigned long long own = 0;
+    for (unsigned long long m = ballot(act); m;) {
+        const int ii = rl(i, ffs64(m));
+        const bool mine = act && i == ii;
+        const unsigned long long mm = ballot(mine);
+        const int p = wscan(mine ? dem : 0, lane);
+        if (mine) { pre = p; own = mm; }
+        m &= ~mm;
+    }
+    const bool adm = act && pre <= fr;
+    const unsigned long long am = ballot(adm) & own;
+    const int na = __popcll(am), cnt = __popcll(own), idx = __popcll(own & lanemask_lt());
+    const int nw = act ? C.nwait[i] : 0;
+    wave_sync();
+    if (adm) {
+        const uint32_t len = wlo(word), rem = wmid(word), fin = t + rem;
+        s_set_wm(C, size_t(i) * C.S + slot, kRunW | ((fin & kFin) << 16) | (len + rem),
+                 (uint32_t(tier) << 2) | kRunning | kAdmitted);
+        // (a request's first admission, one tick after it arrived)
+        stat(C, tier * 8 + kAdmittedCnt, 1);
+        stat(C, tier * 8 + kQdelay, 1);
+        hist_add(C, kHistQdelay, tier, 1);
+        c16_inc(C.res, res_idx(C, i, (len - t - 1u) & C.bmask));
+        tier_inc(C, i, tier);
+        wheel_put(C, fin, i, slot);
+        atomicSub(&C.freeb[i], dem);
+        atomicAdd(&C.held[i], dem);
+    }
+    if (act) {
+        const uint32_t meta = kWaiting | (uint32_t(tier) << 2);
+        if (idx == 0) {
+            atomicAdd(&C.B[i], na);
+            atomicSub(&C.nwait[i], na);
+            if (cnt != nw) stat(C, kInvariant, 1);
+            if (na == cnt) clear_hol(C, i);
+            else if (C.td) { C.qn[i] = min(cnt - na - 1, C.td); C.qh[i] = 0; }
+        }
+        if (idx == na) set_hol(C, i, slot, (rank_of(C, uint32_t(tier)) << 32) | seq, word, meta, t - 1u);
+        else if (C.td && idx > na && idx - na - 1 < C.td)
+            C.qt[i * C.td + idx - na - 1] = qc_pack(seq, slot, word, meta, t - 1u);
+    }
+    wave_sync();
 }
 
 // Admission of instance i's known head of line, which fits (per lane: the
@@ -1542,7 +1725,7 @@ __device__ __forceinline__ void block_sync()
     else wave_sync();
 }
 
-template <int IM, bool INF, bool EXT>
+template <int IM, bool INF, bool EXT, bool QC>
 __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(Params P, unsigned long long t0, uint32_t nt)
 {
     // IPL: instances per lane when one wave covers every instance (the serial
@@ -1552,7 +1735,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
     constexpr int IPL = (IM + 63) / 64;
     constexpr int OPL = (IM + 64 * NW - 1) / (64 * NW);
     extern __shared__ __align__(16) char lds_raw[];
-    Ctx C = carve<IM, INF, EXT>(lds_raw, P);
+    Ctx C = carve<IM, INF, EXT, QC>(lds_raw, P);
     const int lane = lane_id();
     const int wid = NW > 1 ? int(threadIdx.x >> 6) : 0;
     const uint32_t tid = threadIdx.x;
@@ -1581,7 +1764,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
         for (int p = 0; p < kTiers; ++p) C.hq[p] = hq[p];
         const size_t rb = size_t(r) * I * S;
         C.slot = P.slot + rb;
-        if (C.xn) C.qx = P.qx + size_t(r) * I * kQxDepth;
+        if (C.xn) C.qx = P.qx + size_t(r) * I * P.qxd;
         C.wheel = P.wheel + size_t(r) * wsz * P.wcap;
         C.hist = P.hist + size_t(r) * kHistPerReplica;
 
@@ -1906,17 +2089,25 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                                   C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || unk;
                 }
                 bool any = unk;
-                unsigned long long bat[OPL], frm[OPL], cch[OPL];
+                // queues that hold the previous tick's arrivals only
+                {
+                    bool fresh = false;
+#pragma unroll
+                    for (int j = 0; j < OPL; ++j) {
+                        const uint32_t i = uint32_t(lane) + 64u * j;
+                        fresh = fresh || (i < I && C.frs[i] && C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]);
+                    }
+                    if (ballot(fresh)) admit_fresh_all(C, t, lane);
+                }
+                unsigned long long bat[OPL], cch[OPL];
 #pragma unroll
                 for (int j = 0; j < OPL; ++j) {
                     const uint32_t i = (uint32_t(lane) + 64u * j) * NW + uint32_t(wid);
-                    bool batch = false, fresh = false, cachd = false;
+                    bool batch = false, cachd = false;
                     if (i < I && C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]) {
                         const int nw = C.nwait[i];
                         const bool cached = C.td && C.qn[i] > 0;
-                        if (nw >= 2 && nw <= 64 && C.frs[i]) {
-                            fresh = true;
-                        } else if (nw >= 2 && nw <= 64 && !cached) {
+                        if (nw >= 2 && nw <= 64 && !cached) {
                             batch = true;
                         } else if (IM >= 128 && cached) {
                             // the kernels for 128+ instances admit a cached run at
@@ -1935,14 +2126,11 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         }
                     }
                     bat[j] = ballot(batch);
-                    frm[j] = ballot(fresh);
                     cch[j] = ballot(cachd);
                 }
                 wave_sync();
 #pragma unroll
                 for (int j = 0; j < OPL; ++j) {
-                    for (unsigned long long m = frm[j]; m; m &= m - 1)
-                        admit_fresh(C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane);
                     for (unsigned long long m = bat[j]; m; m &= m - 1)
                         admit_batch<(IM >= 128 ? 16 : 4)>(C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane);
                     for (unsigned long long m = cch[j]; m; m &= m - 1)
@@ -2062,9 +2250,12 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 bool full = false;
                 bool drain_mode = false;  // every instance with room is draining (Section 3.4 fallback)
                 int nfall = 0;
+                // (a burst's records are loaded one batch of 64 ahead)
+                unsigned long long a_bt = a0;
                 for (uint32_t k0 = 0; k0 < n; k0 += 64) {
                     const uint32_t cn = n - k0 < 64 ? n - k0 : 64;
-                    const unsigned long long a = k0 == 0 ? a0 : (lane < int(cn) ? rec[k0 + lane] : 0);
+                    const unsigned long long a = a_bt;
+                    if (n - k0 > 64) a_bt = k0 + 64 + lane < n ? rec[k0 + 64 + lane] : 0ull;
                     int tgt = -1, rank = 0;  // rank: among this batch's arrivals bound for tgt
                     uint32_t k = 0;
                     while (k < cn && !full) {
@@ -2142,6 +2333,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         k += uint32_t(m);
                     }
                     // write the dispatch state back for the slot assignment and later phases
+                    bool qc_any = false;
 #pragma unroll
                     for (int j = 0; j < IPL; ++j) {
                         const uint32_t i = lane + 64 * j;
@@ -2159,14 +2351,16 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         if (C.ext && nadd[j] > 0) wlb(C)[i] = t < wlb(C)[i] ? t : wlb(C)[i];
                         if (C.td && nadd[j] > 0) {
                             // queue cache: an arrival that became the head of line pushes
-                            // the old head to the front of the cache; other arrivals may
-                            // fall between cached entries, so the cache is emptied
-                            if (nadd[j] > (pend_r[j] >= 0 ? 1 : 0)) {
-                                C.qn[i] = 0;
-                                qx_clear(C, int(i));
-                            } else if (C.hols[i] >= 0) {
+                            // the old head to the front of the cache; the others enter it
+                            // once their slots are known (an empty queue's arrivals are
+                            // served by the list of this tick's placements)
+                            const bool known = C.hols[i] >= 0;
+                            const bool all = nw0 == (known ? 1 + C.qn[i] + qx_count(C, int(i)) : 0);
+                            const bool skip = !known && n <= uint32_t(kLast);
+                            C.order[i] = skip ? kQcSkip : (all ? kQcAll : kQcPart) | (pend_r[j] >= 0 ? kQcHead : 0);
+                            qc_any = qc_any || !skip;
+                            if (known && pend_r[j] >= 0)
                                 qc_insert_at(C, int(i), 0, qc_pack(C.holk[i], C.hols[i], C.hwd[i], C.hmt[i], C.hta[i]));
-                            }
                         }
                         nadd[j] = 0;
                         if (pend_r[j] >= 0) {
@@ -2253,6 +2447,53 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             C.hwd[tgt] = word;
                             C.hmt[tgt] = meta;
                             C.hta[tgt] = t;
+                        }
+                    }
+                    if (C.td && ballot(qc_any)) {
+                        // the arrivals behind a head of line enter its queue cache
+                        wave_sync();
+                        const uint32_t seq = seq0 + unsigned(a >> 36);
+                        const int mode = tgt >= 0 ? C.order[tgt] : kQcSkip;
+                        const int r = rank - ((mode & kQcHead) ? 1 : 0);  // among them; -1: the head of line
+                        const unsigned long long key = arr_key(C, tier, seq);
+                        const uint4 en = make_uint4(seq, kWaitW | (uint32_t((a >> 16) & 0xFFFFu) << 16) | uint32_t(a & 0xFFFFu),
+                                                    t, uint32_t(s) | (uint32_t(tier) << 12));
+                        const bool can = (mode & 3) != kQcSkip && r >= 0;
+                        int nq = 0, xc = 0, xh = 0;
+                        bool behind = true;  // larger than every cached entry
+                        if (can) {
+                            nq = C.qn[tgt];
+                            if (C.xn) { const int xv = C.xn[tgt]; xc = xv & 0xFFFF; xh = xv >> 16; }
+                            if (nq + xc > 0) {
+                                const uint4 le = xc > 0 ? *qx_at(C, tgt, xh, xc - 1) : C.qt[qc_at(C, tgt, nq - 1)];
+                                behind = key > qc_key(C, le);
+                            }
+                            // the first one behind a cache that lists the whole queue: all are
+                            if (r == 0 && behind && (mode & 3) == kQcAll) C.order[tgt] = mode | kQcRun;
+                        }
+                        wave_sync();
+                        const bool run = can && (C.order[tgt] & kQcRun);
+                        if (run) {
+                            // a run behind the cached entries, all at once (the ring fills
+                            // before the extension starts)
+                            if (xc == 0 && nq + r < C.td) {
+                                C.qt[qc_at(C, tgt, nq + r)] = en;
+                                atomicAdd(&C.qn[tgt], 1);
+                            } else if (C.xn) {
+                                const int k = xc > 0 ? xc + r : nq + r - C.td;
+                                if (k < C.xd) {
+                                    *qx_at(C, tgt, xh, k) = en;
+                                    atomicAdd(&C.xn[tgt], 1);
+                                }
+                            }
+                        }
+                        // the others one after the other (at most td + 1 of one instance
+                        // can have a place in its ring or fall into its extension)
+                        const bool enter = can && !run && r <= C.td &&
+                                           (!behind || (xc == 0 && nq < C.td && (mode & 3) == kQcAll));
+                        for (unsigned long long em = ballot(enter); em; em &= em - 1) {
+                            if (lane == ffs64(em)) qc_arrive(C, tgt, en);
+                            wave_sync();
                         }
                     }
                     // every arrival is dispatched (tgt >= 0) or rejected: no free slot
@@ -2510,6 +2751,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         }
                         const bool act = ds >= 0;
                         const int h = act ? C.hols[src] : kNoHol;
+                        bool deep = false;
+                        uint4 dq = make_uint4(0u, 0u, 0u, 0u);
                         if (act && h >= 0) {
                             // queued move of the source's head of line (fields cached in LDS)
                             const size_t dsb = size_t(dst) * S + ds, hb = size_t(src) * S + h;
@@ -2522,12 +2765,19 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             C.live[src] -= 1; C.nwait[src] -= 1;
                             C.live[dst] += 1; C.nwait[dst] += 1;
                             C.frs[src] = 0; C.frs[dst] = 0;
-                            hol_insert(C, dst, key, ds, hw, hm, ht);
+                            deep = hol_insert(C, dst, key, ds, hw, hm, ht);
+                            if (C.xn) dq = qc_pack(key, ds, hw, hm, ht);
                             hol_pop(C, src);
                             stat(C, kMigQueued, 1);
                             if (C.ext) wlb(C)[dst] = ht < wlb(C)[dst] ? ht : wlb(C)[dst];
                         }
                         wave_sync();
+                        if (C.xn) {
+                            for (unsigned long long dm = ballot(deep); dm; dm &= dm - 1) {
+                                const int l = ffs64(dm);
+                                qx_insert(C, rl(dst, l), make_uint4(rlu(dq.x, l), rlu(dq.y, l), rlu(dq.z, l), rlu(dq.w, l)), lane);
+                            }
+                        }
                         // staged copies: running candidate of largest tier, then fewest
                         // blocks, then newest
                         for (unsigned long long pm = ballot(act && h < 0); pm; pm &= pm - 1) {
@@ -2602,6 +2852,45 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
         block_sync<NW>();
     }
 }
+
+}  // namespace
+
+// The instantiations of the step kernel are compiled in eight translation
+// units (this file with MTS_STEP_PART = 0..7): bit 0 the INFaaS policy, bit 1
+// the Section 6.5 extensions, bit 2 the kernels for 128 or more instances.
+// Each gives the kernel for IM instances with (qc) or without a queue cache.
+#ifdef MTS_STEP_PART
+#define MTS_STEP_FN2(p) step_part_##p
+#define MTS_STEP_FN(p) MTS_STEP_FN2(p)
+namespace {
+template <bool QC>
+const void* step_of(uint32_t IM)
+{
+    constexpr bool INF = (MTS_STEP_PART & 1) != 0, EXT = (MTS_STEP_PART & 2) != 0;
+#if MTS_STEP_PART & 4
+    return IM == 128 ? reinterpret_cast<const void*>(&k_step<128, INF, EXT, QC>)
+                     : reinterpret_cast<const void*>(&k_step<256, INF, EXT, QC>);
+#else
+    return IM == 16   ? reinterpret_cast<const void*>(&k_step<16, INF, EXT, QC>)
+           : IM == 32 ? reinterpret_cast<const void*>(&k_step<32, INF, EXT, QC>)
+                      : reinterpret_cast<const void*>(&k_step<64, INF, EXT, QC>);
+#endif
+}
+}  // namespace
+const void* MTS_STEP_FN(MTS_STEP_PART)(uint32_t IM, bool qc) { return qc ? step_of<true>(IM) : step_of<false>(IM); }
+
+#else
+
+const void* step_part_0(uint32_t, bool);
+const void* step_part_1(uint32_t, bool);
+const void* step_part_2(uint32_t, bool);
+const void* step_part_3(uint32_t, bool);
+const void* step_part_4(uint32_t, bool);
+const void* step_part_5(uint32_t, bool);
+const void* step_part_6(uint32_t, bool);
+const void* step_part_7(uint32_t, bool);
+
+namespace {
 
 // ---------------------------------------------------------------------------
 // initial state: every slot empty, free = M, no migrations, zero counters
@@ -2719,38 +3008,18 @@ int launch_init(const Params& p, hipStream_t stream)
 
 namespace {
 
-template <bool INF, bool EXT>
-const void* step_fn_t(uint32_t I)
-{
-    switch (imax_for(I)) {
-    case 16: return reinterpret_cast<const void*>(&k_step<16, INF, EXT>);
-    case 32: return reinterpret_cast<const void*>(&k_step<32, INF, EXT>);
-    case 64: return reinterpret_cast<const void*>(&k_step<64, INF, EXT>);
-    case 128: return reinterpret_cast<const void*>(&k_step<128, INF, EXT>);
-    default: return reinterpret_cast<const void*>(&k_step<256, INF, EXT>);
-    }
-}
-
 // the kernels with the adaptive-headroom / promotion code are separate
 // instantiations, so that the others carry none of its registers
 bool ext_on(const Params& p) { return p.adapt_epoch != 0 || p.promo_period != 0; }
 
 const void* step_fn(const Params& p)
 {
-    if (p.policy == MTS_POLICY_INFAAS) return ext_on(p) ? step_fn_t<true, true>(p.I) : step_fn_t<true, false>(p.I);
-    return ext_on(p) ? step_fn_t<false, true>(p.I) : step_fn_t<false, false>(p.I);
-}
-
-template <bool INF, bool EXT>
-void launch_step_t(const Params& p, unsigned long long t0, uint32_t nt, uint32_t blocks, size_t lds, hipStream_t stream)
-{
-    switch (imax_for(p.I)) {
-    case 16: hipLaunchKernelGGL((k_step<16, INF, EXT>), dim3(blocks), dim3(64 * waves_for(16)), lds, stream, p, t0, nt); break;
-    case 32: hipLaunchKernelGGL((k_step<32, INF, EXT>), dim3(blocks), dim3(64 * waves_for(32)), lds, stream, p, t0, nt); break;
-    case 64: hipLaunchKernelGGL((k_step<64, INF, EXT>), dim3(blocks), dim3(64 * waves_for(64)), lds, stream, p, t0, nt); break;
-    case 128: hipLaunchKernelGGL((k_step<128, INF, EXT>), dim3(blocks), dim3(64 * waves_for(128)), lds, stream, p, t0, nt); break;
-    default: hipLaunchKernelGGL((k_step<256, INF, EXT>), dim3(blocks), dim3(64 * waves_for(256)), lds, stream, p, t0, nt); break;
-    }
+    using Part = const void* (*)(uint32_t, bool);
+    static constexpr Part parts[8] = {step_part_0, step_part_1, step_part_2, step_part_3,
+                                      step_part_4, step_part_5, step_part_6, step_part_7};
+    const uint32_t IM = imax_for(p.I);
+    const int k = (p.policy == MTS_POLICY_INFAAS ? 1 : 0) | (ext_on(p) ? 2 : 0) | (IM >= 128 ? 4 : 0);
+    return parts[k](IM, p.qdepth != 0);
 }
 
 size_t step_lds(const Params& p)
@@ -2782,13 +3051,10 @@ int step_blocks_per_cu(const Params& p)
 int launch_step(const Params& p, unsigned long long t0, uint32_t nt, uint32_t blocks, hipStream_t stream)
 {
     const size_t lds = step_lds(p);
-    if (p.policy == MTS_POLICY_INFAAS) {
-        if (ext_on(p)) launch_step_t<true, true>(p, t0, nt, blocks, lds, stream);
-        else launch_step_t<true, false>(p, t0, nt, blocks, lds, stream);
-    } else {
-        if (ext_on(p)) launch_step_t<false, true>(p, t0, nt, blocks, lds, stream);
-        else launch_step_t<false, false>(p, t0, nt, blocks, lds, stream);
-    }
+    Params q = p;
+    void* args[] = {&q, &t0, &nt};
+    const hipError_t rc = hipLaunchKernel(step_fn(p), dim3(blocks), dim3(uint32_t(step_threads(p))), args, lds, stream);
+    if (rc != hipSuccess) { (void)hipGetLastError(); return int(rc); }
     return int(hipGetLastError());
 }
 
@@ -2804,5 +3070,7 @@ int launch_digest(const Params& p, uint32_t r0, uint32_t nr, uint32_t tick, hipS
     hipLaunchKernelGGL(k_digest, dim3(nr), dim3(256), 0, stream, p, r0, tick);
     return int(hipGetLastError());
 }
+
+#endif  // MTS_STEP_PART
 
 }  // namespace mts

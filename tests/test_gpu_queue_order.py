@@ -1,0 +1,81 @@
+"""The order kept behind each head of line (the LDS queue cache and, for more
+than 64 instances, its extension in the state buffer) under everything that
+enters a queue: runs of arrivals on empty and on non-empty queues, preempted
+and migrated requests that fall inside the kept order, rings that overflow.
+Bit-exact against the oracle; the kept order is a performance structure and
+must never change a result."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from workloads import preset  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # collected on CPU-only hosts, never run there
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2608_16336_amd import Scheduler  # noqa: E402
+
+
+def _cfg(I, S, M, arrival, K=10, blind=0, interval=1, out=40.0, infaas=False):
+    c = preset("tiny")
+    c.update(n_instances=I, slots_per_instance=S, kv_blocks=M, headroom_base=M / 8.0, headroom_decay=0.7, mig_interval=interval,
+             mig_max_pairs=I // 2, mig_stage_blocks=4, arrival=arrival, prompt=dict(kind="uniform_int", lo=16, hi=600),
+             output=dict(kind="geometric", mean=out), groups=[dict(n_replicas=2, K=K, tiers=dict(kind="uniform"))], seed=77)
+    if blind:
+        c["tier_blind"] = 1
+    if infaas:
+        c["dispatch"] = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
+    return c
+
+
+POISSON = dict(kind="poisson", mean=14.0)
+BURSTS = dict(kind="gamma_poisson", mean=30.0, cv=3.0)
+WIDE_BURSTS = dict(kind="gamma_poisson", mean=120.0, cv=3.0)
+
+
+@pytest.mark.parametrize("cfg,depths", [
+    # short queues on few instances; the ring fills, overflows and drains
+    (_cfg(3, 128, 500, POISSON), (0, 1, 2, 7, 15)),
+    (_cfg(17, 64, 260, BURSTS), (1, 3, 7)),
+    (_cfg(33, 192, 400, BURSTS, K=3), (0, 3, 7)),
+    (_cfg(64, 64, 300, dict(kind="gamma_poisson", mean=60.0, cv=2.0)), (3, 7)),
+    # one tier or tier-blind: every arrival follows the kept order
+    (_cfg(5, 192, 400, BURSTS, K=1), (1, 7)),
+    (_cfg(16, 128, 300, BURSTS, blind=1), (3, 7)),
+    (_cfg(16, 128, 300, POISSON, infaas=True), (1, 7)),
+    # the eight-wave kernels: piles beyond the ring go on in the extension,
+    # preempted and migrated requests enter it in the middle
+    (_cfg(65, 256, 420, WIDE_BURSTS), (1, 7, 15)),
+    (_cfg(130, 1024, 900, WIDE_BURSTS, out=120.0), (0, 3, 11)),
+    (_cfg(256, 2048, 1500, dict(kind="gamma_poisson", mean=300.0, cv=4.0), interval=2, out=200.0), (3, 11)),
+])
+def test_kept_queue_order_never_changes_a_result(cfg, depths):
+    ticks = 160
+    o = oracle.Oracle(cfg)
+    o.step(ticks)
+    want = o.export()
+    for depth in depths:
+        g = Scheduler(cfg)
+        g.queue_cache = depth
+        g.step(ticks - 41)
+        g.step(41)
+        got = g.export()
+        for k in want:
+            assert np.array_equal(got[k], want[k]), "I=%d depth %d field %s" % (cfg["n_instances"], depth, k)
+        assert g.stats()["raw"][86] == 0
+    # the workload reaches what it is there for
+    st = want["stats"].reshape(2, -1)[:, :80].reshape(2, 10, 8)
+    assert st[:, :, 5].sum() > 0 or cfg["n_instances"] > 64
+
+
+def test_depth_is_kept_where_every_replica_stays_resident():
+    # 960 replicas of 32 instances: a cache fits beside them all
+    cfg = preset("sweep")
+    for grp in cfg["groups"]:
+        grp["n_replicas"] = 32
+    g = Scheduler(cfg)
+    assert g.queue_cache > 0
