@@ -138,6 +138,15 @@ Layout make_layout(const mts_cfg& c, const Tables& T, uint32_t R, uint32_t chunk
     L.wheel = o;    o = up256(o + size_t(R) * wsz * wcap * 4);
     // the queue cache's extension, for the kernels of more than 64 instances
     L.qx = o;       o = up256(o + (I > 64 ? size_t(R) * I * qx_depth(R, I, S) * 16 : 0));
+    // the step kernel's LDS between launches, with room for the deepest queue
+    // cache that mts_create picks
+    {
+        const size_t lds = lds_bytes(c.n_instances, c.slots_per_instance, c.block_tokens, wsz, c.dispatch_policy,
+                                     I >= 128 ? 15 : 7, c.adapt_epoch != 0 || c.promote_period != 0);
+        const size_t n = lds / 16 + 1;
+        L.img_n = size_t(R) * n * 16 <= kImgBudget ? uint32_t(n) : 0;
+    }
+    L.img = o;      o = up256(o + size_t(R) * L.img_n * 16);
     L.total = o;
     return L;
 }
@@ -214,6 +223,8 @@ Params make_params(const mts_ctx* h)
     p.wheel = reinterpret_cast<uint32_t*>(d + L.wheel);
     p.qx = h->I > 64 ? reinterpret_cast<uint4*>(d + L.qx) : nullptr;
     p.qxd = qx_depth(h->R, h->I, h->S);
+    p.img = L.img_n ? reinterpret_cast<uint4*>(d + L.img) : nullptr;
+    p.img_n = L.img_n;
     return p;
 }
 
@@ -684,6 +695,9 @@ int mts_import_state(mts_handle h, uint32_t r0, uint32_t nr, const mts_state_vie
     }
     const Layout& L = h->lay;
     hipError_t e = hipStreamSynchronize(h->last);
+    // the replicas' summaries are built afresh from the new slots
+    if (e == hipSuccess && launch_void_images(make_params(h), r0, nr, h->last) != 0) return MTS_EDEVICE;
+    if (e == hipSuccess) e = hipStreamSynchronize(h->last);
     auto put = [&](size_t off, const void* src, size_t n) {
         if (e == hipSuccess && n) e = hipMemcpy(h->dev + off, src, n, hipMemcpyHostToDevice);
     };

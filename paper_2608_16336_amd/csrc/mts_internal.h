@@ -67,6 +67,8 @@ struct Layout {
     size_t arr_cnt, arr_rec;                                            // [R][chunk], [R][chunk][cap]
     size_t wheel;                                                       // [R][wsz][wcap]
     size_t qx;                                                          // [R][I][qx_depth] uint4 (I > 64 only)
+    size_t img;                                                         // [R][img_n] uint4, LDS images (img_n 0: none)
+    uint32_t img_n;
     size_t total;
 };
 
@@ -77,6 +79,8 @@ struct Layout {
 // selection).
 constexpr uint32_t kQxLeast = 64;
 constexpr size_t kQxBudget = size_t(8) << 30;
+// LDS images of the replicas are kept between launches up to this many bytes
+constexpr size_t kImgBudget = size_t(8) << 30;
 inline uint32_t qx_depth(size_t R, size_t I, size_t S)
 {
     return R * I * S * 16 <= kQxBudget ? uint32_t(S) : kQxLeast;
@@ -130,6 +134,8 @@ struct Params {
     uint32_t* wheel;
     uint4* qx;                     // [R][I][qxd] queue cache extension (I > 64; null otherwise)
     uint32_t qxd;                  // its entries per instance
+    uint4* img;                    // [R][img_n] header and LDS of each replica after its last launch (or null)
+    uint32_t img_n, img_lds;       // uint4 per image; LDS bytes of this launch
 };
 
 // LDS bytes of one wave (one replica) of the step kernel
@@ -145,6 +151,7 @@ int launch_step(const Params& p, unsigned long long t0, uint32_t nt, uint32_t bl
 int step_blocks_per_cu(const Params& p);
 int step_threads(const Params& p);
 int launch_digest(const Params& p, uint32_t r0, uint32_t nr, uint32_t tick, hipStream_t stream);
+int launch_void_images(const Params& p, uint32_t r0, uint32_t nr, hipStream_t stream);
 int launch_shift_clock(const Params& p, uint32_t delta, hipStream_t stream);
 
 // static device scratch of mts_step_noalloc (mts_noalloc.hip): its size, the

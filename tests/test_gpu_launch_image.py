@@ -1,0 +1,98 @@
+"""Step launches take up the summaries that the last launch left; whatever
+changes the state, the clock or the layout in between makes them start from
+the slots again.  Bit-exact against the oracle through every such call."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from workloads import scaled, with_extensions  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # collected on CPU-only hosts, never run there
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2608_16336_amd import Scheduler  # noqa: E402
+
+INFAAS = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
+
+
+def _cfg(name, **kw):
+    c = scaled(name, replicas_per_group=3)
+    c["groups"] = [dict(c["groups"][0], n_replicas=3)]
+    c["arrival"]["mean"] *= kw.pop("load", 1.0)
+    if kw.pop("ext", False):
+        c = with_extensions(c)
+    c.update(kw)
+    return c
+
+
+def _same(g, orc, what):
+    for r, o in enumerate(orc):
+        a, b = g.export(r, 1), o.export()
+        for k in b:
+            assert np.array_equal(a[k], b[k]), "%s: replica %d field %s" % (what, r, k)
+
+
+@pytest.mark.parametrize("cfg", [
+    _cfg("tiny", load=2.0), _cfg("enterprise", load=1.5), _cfg("gauss10", ext=True), _cfg("sweep", load=2.5),
+    _cfg("enterprise", load=1.3, dispatch=INFAAS, tier_blind=1), _cfg("wide"), _cfg("wide", ext=True),
+], ids=["tiny", "enterprise", "gauss10_ext", "sweep", "infaas_blind", "wide", "wide_ext"])
+def test_launches_resume_through_every_change_of_state(cfg):
+    g = Scheduler(cfg)
+    orc = [oracle.Oracle(cfg, r, 1) for r in range(g.R)]
+    I = cfg["n_instances"]
+
+    def step(n, noalloc=False):
+        (g.step_noalloc if noalloc else g.step)(n)
+        for o in orc:
+            o.step(n)
+
+    step(60)
+    step(1)
+    step(7)
+    _same(g, orc, "short steps")
+    flags = np.zeros((g.R, I), np.uint8)
+    flags[:, :max(1, I // 4)] = 1
+    g.set_draining(flags)
+    for o in orc:
+        for i in range(max(1, I // 4)):
+            o.set_drain(0, i, True)
+    step(6)
+    _same(g, orc, "draining")
+    # one replica takes another's state, the others go on from their images
+    saved = g.export(0, 1)
+    g.import_state(saved, 1, 1)
+    orc[1].import_state(saved)
+    step(5)
+    _same(g, orc, "one replica imported")
+    depth = g.queue_cache
+    g.queue_cache = 1
+    step(4)
+    g.queue_cache = depth
+    step(3)
+    _same(g, orc, "queue cache depth changed")
+    g.set_wheel_cap(max(1, g.wheel()[1] // 8))
+    step(9)
+    _same(g, orc, "wheel capacity changed")
+    t = g.tick
+    g.tick = t + 1000
+    g.tick = t
+    step(2)
+    step(3, noalloc=True)
+    step(2)
+    _same(g, orc, "clock moved back and forth")
+    # a launch that starts again at an earlier tick's state
+    saved = [g.export(r, 1) for r in range(g.R)]
+    step(8)
+    for r in range(g.R):
+        g.import_state(saved[r], r, 1)
+        orc[r].import_state(saved[r])
+    g.tick = t + 7
+    for o in orc:
+        o.tick = t + 7
+    step(8)
+    _same(g, orc, "rewound")
+    assert g.stats()["raw"][86] == 0
