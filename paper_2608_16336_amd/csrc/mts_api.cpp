@@ -579,16 +579,27 @@ int mts_stats(mts_handle h, mts_stats_t* out)
 
 namespace {
 
-// canonical len | rem << 16 of a slot word at the next tick to run
-uint32_t word_to_lr(uint32_t w, uint64_t tick)
+// Canonical slot arrays pass through the arrival staging of the handle's
+// buffer (free between steps: every step samples its arrivals afresh) in
+// slices of n slots: a flag word, len/rem, seq, arrival tick, meta.
+struct SlotSlice {
+    uint32_t n;  // slots per slice, a multiple of 64
+    uint32_t *bad, *lr, *seq, *tarr;
+    uint8_t* meta;
+};
+
+SlotSlice slot_slice(mts_handle h)
 {
-    const uint32_t st = w >> 30, lo = w & 0xFFFFu, mid = (w >> 16) & 0x3FFFu;
-    if (st == kWaiting) return lo | (mid << 16);
-    if (st == kRunning) {
-        const uint32_t rem = (mid - uint32_t(tick) + 1u) & 0x3FFFu;
-        return (lo - rem) | (rem << 16);
-    }
-    return 0;
+    const size_t avail = size_t(h->R) * h->chunk * h->arr_cap * 8;
+    char* d = h->dev + h->lay.arr_rec;
+    SlotSlice s;
+    s.n = uint32_t(std::min<size_t>((avail - 256) / 13 / 64 * 64, size_t(1) << 26));
+    s.bad = reinterpret_cast<uint32_t*>(d);
+    s.lr = reinterpret_cast<uint32_t*>(d + 256);
+    s.seq = s.lr + s.n;
+    s.tarr = s.seq + s.n;
+    s.meta = reinterpret_cast<uint8_t*>(s.tarr + s.n);
+    return s;
 }
 
 }  // namespace
@@ -603,21 +614,25 @@ int mts_export_state(mts_handle h, uint32_t r0, uint32_t nr, const mts_state_vie
     auto get = [&](void* dst, size_t off, size_t n) {
         if (e == hipSuccess && dst && n) e = hipMemcpy(dst, h->dev + off, n, hipMemcpyDeviceToHost);
     };
-    // slot records {word, meta, seq, arrival tick}; the device marks an empty
-    // slot by its word alone, and an inbound reservation by its word and
-    // meta; their other fields are zero in the canonical state
+    // slot records to the canonical arrays, on the device
     if (v->lr || v->meta || v->seq || v->tarr) {
-        std::vector<uint32_t> rec(size_t(nr) * IS * 4);
-        get(rec.data(), L.slot + size_t(r0) * IS * 16, rec.size() * 4);
-        if (e == hipSuccess)
-            for (size_t k = 0; k < size_t(nr) * IS; ++k) {
-                const uint32_t w = rec[4 * k], st = w >> 30;
-                const bool gone = w == 0 || st == kInbound;
-                if (v->lr) v->lr[k] = word_to_lr(w, h->tick);
-                if (v->meta) v->meta[k] = w == 0 ? 0 : uint8_t(rec[4 * k + 1]);
-                if (v->seq) v->seq[k] = gone ? 0 : rec[4 * k + 2];
-                if (v->tarr) v->tarr[k] = gone ? 0 : rec[4 * k + 3];
-            }
+        const Params p = make_params(h);
+        const SlotSlice sl = slot_slice(h);
+        const size_t N = size_t(nr) * IS;
+        for (size_t f = 0; f < N && e == hipSuccess; f += sl.n) {
+            const uint32_t n = uint32_t(std::min<size_t>(sl.n, N - f));
+            if (launch_pack(p, size_t(r0) * IS + f, n, uint32_t(h->tick), v->meta ? sl.meta : nullptr, v->lr ? sl.lr : nullptr,
+                            v->seq ? sl.seq : nullptr, v->tarr ? sl.tarr : nullptr, h->last) != 0)
+                return MTS_EDEVICE;
+            auto down = [&](void* dst, const void* src, size_t bytes) {
+                if (e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, h->last);
+            };
+            if (v->meta) down(v->meta + f, sl.meta, n);
+            if (v->lr) down(v->lr + f, sl.lr, size_t(n) * 4);
+            if (v->seq) down(v->seq + f, sl.seq, size_t(n) * 4);
+            if (v->tarr) down(v->tarr + f, sl.tarr, size_t(n) * 4);
+            if (e == hipSuccess) e = hipStreamSynchronize(h->last);
+        }
     }
     get(v->free, L.freeb + size_t(r0) * I * 4, size_t(nr) * I * 4);
     get(v->mig, L.mig + size_t(r0) * I * 16, size_t(nr) * I * 16);
@@ -648,32 +663,10 @@ int mts_import_state(mts_handle h, uint32_t r0, uint32_t nr, const mts_state_vie
         return MTS_EINVAL;
     if (r0 > h->R || nr > h->R - r0) return MTS_ERANGE;
     const size_t IS = size_t(h->I) * h->S, I = h->I;
-    std::vector<uint32_t> w(size_t(nr) * IS);
-    std::vector<uint32_t> rec(size_t(nr) * IS * 4);
     // structural checks keep every index the kernel derives from the state in
-    // range; running requests are re-encoded relative to the handle's tick
+    // range (the slots' are made on the device, below)
     for (uint32_t r = 0; r < nr; ++r) {
         const uint32_t K = h->group_K[h->group_of[r0 + r]];
-        for (size_t s = 0; s < IS; ++s) {
-            const size_t k = size_t(r) * IS + s;
-            const uint8_t m = v->meta[k];
-            const uint32_t st = m & 3u, lr = v->lr[k], len = lr & 0xFFFFu, rem = lr >> 16;
-            if (st == kEmpty) {
-                if (m != 0) return MTS_EINVAL;
-                w[k] = 0;
-            } else if (st == kInbound) {
-                w[k] = 3u << 30;
-            } else {
-                if (((m >> 2) & 15u) >= K || len == 0 || rem == 0 || rem > kMaxOutput) return MTS_EINVAL;
-                if (st == kWaiting) {
-                    w[k] = (1u << 30) | (rem << 16) | len;
-                } else {
-                    if (len + rem > 65535u) return MTS_EINVAL;
-                    const uint32_t fin = uint32_t(h->tick) - 1u + rem;
-                    w[k] = (2u << 30) | ((fin & 0x3FFFu) << 16) | (len + rem);
-                }
-            }
-        }
         for (size_t i = 0; i < I; ++i) {
             const int32_t* m = v->mig + (size_t(r) * I + i) * 4;
             if (m[0] < -1 || m[0] >= int32_t(I) || m[0] == int32_t(i)) return MTS_EINVAL;
@@ -695,19 +688,48 @@ int mts_import_state(mts_handle h, uint32_t r0, uint32_t nr, const mts_state_vie
     }
     const Layout& L = h->lay;
     hipError_t e = hipStreamSynchronize(h->last);
-    // the replicas' summaries are built afresh from the new slots
-    if (e == hipSuccess && launch_void_images(make_params(h), r0, nr, h->last) != 0) return MTS_EDEVICE;
-    if (e == hipSuccess) e = hipStreamSynchronize(h->last);
+    // the slots: checked first, all of them, then re-encoded relative to the
+    // handle's tick (a state of one slice is uploaded once)
+    {
+        const Params p = make_params(h);
+        const SlotSlice sl = slot_slice(h);
+        const size_t N = size_t(nr) * IS;
+        auto up = [&](void* dst, const void* src, size_t bytes) {
+            if (e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, h->last);
+        };
+        uint32_t bad = 0;
+        up(sl.bad, &bad, 4);
+        for (size_t f = 0; f < N && e == hipSuccess; f += sl.n) {
+            const uint32_t n = uint32_t(std::min<size_t>(sl.n, N - f));
+            up(sl.meta, v->meta + f, n);
+            up(sl.lr, v->lr + f, size_t(n) * 4);
+            if (e == hipSuccess && launch_check_slots(p, size_t(r0) * IS + f, n, sl.meta, sl.lr, sl.bad, h->last) != 0)
+                return MTS_EDEVICE;
+            if (e == hipSuccess && f + n < N) e = hipStreamSynchronize(h->last);
+        }
+        if (e == hipSuccess) e = hipMemcpyAsync(&bad, sl.bad, 4, hipMemcpyDeviceToHost, h->last);
+        if (e == hipSuccess) e = hipStreamSynchronize(h->last);
+        if (e != hipSuccess) return MTS_EDEVICE;
+        if (bad) return MTS_EINVAL;
+        // the replicas' summaries are built afresh from the new slots
+        if (launch_void_images(p, r0, nr, h->last) != 0) return MTS_EDEVICE;
+        for (size_t f = 0; f < N && e == hipSuccess; f += sl.n) {
+            const uint32_t n = uint32_t(std::min<size_t>(sl.n, N - f));
+            if (N > sl.n) {
+                up(sl.meta, v->meta + f, n);
+                up(sl.lr, v->lr + f, size_t(n) * 4);
+            }
+            up(sl.seq, v->seq + f, size_t(n) * 4);
+            up(sl.tarr, v->tarr + f, size_t(n) * 4);
+            if (e == hipSuccess &&
+                launch_unpack(p, size_t(r0) * IS + f, n, uint32_t(h->tick), sl.meta, sl.lr, sl.seq, sl.tarr, h->last) != 0)
+                return MTS_EDEVICE;
+            if (e == hipSuccess) e = hipStreamSynchronize(h->last);
+        }
+    }
     auto put = [&](size_t off, const void* src, size_t n) {
         if (e == hipSuccess && n) e = hipMemcpy(h->dev + off, src, n, hipMemcpyHostToDevice);
     };
-    for (size_t k = 0; k < w.size(); ++k) {
-        rec[4 * k] = w[k];
-        rec[4 * k + 1] = v->meta[k];
-        rec[4 * k + 2] = v->seq[k];
-        rec[4 * k + 3] = v->tarr[k];
-    }
-    put(L.slot + size_t(r0) * IS * 16, rec.data(), rec.size() * 4);
     put(L.freeb + size_t(r0) * I * 4, v->free, size_t(nr) * I * 4);
     put(L.mig + size_t(r0) * I * 16, v->mig, size_t(nr) * I * 16);
     put(L.next_seq + size_t(r0) * 4, v->next_seq, size_t(nr) * 4);

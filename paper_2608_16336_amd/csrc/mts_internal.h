@@ -151,6 +151,12 @@ int launch_step(const Params& p, unsigned long long t0, uint32_t nt, uint32_t bl
 int step_blocks_per_cu(const Params& p);
 int step_threads(const Params& p);
 int launch_digest(const Params& p, uint32_t r0, uint32_t nr, uint32_t tick, hipStream_t stream);
+int launch_pack(const Params& p, size_t f0, uint32_t n, uint32_t tick, uint8_t* meta, uint32_t* lr, uint32_t* seq,
+                uint32_t* tarr, hipStream_t stream);
+int launch_check_slots(const Params& p, size_t f0, uint32_t n, const uint8_t* meta, const uint32_t* lr, uint32_t* bad,
+                       hipStream_t stream);
+int launch_unpack(const Params& p, size_t f0, uint32_t n, uint32_t tick, const uint8_t* meta, const uint32_t* lr,
+                  const uint32_t* seq, const uint32_t* tarr, hipStream_t stream);
 int launch_void_images(const Params& p, uint32_t r0, uint32_t nr, hipStream_t stream);
 int launch_shift_clock(const Params& p, uint32_t delta, hipStream_t stream);
 

@@ -3126,6 +3126,89 @@ int launch_shift_clock(const Params& p, uint32_t delta, hipStream_t stream)
     return int(hipGetLastError());
 }
 
+// ---------------------------------------------------------------------------
+// slot records to the canonical arrays of mts_export_state and back: f0 and
+// f the handle's flat slot index.  Streaming passes of 16 + 13 bytes per slot;
+// the host's loops over the same slots took most of a checkpoint's time.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_pack(Params P, size_t f0, uint32_t n, uint32_t tick, uint8_t* meta, uint32_t* lr,
+                                              uint32_t* seq, uint32_t* tarr)
+{
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
+        const uint4 rec = P.slot[f0 + j];
+        const uint32_t w = rec.x;
+        // an empty slot's other fields and an inbound reservation's seq and
+        // arrival tick are zero in the canonical state
+        const bool gone = w == 0 || wst(w) == kInbound;
+        if (lr) lr[j] = canonical_lr(w, tick);
+        if (meta) meta[j] = w == 0 ? 0 : uint8_t(rec.y);
+        if (seq) seq[j] = gone ? 0 : rec.z;
+        if (tarr) tarr[j] = gone ? 0 : rec.w;
+    }
+}
+
+// sets *bad when a slot breaks a limit that keeps every index the step kernel
+// derives from the state in range
+__global__ __launch_bounds__(256) void k_check_slots(Params P, size_t f0, uint32_t n, const uint8_t* meta, const uint32_t* lr,
+                                                     uint32_t* bad)
+{
+    const uint32_t IS = P.I * P.S, stride = gridDim.x * blockDim.x;
+    bool b = false;
+    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
+        const uint32_t m = meta[j], st = m & 3u, len = lr[j] & 0xFFFFu, rem = lr[j] >> 16;
+        if (st == kEmpty) {
+            b = b || m != 0;
+        } else if (st != kInbound) {
+            const uint32_t K = P.group_K32[P.group_of[(f0 + j) / IS]];
+            b = b || ((m >> 2) & 15u) >= K || len == 0 || rem == 0 || rem > kMaxOutput;
+            if (st == kRunning) b = b || len + rem > 65535u;
+        }
+    }
+    if (b) atomicOr(bad, 1u);
+}
+
+// running requests are re-encoded relative to tick
+__global__ __launch_bounds__(256) void k_unpack(Params P, size_t f0, uint32_t n, uint32_t tick, const uint8_t* meta,
+                                                const uint32_t* lr, const uint32_t* seq, const uint32_t* tarr)
+{
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
+        const uint32_t m = meta[j], st = m & 3u, len = lr[j] & 0xFFFFu, rem = lr[j] >> 16;
+        uint32_t w = 0;
+        if (st == kInbound) w = kInbW;
+        else if (st == kWaiting) w = kWaitW | (rem << 16) | len;
+        else if (st == kRunning) w = kRunW | (((tick - 1u + rem) & kFin) << 16) | (len + rem);
+        P.slot[f0 + j] = make_uint4(w, m, seq[j], tarr[j]);
+    }
+}
+
+namespace {
+dim3 slot_grid(uint32_t n) { return dim3((n + 1023) / 1024 < 2048 ? (n + 1023) / 1024 : 2048); }
+}  // namespace
+
+int launch_pack(const Params& p, size_t f0, uint32_t n, uint32_t tick, uint8_t* meta, uint32_t* lr, uint32_t* seq,
+                uint32_t* tarr, hipStream_t stream)
+{
+    if (n == 0) return 0;
+    hipLaunchKernelGGL(k_pack, slot_grid(n), dim3(256), 0, stream, p, f0, n, tick, meta, lr, seq, tarr);
+    return int(hipGetLastError());
+}
+int launch_check_slots(const Params& p, size_t f0, uint32_t n, const uint8_t* meta, const uint32_t* lr, uint32_t* bad,
+                       hipStream_t stream)
+{
+    if (n == 0) return 0;
+    hipLaunchKernelGGL(k_check_slots, slot_grid(n), dim3(256), 0, stream, p, f0, n, meta, lr, bad);
+    return int(hipGetLastError());
+}
+int launch_unpack(const Params& p, size_t f0, uint32_t n, uint32_t tick, const uint8_t* meta, const uint32_t* lr,
+                  const uint32_t* seq, const uint32_t* tarr, hipStream_t stream)
+{
+    if (n == 0) return 0;
+    hipLaunchKernelGGL(k_unpack, slot_grid(n), dim3(256), 0, stream, p, f0, n, tick, meta, lr, seq, tarr);
+    return int(hipGetLastError());
+}
+
 // voids the images of replicas [r0, r0 + nr)
 __global__ void k_void_images(Params P, uint32_t r0, uint32_t nr)
 {

@@ -15,6 +15,7 @@ if not torch.cuda.is_available():  # collected on CPU-only hosts, never run ther
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from paper_2608_16336_amd import Scheduler  # noqa: E402
+from paper_2608_16336_amd.mts import MtsError  # noqa: E402
 
 INFAAS = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
 
@@ -96,3 +97,48 @@ def test_launches_resume_through_every_change_of_state(cfg):
     step(8)
     _same(g, orc, "rewound")
     assert g.stats()["raw"][86] == 0
+
+
+def test_checkpoint_larger_than_one_slice_of_the_staging():
+    # few sampled arrivals leave a staging area far smaller than the slots, so
+    # the canonical arrays pass in many slices; the last one is partial
+    c = _cfg("tiny", n_instances=61, slots_per_instance=576, mig_max_pairs=30)
+    c["arrival"]["mean"] = 0.05
+    c["groups"] = [dict(c["groups"][0], n_replicas=2)]
+    g = Scheduler(c)
+    orc = [oracle.Oracle(c, r, 1) for r in range(2)]
+    rng = np.random.RandomState(5)
+    st = g.export()
+    N = 61 * 576
+    # requests all over the slots (waiting, lengths and tiers at random)
+    for r in range(2):
+        at = rng.choice(N, 3000, replace=False) + r * N
+        at[-1] = (r + 1) * N - 1
+        at = np.unique(at)
+        st["meta"][at] = 1 | (rng.randint(0, 2, len(at)) << 2)
+        st["lr"][at] = rng.randint(1, 900, len(at)) | (rng.randint(1, 300, len(at)) << 16)
+        st["seq"][at] = rng.permutation(len(at))
+        st["next_seq"][r] = len(at)
+    g.import_state(st)
+    for k, v in g.export().items():
+        assert np.array_equal(v, st[k]), k
+    n = {k: len(v) // 2 for k, v in st.items()}
+    for r, o in enumerate(orc):
+        o.import_state({k: v[r * n[k]:(r + 1) * n[k]] for k, v in st.items()})
+        o.step(20)
+    g.step(20)
+    _same(g, orc, "after the import")
+    # a bad slot in the last slice refuses the whole state and changes nothing
+    before = g.export()
+    bad = {k: v.copy() for k, v in before.items()}
+    bad["meta"][2 * N - 1] = 1 | (9 << 2)
+    bad["seq"][0] ^= 1
+    with pytest.raises(MtsError) as e:
+        g.import_state(bad)
+    assert e.value.code == -1
+    for k, v in g.export().items():
+        assert np.array_equal(v, before[k]), k
+    g.step(5)
+    for o in orc:
+        o.step(5)
+    _same(g, orc, "after the refused import")
