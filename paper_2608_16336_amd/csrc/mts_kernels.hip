@@ -41,7 +41,7 @@ constexpr int kTiers = MTS_MAX_TIERS;
 constexpr unsigned long long kNone = ~0ull;
 constexpr uint32_t kWaitW = 1u << 30, kRunW = 2u << 30, kInbW = 3u << 30;
 constexpr uint32_t kFin = 0x3FFFu;
-constexpr int kNoHol = -1, kHolUnknown = -2, kHolPending = -3;
+constexpr int kNoHol = -1, kHolUnknown = -2;
 constexpr int kFlagAbort = 1, kFlagBusy = 2, kFlagIntf = 4;
 
 __device__ __forceinline__ uint32_t wst(uint32_t v) { return v >> 30; }
@@ -51,7 +51,7 @@ __device__ __forceinline__ uint32_t wmid(uint32_t v) { return (v >> 16) & kFin; 
 // ---------------------------------------------------------------------------
 // LDS of one wave (one replica)
 // ---------------------------------------------------------------------------
-constexpr int kInts = 20;
+constexpr int kInts = 18;
 // placements of the previous tick's dispatch kept in LDS (at most one wave's worth)
 constexpr int kLast = 64;
 // requests preempted in the current tick, listed for the prefetched finish visit
@@ -63,7 +63,7 @@ enum { kXSlo = 0, kXAge = 10, kXPromoMin = 20, kXPromoPeriod, kXAdaptEpoch, kXAd
 static_assert(kXWords == MTS_EXT_WORDS, "extension table size");
 
 struct LdsLayout {
-    uint32_t stats, occ, holk, fd, ints, res, tcnt, mig, last, vic, wc, wov, inf, qt, qn, xn, ext, blk, rsel, total;
+    uint32_t stats, occ, holk, fd, ht, ints, res, tcnt, mig, last, vic, wc, wov, inf, qt, qn, xn, ext, blk, rsel, total;
 };
 
 // Waves per replica: the kernels for 128 or more instances run a workgroup of
@@ -90,6 +90,7 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     L.stats = o; o += kNstat * 8;
     L.holk = o;  o += IM * 8;
     L.fd = o;    o += IM * 8;
+    L.ht = o;    o += 64 * 4;
     L.ints = o;  o += IM * kInts * 4;
     L.tcnt = o;  o += IM * kTiers / 2 * 4;
     L.mig = o;   o += IM * 16;
@@ -134,8 +135,9 @@ struct Ctx {
     unsigned long long* stats;
     unsigned long long* occ;   // [I][W] slot not empty
     unsigned long long* holk;  // [I] head-of-line key tier << 32 | seq
-    double* fd;                // [I] freeness num / den (exact order for S <= 2048)
-    int *freeb, *B, *live, *nwait, *hols, *hold, *num, *den, *held, *inb, *tmask, *flags, *gtmp, *order, *pend;
+    double* fd;                // [I] freeness num / max(B, 1) (exact order for S <= 2048)
+    int* ht;                   // [64] headroom sums: [m] of tiers 0-4 in mask m, [32 + m] of tiers 5-9
+    int *freeb, *B, *live, *nwait, *hols, *hold, *num, *held, *inb, *tmask, *flags, *gtmp, *order;
     int* drn;                  // [I] draining (infinite virtual-usage sentinel)
     int* frs;                  // [I] 1: every waiting request was placed by the previous tick's dispatch
     unsigned *lw, *lsl, *lsq;  // [kLast] previous tick's placements in dispatch order: slot word,
@@ -184,7 +186,6 @@ struct Ctx {
     uint32_t wmask, wcap;
     uint4* slot;               // [I][S] slot records of this replica
     uint32_t I, S, W, RB, shift, bmask, M, K;
-    int hq[kTiers];
 };
 
 // Section 6.5 extension state in LDS, at fixed offsets from C.ext: the
@@ -222,6 +223,7 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.occ = reinterpret_cast<unsigned long long*>(base + Y.occ);
     C.holk = reinterpret_cast<unsigned long long*>(base + Y.holk);
     C.fd = reinterpret_cast<double*>(base + Y.fd);
+    C.ht = reinterpret_cast<int*>(base + Y.ht);
     int* p = reinterpret_cast<int*>(base + Y.ints);
     C.freeb = p; p += IM;
     C.B = p; p += IM;
@@ -230,14 +232,12 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.hols = p; p += IM;
     C.hold = p; p += IM;
     C.num = p; p += IM;
-    C.den = p; p += IM;
     C.held = p; p += IM;
     C.inb = p; p += IM;
     C.tmask = p; p += IM;
     C.flags = p; p += IM;
     C.gtmp = p; p += IM;
     C.order = p; p += IM;
-    C.pend = p; p += IM;
     C.drn = p; p += IM;
     C.frs = p; p += IM;
     C.hwd = reinterpret_cast<unsigned*>(p); p += IM;
@@ -392,6 +392,24 @@ __device__ __forceinline__ double wave_max_f64(double v)
     return __hiloint2double(hi, lo);
 }
 
+// Sum over the first NL lanes (NL = 16, 32 or 64) of doubles whose sums are
+// exact, for every lane; the other lanes hold 0.
+template <int NL>
+__device__ __forceinline__ double wsum_f64(double x)
+{
+    x += dpp_row_f64<0xB1>(x);
+    x += dpp_row_f64<0x4E>(x);
+    x += dpp_row_f64<0x141>(x);
+    x += dpp_row_f64<0x140>(x);
+    auto row = [&](int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+    };
+    double r = row(0);
+    if (NL > 16) r += row(16);
+    if (NL > 32) r += row(32) + row(48);
+    return r;
+}
+
 __device__ __forceinline__ int blocks_of(uint32_t len, uint32_t shift)
 {
     return int((len + (1u << shift) - 1u) >> shift);
@@ -400,19 +418,38 @@ __device__ __forceinline__ int blocks_of(uint32_t len, uint32_t shift)
 // full finish tick of a running word, given that it has not finished before t
 __device__ __forceinline__ uint32_t fin_of(uint32_t v, uint32_t t) { return t + ((wmid(v) - t) & kFin); }
 
+// Headroom of the tiers in mask tm (Eq. 4), 1/256 block: two reads of the
+// replica's table of sums instead of a term per tier, whose ten values would
+// stay in registers through the tick loop.
+__device__ __forceinline__ int headroom_sum(const Ctx& C, int tm) { return C.ht[tm & 31] + C.ht[32 + (tm >> 5)]; }
+// The table of headroom values hq[0..9], by one wave.
+__device__ inline void headroom_table(const Ctx& C, const int32_t* hq, int lane)
+{
+    int v = 0;
+#pragma unroll
+    for (int p = 0; p < 5; ++p) v += (lane >> p) & 1 ? (lane < 32 ? hq[p] : hq[5 + p]) : 0;
+    C.ht[lane] = v;
+}
+
+// a / den for an integer a (exact in a double) and a divisor den whose
+// correctly rounded reciprocal is rd: the correctly rounded quotient
+// (Markstein 1990: with r = RN(1/den), q = RN(a r) and the exact remainder
+// a - q den, RN(q + remainder r) is RN(a/den)), in three operations where
+// the full division takes eleven.
+__device__ __forceinline__ double quot(double a, double den, double rd)
+{
+    const double q = a * rd;
+    return __builtin_fma(__builtin_fma(-q, den, a), rd, q);
+}
+
 // Freeness of instance i (Eq. 1-4): num = 256 (free - hol demand) - sum of H_p
-// over the tiers with a running request, den = max(B, 1).
+// over the tiers with a running request, over max(B, 1).
 __device__ inline void set_f(const Ctx& C, int i)
 {
-    int hs = 0;
-    const int tm = C.tmask[i];
-#pragma unroll
-    for (int p = 0; p < kTiers; ++p) hs += (tm >> p) & 1 ? C.hq[p] : 0;
-    const int num = 256 * (C.freeb[i] - C.hold[i]) - hs;
-    const int den = C.B[i] > 0 ? C.B[i] : 1;
+    const int tm = C.tmask[i], b = C.B[i], fr = C.freeb[i], hd = C.hold[i];
+    const int num = 256 * (fr - hd) - headroom_sum(C, tm);
     C.num[i] = num;
-    C.den[i] = den;
-    C.fd[i] = double(num) / double(den);
+    C.fd[i] = double(num) / double(b > 0 ? b : 1);
 }
 
 // running requests of instance i whose length is r mod block_tokens: laid out
@@ -480,14 +517,24 @@ __device__ __forceinline__ int live_chunks(const Ctx& C, int i, int lane)
     return nz ? 64 - __clzll(static_cast<long long>(nz)) : 0;
 }
 
-// position of the k-th (from 0) set bit of m; m has more than k set bits
+// position of the k-th (from 0) set bit of m; m has more than k set bits.  The
+// half is chosen first, so that the rest works on one 32-bit register.
 __device__ __forceinline__ int kth_set_bit(unsigned long long m, int k)
 {
-    int pos = 0;
+    const uint32_t lo = uint32_t(m);
+    const int cl = __popc(lo);
+    const bool up = k >= cl;
+    uint32_t x = up ? uint32_t(m >> 32) : lo;
+    int pos = up ? 32 : 0;
+    k -= up ? cl : 0;
 #pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const int c = __popcll((m >> pos) & ((1ull << w) - 1ull));
-        if (k >= c) { k -= c; pos += w; }
+    for (int w = 16; w >= 1; w >>= 1) {
+        const uint32_t part = x & ((1u << w) - 1u);
+        const int c = __popc(part);
+        const bool skip = k >= c;
+        x = skip ? x >> w : part;
+        k -= skip ? c : 0;
+        pos += skip ? w : 0;
     }
     return pos;
 }
@@ -854,7 +901,7 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
                 C.B[i] -= 1;
                 C.nwait[i] += 1;
                 C.frs[i] = 0;
-                C.flags[i] |= kFlagIntf;
+                if (C.fsum) C.flags[i] |= kFlagIntf;  // (INFaaS state)
                 // (several waves may preempt at once; a count above kVic means
                 // the list missed some)
                 const int nv = atomicAdd(C.nvic, 1);
@@ -945,6 +992,7 @@ __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint
     const int i = int(e >> 16), s = int(e & 0xFFFFu);
     const bool valid = inb && uint32_t(i) < C.I && uint32_t(s) < C.S;
     if (!valid) v = 0;
+    const int2 mg = *reinterpret_cast<const int2*>(&C.mig[valid ? 4 * i : 0]);
     const uint32_t fin = fin_of(v, t);
     // entries name distinct running requests (wheel_erase)
     const bool f = valid && wst(v) == 2u && fin == t;
@@ -966,7 +1014,7 @@ __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint
         tier_dec(C, i, tier);
         // being copied out: the source of its instance's migration record (the
         // slot's meta may predate the migration's start)
-        ab = C.mig[4 * i] >= 0 && C.mig[4 * i + 1] == s;
+        ab = mg.x >= 0 && mg.y == s;
         if (ab) atomicOr(&C.flags[i], kFlagAbort);
         atomicAnd(&C.occ[i * C.W + (s >> 6)], ~(1ull << (s & 63)));
         atomicAdd(&C.freeb[i], bl);
@@ -1022,42 +1070,6 @@ __device__ inline void finish_tick(const Ctx& C, uint32_t t, int lane, bool& abo
         kept = finish_batch(C, t, lane, ent, kept, inb, e, v, m, ta, abort_any);
     }
     wheel_set_count(C, bk, kept, lane);
-}
-
-// Adds to stats[tier * 8 + fd0], for every tier, the number of lanes of that
-// tier with f0 set, and likewise for (f1, fd1) and (f2, fd2): the boundaries
-// of the tiers' runs of lanes are found once.  The lanes' tiers are
-// non-decreasing (arrivals are sorted by tier) unless scheduling is
-// tier-blind; lanes that hold no arrival carry tier 15.
-__device__ __forceinline__ void tier_stat3(const Ctx& C, int tier, bool f0, int fd0, bool f1, int fd1, bool f2, int fd2,
-                                           int lane)
-{
-    const unsigned long long m0 = ballot(f0), m1 = ballot(f1), m2 = ballot(f2);
-    if (C.blind) {
-        for (int p = 0; p < int(C.K); ++p) {
-            const unsigned long long tp = ballot(tier == p);
-            const int c0 = __popcll(m0 & tp), c1 = __popcll(m1 & tp), c2 = __popcll(m2 & tp);
-            if (lane == 0) {
-                if (c0) stat(C, p * 8 + fd0, c0);
-                if (c1) stat(C, p * 8 + fd1, c1);
-                if (c2) stat(C, p * 8 + fd2, c2);
-            }
-        }
-        return;
-    }
-    const int tn = __builtin_amdgcn_update_dpp(tier, tier, 0x130, 0xF, 0xF, false);  // wave_shl:1 (lane 63 keeps its own)
-    const bool last = lane == 63 || tn != tier;
-    const unsigned long long bm = ballot(last);
-    if (last && tier < kTiers) {
-        const unsigned long long below = bm & lanemask_lt();
-        const int start = below ? 64 - __clzll(static_cast<long long>(below)) : 0;
-        const unsigned long long upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull;
-        const unsigned long long run = upto & ~((1ull << start) - 1ull);
-        const int c0 = __popcll(m0 & run), c1 = __popcll(m1 & run), c2 = __popcll(m2 & run);
-        if (c0) stat(C, tier * 8 + fd0, c0);
-        if (c1) stat(C, tier * 8 + fd1, c1);
-        if (c2) stat(C, tier * 8 + fd2, c2);
-    }
 }
 
 // Admits the longest prefix of w ranked waiting requests of instance i (lane
@@ -1790,8 +1802,6 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             const int32_t* hqr = ext_hqr(P);
             if (hqr) hq = hqr + size_t(r) * kTiers;
         }
-#pragma unroll
-        for (int p = 0; p < kTiers; ++p) C.hq[p] = hq[p];
         const size_t rb = size_t(r) * I * S;
         C.slot = P.slot + rb;
         if (C.xn) C.qx = P.qx + size_t(r) * I * P.qxd;
@@ -1923,6 +1933,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             if (!warm)
                 for (uint32_t i = tid; i < P.I; i += NT) wlb(C)[i] = 0u;
         }
+        if (wid == 0) headroom_table(C, hq, lane);
         unsigned next_seq = P.next_seq[r];
         uint32_t run_acc = 0, wait_acc = 0;  // per lane, at most 1024 ticks x 4 x 2048
         const unsigned long long* recs = P.arr_rec + size_t(r) * P.chunk * P.arr_cap;
@@ -1975,9 +1986,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 }
                 block_sync<NW>();
                 if (ep && al == 0) {
-                    const int32_t* hq = ext_hqr(P) + size_t(r) * kTiers;
-#pragma unroll
-                    for (int p = 0; p < kTiers; ++p) C.hq[p] = hq[p];
+                    if (wid == 0) headroom_table(C, ext_hqr(P) + size_t(r) * kTiers, lane);
+                    block_sync<NW>();
                 }
                 if (tid == 0) {
                     xleft(C)[0] = per && pl + 1 < per ? pl + 1 : 0;
@@ -1997,15 +2007,15 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 bool np = false;
                 if (i < I) {
                     const int G = int(c16_get(C.res, res_idx(C, i, cres)));
-                    const int fr = C.freeb[i];
+                    const int fr = C.freeb[i], he = C.held[i];
                     np = G > fr;
                     if (np) {
                         C.gtmp[i] = G;
                     } else {
                         C.freeb[i] = fr - G;
-                        C.held[i] += G;
+                        C.held[i] = he + G;
                     }
-                    if (C.flags[i] & kFlagIntf) C.flags[i] &= ~kFlagIntf;
+                    if (INF) C.flags[i] &= ~kFlagIntf;
                     if (C.fsum) { C.fsum[i] = 0; C.fcnt[i] = 0; }
                 }
                 pre[j] = ballot(np);
@@ -2129,97 +2139,84 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 // phase C reads the instances each wave owns, which any wave
                 // may have admitted on
                 block_sync<NW>();
-            } else
-            for (;;) {
-                // heads of line left unknown: found by a rescan, which admits at once
-                bool unk = false;
-#pragma unroll
-                for (int j = 0; j < OPL; ++j) {
-                    const uint32_t i = (uint32_t(lane) + 64u * j) * NW + uint32_t(wid);
-                    for (unsigned long long m = ballot(i < I && C.hols[i] == kHolUnknown); m; m &= m - 1)
-                        unk = rescan_admit<(IM >= 128 ? 16 : 4), (IM >= 128 ? 4 : 2)>(
-                                  C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || unk;
-                }
-                bool any = unk;
-                // queues that hold the previous tick's arrivals only
-                {
-                    bool fresh = false;
-#pragma unroll
-                    for (int j = 0; j < OPL; ++j) {
-                        const uint32_t i = uint32_t(lane) + 64u * j;
-                        fresh = fresh || (i < I && C.frs[i] && C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]);
+            } else {
+                // lane i holds instance i; its summary is read once per round
+                const int i = lane;
+                const bool own = uint32_t(i) < I;
+                for (;;) {
+                    int h = kNoHol, hd = 0, fr = 0, nw = 0, fs = 0, qn = 0;
+                    auto look = [&] {
+                        if (own) {
+                            h = C.hols[i]; hd = C.hold[i]; fr = C.freeb[i]; nw = C.nwait[i]; fs = C.frs[i];
+                            if (C.td) qn = C.qn[i];
+                        }
+                    };
+                    look();
+                    // heads of line left unknown: found by a rescan, which admits at once
+                    bool any = false;
+                    const unsigned long long um = ballot(h == kHolUnknown);
+                    if (um) {
+                        for (unsigned long long m = um; m; m &= m - 1) any = rescan_admit<4, 2>(C, ffs64(m), t, lane) || any;
+                        look();
                     }
-                    if (ballot(fresh)) admit_fresh_all(C, t, lane);
-                }
-                unsigned long long bat[OPL], cch[OPL];
-#pragma unroll
-                for (int j = 0; j < OPL; ++j) {
-                    const uint32_t i = (uint32_t(lane) + 64u * j) * NW + uint32_t(wid);
-                    bool batch = false, cachd = false;
-                    if (i < I && C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]) {
-                        const int nw = C.nwait[i];
-                        const bool cached = C.td && C.qn[i] > 0;
-                        if (nw >= 2 && nw <= 64 && !cached) {
-                            batch = true;
-                        } else if (IM >= 128 && cached) {
-                            // the kernels for 128+ instances admit a cached run at
-                            // once (the head of line may be unknown afterwards)
-                            cachd = true;
-                            any = true;
-                        } else {
+                    const bool fits = h >= 0 && hd <= fr;
+                    // queues that hold the previous tick's arrivals only
+                    if (ballot(fits && fs)) admit_fresh_all(C, t, lane);
+                    const bool rest = fits && !fs;
+                    if (ballot(rest)) {
+                        const bool batch = rest && nw >= 2 && nw <= 64 && !(C.td && qn > 0);
+                        if (rest && !batch) {
                             // the only waiting request, a queue longer than a wave or one
                             // whose next requests are cached: admit heads of line one at a
                             // time while they fit and are known
                             do {
-                                admit_head(C, int(i), t);
+                                admit_head(C, i, t);
                             } while (C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]);
                             // an unknown head of line is found by the next round's rescan
                             any = any || C.hols[i] == kHolUnknown;
                         }
+                        wave_sync();
+                        for (unsigned long long m = ballot(batch); m; m &= m - 1) admit_batch<4>(C, ffs64(m), t, lane);
                     }
-                    bat[j] = ballot(batch);
-                    cch[j] = ballot(cachd);
+                    if (!ballot(any)) break;
                 }
-                wave_sync();
-#pragma unroll
-                for (int j = 0; j < OPL; ++j) {
-                    for (unsigned long long m = bat[j]; m; m &= m - 1)
-                        admit_batch<(IM >= 128 ? 16 : 4)>(C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane);
-                    for (unsigned long long m = cch[j]; m; m &= m - 1)
-                        admit_cached(C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane);
-                }
-                if (!ballot(any)) break;
             }
             // auto-scaling signal (Section 3.6): the cluster average of the
             // normal-priority freeness F_normal = (free - head-of-line demand) /
             // max(B, 1) -- no headroom, no draining sentinel -- in fixed point,
             // floor(F_normal * 2^20) per instance, against -1/2 and 3/2
-            long long fsum = 0;
+            double fsum = 0.0;
+            // (the one-wave kernels hand each lane's instance on to the dispatch)
+            int c_num = 0, c_hold = 0, c_nw = 0;
+            double c_den = 1.0, c_rd = 1.0, c_fd = 0.0;
 #pragma unroll
             for (int j = 0; j < OPL; ++j) {
                 const uint32_t i = (uint32_t(lane) + 64u * j) * NW + uint32_t(wid);
                 if (i >= I) continue;
-                set_f(C, int(i));
+                // every field first: one LDS round trip
+                const int fr = C.freeb[i], hd = C.hold[i], tm = C.tmask[i], b = C.B[i], nw = C.nwait[i], he = C.held[i],
+                          ib = C.inb[i];
+                // Eq. 1-4 and the normal-priority freeness share the divisor
+                const double den = double(b > 0 ? b : 1), rd = 1.0 / den;
+                const int num = 256 * (fr - hd) - headroom_sum(C, tm);
+                const double f = quot(double(num), den, rd);
+                C.num[i] = num;
+                C.fd[i] = f;
+                c_num = num; c_hold = hd; c_nw = nw; c_den = den; c_rd = rd; c_fd = f;
                 // slot-ticks: running and waiting requests at the end of the tick.
                 // Later phases move running and waiting requests between
                 // instances (commits, queued moves) and add only the arrivals
                 // the dispatch places, counted there
-                run_acc += unsigned(C.B[i]);
-                wait_acc += unsigned(C.nwait[i]);
-                if (C.freeb[i] < 0 || C.freeb[i] + C.held[i] + C.inb[i] != int(C.M)) stat(C, kInvariant, 1);
+                run_acc += unsigned(b);
+                wait_acc += unsigned(nw);
+                if (fr < 0 || fr + he + ib != int(C.M)) stat(C, kInvariant, 1);
                 // floor(x 2^20 / den): x 2^20 is exact in a double (|x| < 2^22) and
                 // the correctly rounded quotient never crosses an integer (the
-                // quotient sits at least 1/den >= 2^-11 from one, more than half
-                // an ulp below 2^42); the integer residual check keeps it exact
-                const long long a = static_cast<long long>(C.freeb[i] - C.hold[i]) * 1048576ll;
-                const long long d = C.den[i];
-                long long q = static_cast<long long>(floor(double(a) / double(d)));
-                const long long rr = a - q * d;
-                if (rr < 0) q -= 1;
-                else if (rr >= d) q += 1;
-                fsum += q;
+                // quotient, below 2^42, sits at least 1/den >= 2^-11 from one, more
+                // than half an ulp).  Sums of 256 such integers are exact.
+                fsum += floor(quot(double(fr - hd) * 1048576.0, den, rd));
             }
-            fsum = static_cast<long long>(wsum64(static_cast<unsigned long long>(fsum)));
+            fsum = wsum_f64<(IM < 64 ? IM : 64)>(fsum);
             if (C.svc) {
                 // INFaaS: service-time estimate from this tick's finishes, then
                 // the state penalty (OVERLOADED before INTERFERED before ACTIVE)
@@ -2243,14 +2240,16 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 }
             }
             if (NW > 1) {
-                if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long*>(C.bsum), static_cast<unsigned long long>(fsum));
+                if (lane == 0)
+                    atomicAdd(reinterpret_cast<unsigned long long*>(C.bsum),
+                              static_cast<unsigned long long>(static_cast<long long>(fsum)));
                 block_sync<NW>();
-                fsum = *C.bsum;
+                fsum = double(*C.bsum);
             }
             if (tid == 0) {
-                const long long half = static_cast<long long>(I) << 19;
+                const double half = double(I) * 524288.0;
                 if (fsum < -half) stat(C, kScaleOut, 1);
-                else if (fsum > 3 * half) stat(C, kScaleIn, 1);
+                else if (fsum > 3.0 * half) stat(C, kScaleIn, 1);
             }
             wave_sync();
 
@@ -2272,11 +2271,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 // per-instance dispatch state in registers: lane l, register j <-> instance 64 j + l
                 // key: F of the instances that can take an arrival (minus infinity
                 // for a full instance and, in the first mode, for a draining one)
-                // (an arrival that becomes an instance's head of line updates its
-                // demand, num and F in LDS at once: only that instance's lane
-                // touches them until the write-back)
-                double key[IPL], fnew[IPL];
-                int live_r[IPL], nadd[IPL], pend_r[IPL], num_r[IPL], hold_r[IPL];
+                double key[IPL], fnew[IPL], den[IPL], rd[IPL];
+                int live_r[IPL], nw_r[IPL], nadd[IPL], pend_r[IPL], num_r[IPL], hold_r[IPL];
                 unsigned long long hk_r[IPL];
 #pragma unroll
                 for (int j = 0; j < IPL; ++j) {
@@ -2285,17 +2281,29 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     pend_r[j] = -1;
                     num_r[j] = 0;
                     hold_r[j] = 0;
+                    nw_r[j] = 0;
                     fnew[j] = 0.0;
+                    den[j] = 1.0;
+                    rd[j] = 1.0;
+                    live_r[j] = int(S); hk_r[j] = 0;
+                    key[j] = -__builtin_inf();
                     if (i < I) {
+                        const int h = C.hols[i], dr = C.drn[i];
                         live_r[j] = C.live[i];
-                        num_r[j] = C.num[i];
-                        hold_r[j] = C.hold[i];
-                        hk_r[j] = C.hols[i] == kNoHol ? kNone : C.holk[i];
-                        key[j] = live_r[j] < int(S) && !C.drn[i] ? (infaas ? -infaas_cost(C, P, int(i), 0) : C.fd[i])
-                                                                 : -__builtin_inf();
-                    } else {
-                        live_r[j] = int(S); hk_r[j] = 0;
-                        key[j] = -__builtin_inf();
+                        hk_r[j] = C.holk[i];
+                        double f;
+                        if (NW == 1) {
+                            num_r[j] = c_num; hold_r[j] = c_hold; nw_r[j] = c_nw; den[j] = c_den; rd[j] = c_rd; f = c_fd;
+                        } else {
+                            num_r[j] = C.num[i]; hold_r[j] = C.hold[i]; nw_r[j] = C.nwait[i];
+                            const int b = C.B[i];
+                            den[j] = double(b > 0 ? b : 1);
+                            rd[j] = 1.0 / den[j];
+                            f = C.fd[i];
+                        }
+                        if (h == kNoHol) hk_r[j] = kNone;
+                        if (infaas) f = -infaas_cost(C, P, int(i), 0);
+                        if (live_r[j] < int(S) && !dr) key[j] = f;
                     }
                 }
                 int cur = -1;
@@ -2309,14 +2317,31 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     const unsigned long long a = a_bt;
                     if (n - k0 > 64) a_bt = k0 + 64 + lane < n ? rec[k0 + 64 + lane] : 0ull;
                     int tgt = -1, rank = 0;  // rank: among this batch's arrivals bound for tgt
+                    unsigned long long heads = 0;  // arrivals of this batch that became a head of line
                     uint32_t k = 0;
                     while (k < cn && !full) {
+                        // what arrival k would change on every instance, beside the
+                        // argmax's chain: whether it becomes the head of line there, and F
+                        const unsigned long long ak = rl64(a, int(k));
+                        const unsigned long long hk = rank_of(C, uint32_t(ak >> 32) & 15u) << 32 | (seq0 + unsigned(ak >> 36));
+                        const int dem = blocks_of(uint32_t(ak & 0xFFFFu), C.shift);
+                        unsigned long long lower[IPL];
+                        int nn[IPL];
+                        double fn[IPL];
+#pragma unroll
+                        for (int j = 0; j < IPL; ++j) {
+                            lower[j] = ballot(hk < hk_r[j]);
+                            // Eq. 1-2: F moves by the change of head-of-line demand
+                            nn[j] = num_r[j] - 256 * (dem - hold_r[j]);
+                            fn[j] = quot(double(nn[j]), den[j], rd[j]);
+                        }
                         if (cur < 0) {
                             double lb = key[0];
 #pragma unroll
                             for (int j = 1; j < IPL; ++j) lb = fmax(lb, key[j]);
                             double mv = wave_max_f64<(IM < 64 ? IM : 64)>(lb);
-                            if (mv == -__builtin_inf() && !drain_mode) {
+                            if (mv == -__builtin_inf()) {
+                                if (drain_mode) { full = true; break; }
                                 // no non-draining instance has a free slot: the least
                                 // loaded draining one (largest F without the sentinel);
                                 // slots only fill up, so the mode holds for the tick
@@ -2332,8 +2357,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
 #pragma unroll
                                 for (int j = 1; j < IPL; ++j) lb = fmax(lb, key[j]);
                                 mv = wave_max_f64<(IM < 64 ? IM : 64)>(lb);
+                                if (mv == -__builtin_inf()) { full = true; break; }
                             }
-                            if (mv == -__builtin_inf()) { full = true; break; }
 #pragma unroll
                             for (int j = IPL - 1; j >= 0; --j) {
                                 const unsigned long long bm = ballot(key[j] == mv);
@@ -2341,14 +2366,10 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             }
                         }
                         const int jc = cur >> 6, lc = cur & 63;
-                        int lv = 0, na0 = 0;
-                        unsigned long long hkc = 0;
+                        bool becomes = false;
 #pragma unroll
                         for (int j = 0; j < IPL; ++j)
-                            if (j == jc) { lv = rl(live_r[j], lc); hkc = rl64(hk_r[j], lc); na0 = rl(nadd[j], lc); }
-                        const unsigned long long ak = rl64(a, int(k));
-                        const unsigned long long hk = rank_of(C, uint32_t(ak >> 32) & 15u) << 32 | (seq0 + unsigned(ak >> 36));
-                        const bool becomes = hk < hkc;
+                            if (j == jc) becomes = (lower[j] >> lc) & 1ull;
                         // Arrival k goes to cur.  If it becomes cur's head of line, F of cur
                         // changes and the argmax is taken again.  Otherwise F stays, and
                         // so does the argmax for the following arrivals, none of which can
@@ -2356,28 +2377,27 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         // they all go to cur until its slots run out.
                         // (under INFaaS every placement raises cur's cost by alpha)
                         const bool step1 = becomes || (infaas && P.alpha256 > 0);
+                        int lv = 0, na0 = 0;
+#pragma unroll
+                        for (int j = 0; j < IPL; ++j)
+                            if (j == jc) { lv = rl(live_r[j], lc); na0 = rl(nadd[j], lc); }
                         const int m = step1 ? 1 : min(int(cn - k), int(S) - lv);
                         const int nl = lv + m;
-                        if (lane == lc) {
+                        heads |= becomes ? 1ull << k : 0ull;
 #pragma unroll
-                            for (int j = 0; j < IPL; ++j) {
-                                if (j != jc) continue;
-                                live_r[j] = nl;
-                                nadd[j] += m;
-                                if (becomes) {
-                                    hk_r[j] = hk;
-                                    pend_r[j] = int(k0 + k);
-                                    // Eq. 1-2: F moves by the change of head-of-line demand
-                                    // (num and the demand stay in registers until the write-back)
-                                    const int dem = blocks_of(uint32_t(ak & 0xFFFFu), C.shift);
-                                    num_r[j] -= 256 * (dem - hold_r[j]);
-                                    hold_r[j] = dem;
-                                    fnew[j] = double(num_r[j]) / double(C.den[lc + 64 * j]);
-                                    if (!infaas) key[j] = fnew[j];
-                                }
-                                if (infaas) key[j] -= double(P.alpha256) * double(m);
-                                if (nl >= int(S)) key[j] = -__builtin_inf();
-                            }
+                        for (int j = 0; j < IPL; ++j) {
+                            if (j != jc) continue;
+                            const bool me = lane == lc, hd = me && becomes;
+                            live_r[j] = me ? nl : live_r[j];
+                            nadd[j] = me ? nadd[j] + m : nadd[j];
+                            hk_r[j] = hd ? hk : hk_r[j];
+                            pend_r[j] = hd ? int(k0 + k) : pend_r[j];
+                            num_r[j] = hd ? nn[j] : num_r[j];
+                            hold_r[j] = hd ? dem : hold_r[j];
+                            fnew[j] = hd ? fn[j] : fnew[j];
+                            if (infaas) key[j] = me ? key[j] - double(P.alpha256) * double(m) : key[j];
+                            else key[j] = hd ? fn[j] : key[j];
+                            key[j] = me && nl >= int(S) ? -__builtin_inf() : key[j];
                         }
                         if (lane >= int(k) && lane < int(k) + m) { tgt = cur; rank = na0 + lane - int(k); }
                         if (step1 || nl >= int(S)) cur = -1;
@@ -2391,9 +2411,10 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         const uint32_t i = lane + 64 * j;
                         if (i >= I) continue;
                         C.live[i] = live_r[j];
-                        const int nw0 = C.nwait[i];
+                        const int nw0 = nw_r[j];
                         if (k0 == 0) C.frs[i] = nw0 == 0 && n <= uint32_t(kLast);
-                        C.nwait[i] = nw0 + nadd[j];
+                        nw_r[j] = nw0 + nadd[j];
+                        C.nwait[i] = nw_r[j];
                         wait_acc += unsigned(nadd[j]);
                         if (pend_r[j] >= 0) {
                             C.num[i] = num_r[j];
@@ -2416,8 +2437,6 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         }
                         nadd[j] = 0;
                         if (pend_r[j] >= 0) {
-                            C.hols[i] = kHolPending;
-                            C.pend[i] = pend_r[j];
                             C.holk[i] = hk_r[j];
                             pend_r[j] = -1;
                         }
@@ -2456,25 +2475,30 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         }
                     }
                     if (tgt >= 0 && !searched) {
-                        // the rank-th empty slot, four occupancy words per step
-                        int rk = rank;
-                        for (uint32_t w0 = 0; w0 < W && s < 0; w0 += 4) {
+                        // the rank-th empty slot: its occupancy word, four words per
+                        // step, then its place in that word (once for all lanes,
+                        // wherever their words lie)
+                        int rk = rank, wi = -1;
+                        unsigned long long fw = 0;
+                        for (uint32_t w0 = 0; w0 < W && wi < 0; w0 += 4) {
                             unsigned long long wd[4];
 #pragma unroll
                             for (int k = 0; k < 4; ++k) wd[k] = w0 + k < W ? C.occ[tgt * W + w0 + k] : kNone;
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
                                 const int z = 64 - __popcll(wd[k]);
-                                if (s < 0) {
-                                    if (rk < z) s = int(w0 + k) * 64 + kth_set_bit(~wd[k], rk);
-                                    else rk -= z;
-                                }
+                                const bool here = wi < 0 && rk < z;
+                                fw = here ? ~wd[k] : fw;
+                                wi = here ? int(w0 + k) : wi;
+                                rk -= wi < 0 ? z : 0;
                             }
                         }
+                        if (wi >= 0) s = wi * 64 + kth_set_bit(fw, rk);
                     }
                     if (tgt >= 0 && s < 0) {  // occupancy and live count disagree: flag, drop the arrival
                         stat(C, kInvariant, 1);
                         stat(C, tier * 8 + kRejected, 1);
+                        if ((heads >> lane) & 1ull) C.hols[tgt] = kHolUnknown;
                         tgt = -2;
                     }
                     wave_sync();
@@ -2494,7 +2518,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         const uint32_t word = kWaitW | (uint32_t((a >> 16) & 0xFFFFu) << 16) | uint32_t(a & 0xFFFFu);
                         const uint32_t meta = kWaiting | (unsigned(tier) << 2);
                         C.slot[sb] = make_uint4(word, meta, seq0 + unsigned(a >> 36), t);
-                        if (C.hols[tgt] == kHolPending && C.pend[tgt] == int(k0) + lane) {
+                        if ((heads >> lane) & 1ull) {
                             C.hols[tgt] = s;
                             C.hwd[tgt] = word;
                             C.hmt[tgt] = meta;
@@ -2551,9 +2575,9 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     // every arrival is dispatched (tgt >= 0) or rejected: no free slot
                     // anywhere (-1), or dropped by the occupancy check (-2, counted
                     // above)
-                    const int vt = lane < int(cn) ? tier : 15;
-                    tier_stat3(C, vt, lane < int(cn), kArrived, tgt >= 0, kDispatched, tgt == -1 && lane < int(cn),
-                               kRejected, lane);
+                    if (lane < int(cn)) stat(C, tier * 8 + kArrived, 1);
+                    if (tgt >= 0) stat(C, tier * 8 + kDispatched, 1);
+                    else if (tgt == -1 && lane < int(cn)) stat(C, tier * 8 + kRejected, 1);
                     wave_sync();
                 }
                 if (lane == 0 && nfall) stat(C, kDrainFallback, unsigned(nfall));
@@ -2570,7 +2594,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
 
             // ===================== E1: staged copies =====================
             // a commit leaves the source slot: its wheel entry (source slot in
-            // gtmp, finish tick in pend) is erased after the loop
+            // gtmp, finish tick in order) is erased after the loop
             if (migs) {
             for (uint32_t i = lane; i < I; i += 64) C.gtmp[i] = -1;
             for (uint32_t i = lane; i < I; i += 64) {
@@ -2619,7 +2643,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     tier_inc(C, d, tier);
                     wheel_put(C, fin, d, m[2]);
                     C.gtmp[i] = m[1];
-                    C.pend[i] = int(fin);
+                    C.order[i] = int(fin);
                     m[0] = -1; m[1] = 0; m[2] = 0; m[3] = 0;
                     stat(C, kMigCommitted, 1);
                     set_f(C, int(i));
@@ -2632,7 +2656,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 const uint32_t i0 = lane + 64 * j;
                 for (unsigned long long m = ballot(i0 < I && C.gtmp[i0] >= 0); m; m &= m - 1) {
                     const int ii = 64 * j + ffs64(m);
-                    wheel_erase(C, uint32_t(C.pend[ii]), ii, C.gtmp[ii], lane);
+                    wheel_erase(C, uint32_t(C.order[ii]), ii, C.gtmp[ii], lane);
                 }
             }
             wave_sync();
@@ -2648,63 +2672,62 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             // (wave 0), their order (wave 0 by counting ranks; in the
             // eight-wave kernels every thread counts), the pairs (wave 0)
             if (!infaas && mig_tick) {
+                // F and the draining flag of each lane's instances
+                double ef[IPL];
                 bool neg = false;
-                for (uint32_t i = lane; i < I; i += 64) neg |= C.num[i] < 0 || C.drn[i];
+#pragma unroll
+                for (int j = 0; j < IPL; ++j) {
+                    const uint32_t i = lane + 64 * j;
+                    ef[j] = 0.0;
+                    if (i < I) {
+                        const double f = C.fd[i];
+                        const int dr = C.drn[i];
+                        ef[j] = dr ? -__builtin_inf() : f;
+                        neg = neg || dr || f < 0.0;
+                    }
+                }
                 if (ballot(neg)) {
                     e2 = true;
-                    for (uint32_t i = lane; i < I; i += 64) C.flags[i] &= ~kFlagBusy;
-                    wave_sync();
-                    for (uint32_t i = lane; i < I; i += 64) {
-                        const int d = C.mig[4 * i];
-                        if (d >= 0) { atomicOr(&C.flags[i], kFlagBusy); atomicOr(&C.flags[d], kFlagBusy); }
-                    }
-                    wave_sync();
-                    // rank the instances not in a migration by (F, index): F as an
-                    // order-preserving 64-bit key (a draining instance's F is minus
-                    // infinity)
-                    unsigned long long fk[IPL];
+                    // the instances not in a migration (no record is active: all)
                     unsigned long long avm[IPL];
+                    if (migs) {
+                        for (uint32_t i = lane; i < I; i += 64) C.flags[i] &= ~kFlagBusy;
+                        wave_sync();
+                        for (uint32_t i = lane; i < I; i += 64) {
+                            const int d = C.mig[4 * i];
+                            if (d >= 0) { atomicOr(&C.flags[i], kFlagBusy); atomicOr(&C.flags[d], kFlagBusy); }
+                        }
+                        wave_sync();
+                    }
 #pragma unroll
                     for (int j = 0; j < IPL; ++j) {
                         const uint32_t i = lane + 64 * j;
-                        const bool av = i < I && !(C.flags[i] & kFlagBusy);
-                        const double f = i < I && C.drn[i] ? -__builtin_inf() : (i < I ? C.fd[i] : 0.0);
-                        const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(f));
-                        fk[j] = (bits >> 63) ? ~bits : bits | (1ull << 63);
-                        avm[j] = ballot(av);
+                        avm[j] = ballot(i < I && !(migs && (C.flags[i] & kFlagBusy)));
                         n2 += __popcll(avm[j]);
                     }
                     if (NW > 1) {
                         // the keys for the workgroup's count, in the freeness array
-                        // (set again in phase C before its next use); an instance in
-                        // a migration carries the largest key
+                        // (set again in phase C before its next use): F as an
+                        // order-preserving 64-bit key; an instance in a migration
+                        // carries the largest one
 #pragma unroll
                         for (int j = 0; j < IPL; ++j) {
                             const uint32_t i = lane + 64 * j;
+                            const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(ef[j]));
+                            const unsigned long long fk = (bits >> 63) ? ~bits : bits | (1ull << 63);
                             if (i < I)
-                                reinterpret_cast<unsigned long long*>(C.fd)[i] = (avm[j] >> lane) & 1ull ? fk[j] : kNone;
+                                reinterpret_cast<unsigned long long*>(C.fd)[i] = (avm[j] >> lane) & 1ull ? fk : kNone;
                         }
                     } else {
-                        // L: every instance's rank, from every other lane's key
-                        int rk[IPL];
-#pragma unroll
-                        for (int j = 0; j < IPL; ++j) rk[j] = 0;
-#pragma unroll
-                        for (int jj = 0; jj < IPL; ++jj) {
-                            for (unsigned long long mm = avm[jj]; mm; mm &= mm - 1) {
-                                const int l = ffs64(mm);
-                                const unsigned long long kl = rl64(fk[jj], l);
-                                const int il = 64 * jj + l;
-#pragma unroll
-                                for (int j = 0; j < IPL; ++j) {
-                                    const int i = lane + 64 * j;
-                                    rk[j] += (kl < fk[j] || (kl == fk[j] && il < i)) ? 1 : 0;
-                                }
-                            }
+                        // L: every instance's rank by (F, index), from every other
+                        // lane's F (the lanes above it also count an equal one)
+                        int rk = 0;
+                        for (unsigned long long mm = avm[0]; mm; mm &= mm - 1) {
+                            const int l = ffs64(mm);
+                            const double fl = __hiloint2double(rl(__double2hiint(ef[0]), l), rl(__double2loint(ef[0]), l));
+                            rk += (fl < ef[0]) | ((fl == ef[0]) & (l < lane)) ? 1 : 0;
                         }
-#pragma unroll
-                        for (int j = 0; j < IPL; ++j)
-                            if ((avm[j] >> lane) & 1ull) C.order[rk[j]] = lane + 64 * j;
+                        if ((avm[0] >> lane) & 1ull) C.order[rk] = lane;
                     }
                 }
             }
@@ -2717,12 +2740,12 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 // order, in two steps: waves 0..3 each sort a block of 64
                 // instances by counting (into the rescans' selection buffers,
                 // free at this point of the tick), then every instance adds its
-                // place in each block, found by bisection, summed in pend[]
+                // place in each block, found by bisection, summed in gtmp[]
                 const unsigned long long* key = reinterpret_cast<const unsigned long long*>(C.fd);
                 constexpr uint32_t kParts = NT / uint32_t(IM);
                 const uint32_t nblk = (I + 63u) / 64u;
                 ulonglong2* sblk = reinterpret_cast<ulonglong2*>(C.rsel - 64 * wid);
-                for (uint32_t i = tid; i < I; i += NT) C.pend[i] = 0;
+                for (uint32_t i = tid; i < I; i += NT) C.gtmp[i] = 0;
                 if (uint32_t(wid) < nblk) {
                     // (entries past I and unavailable instances carry the largest key)
                     const uint32_t i = 64u * uint32_t(wid) + uint32_t(lane);
@@ -2756,12 +2779,12 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             }
                             rk += lo;
                         }
-                        if (rk) atomicAdd(&C.pend[i], rk);
+                        if (rk) atomicAdd(&C.gtmp[i], rk);
                     }
                 }
                 block_sync<NW>();
                 for (uint32_t i = tid; i < I; i += NT)
-                    if (key[i] != kNone) C.order[C.pend[i]] = int(i);
+                    if (key[i] != kNone) C.order[C.gtmp[i]] = int(i);
                 block_sync<NW>();
             }
             if (wid == 0) {
@@ -2785,10 +2808,11 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             } else if (!C.drn[src]) {
                                 // (a draining source is overloaded and any destination is
                                 // more than theta freer)
-                                const long long lhs = (long long)P.theta_den *
-                                    ((long long)C.num[dst] * C.den[src] - (long long)C.num[src] * C.den[dst]);
-                                const long long rhs = (long long)P.theta_num * 256 * C.den[src] * C.den[dst];
-                                stop = C.num[src] >= 0 || lhs < rhs;
+                                const int bs = C.B[src], bd = C.B[dst], ns = C.num[src], nd = C.num[dst];
+                                const long long es = bs > 0 ? bs : 1, ed = bd > 0 ? bd : 1;
+                                const long long lhs = (long long)P.theta_den * (nd * es - ns * ed);
+                                const long long rhs = (long long)P.theta_num * 256 * es * ed;
+                                stop = ns >= 0 || lhs < rhs;
                             }
                         }
                         const unsigned long long sm = ballot(stop);

@@ -64,3 +64,48 @@ def test_the_bound_is_needed():
     # (here numerators beyond 2^53), so the limits are what makes the order exact
     a, b = 2**53 + 1, 2**53
     assert a != b and float(a) / 1.0 == float(b) / 1.0
+
+
+QUOT_C = r"""
+#include <math.h>
+#include <stdint.h>
+/* the device's three-step quotient: r = 1 / den correctly rounded */
+static double quot(double a, double den, double rd)
+{
+    const double q = a * rd;
+    return fma(fma(-q, den, a), rd, q);
+}
+static uint64_t x = 88172645463325252ull;
+static uint64_t rnd(void) { x ^= x << 13; x ^= x >> 7; x ^= x << 17; return x; }
+/* numerators around every power of two and at random, each divisor up to
+ * 2048 (an instance's slots): counts quotients that are not the division's,
+ * and floors of free 2^20 / den that are not the integer division's */
+uint64_t mismatches(int per_den)
+{
+    uint64_t bad = 0;
+    for (int d = 1; d <= 2048; ++d) {
+        const double den = d, rd = 1.0 / den;
+        for (int k = 0; k < per_den; ++k) {
+            int64_t a = k < 124 ? ((int64_t)1 << (k / 4)) + (k % 4) - 2 : (int64_t)(rnd() >> 34);
+            if (k & 1) a = -a;
+            bad += quot((double)a, den, rd) != (double)a / den;
+            const int64_t f = k < 84 ? ((int64_t)1 << (k / 4)) + (k % 4) - 2 : (int64_t)(rnd() >> 42);
+            const int64_t n = (k & 1 ? -f : f) * 1048576;
+            const int64_t fl = n >= 0 ? n / d : -((-n + d - 1) / d);
+            bad += (int64_t)floor(quot((double)n, den, rd)) != fl;
+        }
+    }
+    return bad;
+}
+"""
+
+
+def test_three_step_quotient_is_the_correctly_rounded_one(tmp_path):
+    import ctypes
+    import subprocess
+    src, lib = tmp_path / "quot.c", tmp_path / "quot.so"
+    src.write_text(QUOT_C)
+    subprocess.run(["gcc", "-O2", "-ffp-contract=off", "-shared", "-fPIC", "-o", str(lib), str(src), "-lm"], check=True)
+    L = ctypes.CDLL(str(lib))
+    L.mismatches.restype = ctypes.c_uint64
+    assert L.mismatches(2000) == 0
