@@ -8,8 +8,8 @@
 //               state lives in HBM and is touched only by events.
 //   k_init      empty clusters; k_digest the canonical state digest.
 //
-// Slot record (uint4 per slot): x = slot word, y = meta, z = seq, w = arrival
-// tick, so that an event reads or writes one 16-byte record.  Slot word (u32,
+// Slot record (uint4 per slot): x = slot word, y = meta (a running request's
+// place in its finish bucket from bit 8 on), z = seq, w = arrival tick, so that an event reads or writes one 16-byte record.  Slot word (u32,
 // bits 31..30 = status):
 //   waiting   01 | rem (14 bits) | len (16 bits)
 //   running   10 | fin mod 2^14  | final length (16 bits)
@@ -681,21 +681,56 @@ __device__ __forceinline__ unsigned long long arr_key(const Ctx& C, int tier, ui
 {
     return (rank_of(C, uint32_t(tier)) << 32) | seq;
 }
-// arrival e of instance i, larger than its head of line, enters the cache: at
-// its place among the cached entries (looked for from the end, where a new
-// arrival of a low tier belongs), behind them when they list every waiting
-// request and there is room, else not at all (it is larger than the cached
-// prefix).  One that falls behind the ring drops the extension, which it may
-// fall into.
-__device__ inline void qc_arrive(const Ctx& C, int i, uint4 e)
+// The arrivals of mask em (one per lane, ascending keys, entries en), all
+// larger than instance i's head of line, enter its ring in one merge: lane l
+// holds entry l, each arrival finds its place by a ballot and the entries
+// behind it move up.  An arrival behind the last entry enters only when the
+// head and the ring list every waiting request (all); the first one without a
+// place ends the merge, the rest being larger still.  Entries that drop out of
+// a full ring go to the front of the extension; it is dropped when an arrival
+// that got no place belongs in front of its end (inside: such arrivals).  Uniform.
+// (Entering the arrivals one after the other by their own lanes took the
+// overloaded study 12-13K cycles a tick.)
+__device__ inline void qc_merge(const Ctx& C, int i, unsigned long long em, unsigned long long key, uint4 en, bool all,
+                                unsigned long long inside, int lane)
 {
-    const unsigned long long key = qc_key(C, e);
-    const int n = C.qn[i];
-    int p = n;
-    while (p > 0 && key < qc_key(C, C.qt[qc_at(C, i, p - 1)])) --p;
-    if (p < n) { qc_insert_at(C, i, p, e); return; }
-    if (qx_count(C, i) > 0) { qx_clear(C, i); C.order[i] = kQcPart; return; }
-    if (n < C.td && (C.order[i] & 3) == kQcAll) { C.qt[qc_at(C, i, n)] = e; C.qn[i] = n + 1; }
+    const int n = C.qn[i], h = C.qh[i], xv = C.xn ? C.xn[i] : 0, xc = xv & 0xFFFF;
+    uint4 e = make_uint4(0u, 0u, 0u, 0u);
+    unsigned long long ke = kNone;
+    if (lane < n) {
+        const int x = h + lane;
+        e = C.qt[i * C.td + (x >= C.td ? x - C.td : x)];
+        ke = qc_key(C, e);
+    }
+    int up = 0, ins = 0, at = -1;
+    bool split = false;  // an arrival without a place is smaller than some entry
+    unsigned long long m = em;
+    for (; m; m &= m - 1) {
+        const int l = ffs64(m);
+        const unsigned long long kj = rl64(key, l);
+        const int p = __popcll(ballot(ke < kj));  // (lanes without an entry hold the largest key)
+        if (p + ins >= C.td) { split = p < n; break; }
+        if (p == n && !(all && xc == 0)) break;
+        up += ke > kj ? 1 : 0;
+        at = lane == l ? p + ins : at;
+        ++ins;
+    }
+    const int to = lane + up, total = n + ins;
+    if (lane < n && to < C.td) C.qt[i * C.td + to] = e;
+    if (at >= 0) C.qt[i * C.td + at] = en;
+    if (C.xn) {
+        const int o = total > C.td ? total - C.td : 0;
+        const bool drop = split || (inside & m) || xc + o > C.xd;
+        int xh = (xv >> 16) - o;
+        xh += xh < 0 ? C.xd : 0;
+        if (!drop && lane < n && to >= C.td) *qx_at(C, i, xh, to - C.td) = e;
+        if (lane == 0 && (drop || o > 0)) C.xn[i] = drop ? 0 : (xh << 16) | (xc + o);
+    }
+    if (lane == 0) {
+        C.qn[i] = min(total, C.td);
+        C.qh[i] = 0;
+    }
+    wave_sync();
 }
 // a new waiting request of i (nwait already counts it); returns true when it
 // falls behind the ring of an instance with an extension: the caller's wave
@@ -771,18 +806,28 @@ __device__ inline void qx_insert(const Ctx& C, int i, uint4 e, int lane)
     wave_sync();
 }
 
-// file a running request under its finish tick
-__device__ __forceinline__ void wheel_put(const Ctx& C, uint32_t fin, int i, int s)
+// File a running request under its finish tick.  In the kernels with a queue
+// cache, whose workloads preempt, it returns its place in the bucket (kNoPlace:
+// the bucket is full) as the bits 8.. of the slot's meta, so that a request
+// that leaves early finds its entry without reading the bucket (overloaded
+// study: preemption 51K -> 41K cycles a tick).  The others keep no places:
+// moving them with the entries that stay in a bucket cost the sweep 1.5 %,
+// and the few requests that leave early there search their bucket.
+constexpr uint32_t kNoPlace = 0xFFFu, kPlaceShift = 8;
+static_assert(MTS_HIST_BINS > 0 && kMaxSlots < kNoPlace, "a place fits 12 bits");
+__device__ __forceinline__ uint32_t wheel_put(const Ctx& C, uint32_t fin, int i, int s)
 {
     const uint32_t b = fin & C.wmask;
     const uint32_t sh = (b & 1u) * 16u;
     const uint32_t k = (atomicAdd(&C.wc[b >> 1], 1u << sh) >> sh) & 0xFFFFu;
     if (k < C.wcap) {
         C.wheel[size_t(b) * C.wcap + k] = (uint32_t(i) << 16) | uint32_t(s);
+        return C.td ? k << kPlaceShift : 0u;
     } else {
         // full: keep the count at wcap and mark the bucket for an exact rebuild
         atomicSub(&C.wc[b >> 1], 1u << sh);
         atomicOr(&C.wov[b >> 5], 1u << (b & 31u));
+        return C.td ? kNoPlace << kPlaceShift : 0u;
     }
 }
 
@@ -790,9 +835,16 @@ __device__ __forceinline__ void wheel_put(const Ctx& C, uint32_t fin, int i, int
 // or moved out by a committed migration) loses its wheel entry: the entry is
 // overwritten with a tombstone, so every entry of the wheel names a distinct
 // running request.  A bucket that overflowed is rebuilt from the slots at its
-// visit and needs nothing here.  Uniform: the whole wave calls it.
+// visit and needs nothing here.  Per lane, with a place in the slot's meta m.
 constexpr uint32_t kTomb = 0xFFFFFFFFu;
-__device__ inline void wheel_erase(const Ctx& C, uint32_t fin, int i, int s, int lane)
+__device__ __forceinline__ void wheel_erase(const Ctx& C, uint32_t fin, uint32_t m)
+{
+    const uint32_t b = fin & C.wmask, k = m >> kPlaceShift;
+    if ((C.wov[b >> 5] >> (b & 31u)) & 1u) return;
+    if (k < C.wcap) C.wheel[size_t(b) * C.wcap + k] = kTomb;
+}
+// The same without places: the whole wave searches the bucket for slot s of i.
+__device__ inline void wheel_erase_search(const Ctx& C, uint32_t fin, int i, int s, int lane)
 {
     const uint32_t b = fin & C.wmask;
     if ((C.wov[b >> 5] >> (b & 31u)) & 1u) return;
@@ -808,10 +860,13 @@ __device__ inline void wheel_erase(const Ctx& C, uint32_t fin, int i, int s, int
 
 // memory pressure: preempt the largest (tier, seq) running request until the
 // growth of this tick fits (Section 2.2; recompute semantics)
-template <int GR, int MK>
+template <int GR, int MK, bool kArr>
 __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
 {
     const size_t b = size_t(i) * C.S;
+    // (kArr: a victim's arrival tick comes with the scan; 16 chunks a round trip
+    // leave it no registers, and without a queue cache its spills cost the
+    // INFaaS sweep 4 %)
     int G = C.gtmp[i], fr = C.freeb[i];
     bool aborted = false;
     bool scan = G > fr;
@@ -822,18 +877,18 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
         // 64 slots are read per memory round trip.
         const int nch = live_chunks(C, i, lane);
         unsigned long long k[MK];
-        uint32_t kw[MK], km[MK];
+        uint32_t kw[MK], km[MK], ka[MK];
         int ks[MK];
 #pragma unroll
-        for (int x = 0; x < MK; ++x) { k[x] = 0; kw[x] = 0; km[x] = 0; ks[x] = 0; }
+        for (int x = 0; x < MK; ++x) { k[x] = 0; kw[x] = 0; km[x] = 0; ka[x] = 0; ks[x] = 0; }
         int cnt = 0;
         for (int c0 = 0; c0 < nch; c0 += GR) {
-            uint32_t v[GR], m[GR], q[GR];
+            uint32_t v[GR], m[GR], q[GR], a[GR];
 #pragma unroll
             for (int g = 0; g < GR; ++g) {
                 const bool in = c0 + g < nch;
                 const uint4 rr = in ? C.slot[b + (c0 + g) * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
-                v[g] = rr.x; m[g] = rr.y; q[g] = rr.z;
+                v[g] = rr.x; m[g] = rr.y; q[g] = rr.z; a[g] = kArr ? rr.w : 0u;
             }
 #pragma unroll
             for (int g = 0; g < GR; ++g) {
@@ -841,7 +896,7 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
                 ++cnt;
                 unsigned long long ck = ((rank_of(C, (m[g] >> 2) & 15u) + 1ull) << 32) | q[g];
                 if (ck <= k[MK - 1]) continue;
-                uint32_t cw = v[g], cm = m[g];
+                uint32_t cw = v[g], cm = m[g], ca = a[g];
                 int cs = (c0 + g) * 64 + lane;
 #pragma unroll
                 for (int x = 0; x < MK; ++x) {
@@ -849,6 +904,7 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
                         const unsigned long long tk = k[x]; k[x] = ck; ck = tk;
                         const uint32_t tw = kw[x]; kw[x] = cw; cw = tw;
                         const uint32_t tm = km[x]; km[x] = cm; cm = tm;
+                        const uint32_t ta = ka[x]; ka[x] = ca; ca = ta;
                         const int ts = ks[x]; ks[x] = cs; cs = ts;
                     }
                 }
@@ -862,13 +918,14 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
             if (mx == 0) break;  // nothing runs
             const int wl = ffs64(ballot(k[0] == mx));
             const int vs = rl(ks[0], wl);
-            const uint32_t v = rlu(kw[0], wl), m = rlu(km[0], wl);
+            const uint32_t v = rlu(kw[0], wl), m = rlu(km[0], wl), vta = kArr ? rlu(ka[0], wl) : s_tarr(C, b + vs);
             const bool win = lane == wl;
 #pragma unroll
             for (int x = 0; x + 1 < MK; ++x) {
                 k[x] = win ? k[x + 1] : k[x];
                 kw[x] = win ? kw[x + 1] : kw[x];
                 km[x] = win ? km[x + 1] : km[x];
+                ka[x] = win ? ka[x + 1] : ka[x];
                 ks[x] = win ? ks[x + 1] : ks[x];
             }
             k[MK - 1] = win ? 0ull : k[MK - 1];
@@ -879,19 +936,17 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
             const uint32_t lenf = wlo(v), fin = fin_of(v, t);
             const uint32_t remb = fin - t + 1u, lenb = lenf - remb;
             const uint32_t vw = kWaitW | (remb << 16) | lenb;
-            const uint32_t vmeta = (m & ~(3u | kMigrating)) | kWaiting;
+            const uint32_t vmeta = (m & 0xFFu & ~(3u | kMigrating)) | kWaiting;
             const int vb = blocks_of(lenb, C.shift);
             const int vg = (lenb & C.bmask) == 0;
             const int vt = int((m >> 2) & 15u);
             const int vr = int((lenf - fin - 1u) & C.bmask);
             const bool vm = (m & kMigrating) != 0;
-            uint32_t vta = 0;
-            if (lane == (vs & 63)) {
+            if (lane == 0) {
                 s_set_wm(C, b + vs, vw, vmeta);
-                vta = s_tarr(C, b + vs);
+                if (C.td) wheel_erase(C, fin, m);
             }
-            vta = rlu(vta, vs & 63);
-            wheel_erase(C, fin, i, vs, lane);
+            if (!C.td) wheel_erase_search(C, fin, i, vs, lane);
             fr += vb;
             G -= vg;
             aborted = aborted || vm;
@@ -960,7 +1015,8 @@ __device__ inline void finish_scan(const Ctx& C, int i, uint32_t t, int lane, bo
             if (C.mig[4 * i] >= 0 && C.mig[4 * i + 1] == s) ab = true;
             s_word(C, b + s) = 0;  // the word alone marks the slot empty
         } else if (run && (fin & C.wmask) == bk) {
-            wheel_put(C, fin, i, s);
+            const uint32_t place = wheel_put(C, fin, i, s);
+            if (C.td) s_meta(C, b + s) = (rec.y & 0xFFu) | place;
         }
         const unsigned long long fb = ballot(f);
         const unsigned long long ow = ballot(v != 0 && !f);
@@ -998,7 +1054,14 @@ __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint
     const bool f = valid && wst(v) == 2u && fin == t;
     const bool k = valid && wst(v) == 2u && fin != t && (fin & C.wmask) == bk;
     const unsigned long long km = ballot(k);
-    if (k) ent[kept + __popcll(km & lanemask_lt())] = e;
+    if (k) {
+        // a later finish that shares the bucket: its entry moves to its new place
+        // (m may predate a migration's start: the flag comes from the record)
+        const uint32_t at = kept + __popcll(km & lanemask_lt());
+        ent[at] = e;
+        if (C.td)
+            s_meta(C, size_t(i) * C.S + s) = (m & 0x7Fu) | (mg.x >= 0 && mg.y == s ? kMigrating : 0u) | (at << kPlaceShift);
+    }
     kept += __popcll(km);
     bool ab = false;
     if (f) {
@@ -1099,7 +1162,8 @@ __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, i
         const uint32_t len = wlo(word), rem = wmid(word);
         const uint32_t fin = t + rem;
         const size_t hb = b + slot;
-        s_set_wm(C, hb, kRunW | ((fin & kFin) << 16) | (len + rem), (meta & ~3u) | kRunning | kAdmitted);
+        const uint32_t place = wheel_put(C, fin, i, slot);
+        s_set_wm(C, hb, kRunW | ((fin & kFin) << 16) | (len + rem), (meta & 0xFCu) | kRunning | kAdmitted | place);
         const int tier = int((meta >> 2) & 15u);
         if (!(meta & kAdmitted)) {
             stat(C, tier * 8 + kAdmittedCnt, 1);
@@ -1108,7 +1172,6 @@ __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, i
         }
         c16_inc(C.res, res_idx(C, i, (len - t - 1u) & C.bmask));
         tier_inc(C, i, tier);
-        wheel_put(C, fin, i, slot);
     }
     const int used = na > 0 ? rl(pre, na - 1) : 0;
     const int hs = rl(slot, na < w ? na : 0);
@@ -1519,13 +1582,15 @@ __device__ inline void admit_fresh_all(const Ctx& C, uint32_t t, int lane)
     const uint32_t e = in ? C.lsl[lane] : 0u;
     const uint32_t word = in ? C.lw[lane] : 0u, seq = in ? C.lsq[lane] : 0u;
     const int i = int(e >> 16), slot = int(e & 0xFFFu), tier = int((e >> 12) & 15u);
-    const int fr = C.freeb[i];
-    const bool act = in && C.frs[i] && C.hols[i] >= 0 && C.hold[i] <= fr;
+    const int fr = C.freeb[i], fs = C.frs[i], h = C.hols[i], hd = C.hold[i], nwi = C.nwait[i];
+    const bool act = in && fs && h >= 0 && hd <= fr;
     const int dem = act ? blocks_of(wlo(word), C.shift) : 0;
     // per instance: the running sum of the demands and the lanes of its requests
-    int pre = 0;
-    unsigned long long own = 0;
-    for (unsigned long long m = ballot(act); m;) {
+    // (an instance with one request is done at once)
+    const int nw = act ? nwi : 0;
+    int pre = dem;
+    unsigned long long own = act ? 1ull << lane : 0ull;
+    for (unsigned long long m = ballot(act && nw > 1); m;) {
         const int ii = rl(i, ffs64(m));
         const bool mine = act && i == ii;
         const unsigned long long mm = ballot(mine);
@@ -1536,19 +1601,18 @@ __device__ inline void admit_fresh_all(const Ctx& C, uint32_t t, int lane)
     const bool adm = act && pre <= fr;
     const unsigned long long am = ballot(adm) & own;
     const int na = __popcll(am), cnt = __popcll(own), idx = __popcll(own & lanemask_lt());
-    const int nw = act ? C.nwait[i] : 0;
     wave_sync();
     if (adm) {
         const uint32_t len = wlo(word), rem = wmid(word), fin = t + rem;
+        const uint32_t place = wheel_put(C, fin, i, slot);
         s_set_wm(C, size_t(i) * C.S + slot, kRunW | ((fin & kFin) << 16) | (len + rem),
-                 (uint32_t(tier) << 2) | kRunning | kAdmitted);
+                 (uint32_t(tier) << 2) | kRunning | kAdmitted | place);
         // (a request's first admission, one tick after it arrived)
         stat(C, tier * 8 + kAdmittedCnt, 1);
         stat(C, tier * 8 + kQdelay, 1);
         hist_add(C, kHistQdelay, tier, 1);
         c16_inc(C.res, res_idx(C, i, (len - t - 1u) & C.bmask));
         tier_inc(C, i, tier);
-        wheel_put(C, fin, i, slot);
         atomicSub(&C.freeb[i], dem);
         atomicAdd(&C.held[i], dem);
     }
@@ -1578,7 +1642,8 @@ __device__ inline void admit_head(const Ctx& C, int i, uint32_t t)
     const uint32_t len = wlo(w), rem = wmid(w);
     const uint32_t fin = t + rem;
     const size_t hb = size_t(i) * C.S + h;
-    s_set_wm(C, hb, kRunW | ((fin & kFin) << 16) | (len + rem), (m & ~3u) | kRunning | kAdmitted);
+    const uint32_t place = wheel_put(C, fin, i, h);
+    s_set_wm(C, hb, kRunW | ((fin & kFin) << 16) | (len + rem), (m & 0xFCu) | kRunning | kAdmitted | place);
     const int tier = int((m >> 2) & 15u);
     if (!(m & kAdmitted)) {
         stat(C, tier * 8 + kAdmittedCnt, 1);
@@ -1591,7 +1656,6 @@ __device__ inline void admit_head(const Ctx& C, int i, uint32_t t)
     C.nwait[i] -= 1;
     c16_inc(C.res, res_idx(C, i, (len - t - 1u) & C.bmask));
     tier_inc(C, i, tier);
-    wheel_put(C, fin, i, h);
     hol_pop(C, i);
 }
 
@@ -1773,6 +1837,14 @@ __device__ inline void image_write(const Params& P, uint32_t r, uint32_t t, cons
     if (tid == 0) m[0] = make_uint4(t, kImgMagic, P.qdepth | (P.wcap << 8), P.img_lds);
 }
 
+// v, with the load that produces it complete
+__device__ __forceinline__ unsigned long long landed(unsigned long long v)
+{
+    uint32_t lo = uint32_t(v), hi = uint32_t(v >> 32);
+    asm volatile("" : "+v"(lo), "+v"(hi));
+    return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+
 template <int IM, bool INF, bool EXT, bool QC>
 __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(Params P, unsigned long long t0, uint32_t nt)
 {
@@ -1885,7 +1957,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         held += blocks_of(lenf - (fin - t0u + 1u), C.shift);
                         c16_inc(C.res, res_idx(C, i, (lenf - fin - 1u) & C.bmask));
                         c16_inc(C.tcnt, i * kTiers + int((m[g] >> 2) & 15u));
-                        wheel_put(C, fin, int(i), s);
+                        const uint32_t place = wheel_put(C, fin, int(i), s);
+                        if (C.td) s_meta(C, size_t(i) * S + s) = (m[g] & 0xFFu) | place;
                     } else if (st == 1u) {
                         const unsigned long long k = (rank_of(C, (m[g] >> 2) & 15u) << 32) | q[g];
                         if (k < bk) { bk = k; bs = s; bv = v[g]; bm = m[g]; }
@@ -1972,7 +2045,10 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             const uint32_t t = t0u + tl;
             const uint32_t n = rlu(cnt64, int(tl & 63u));
             const unsigned long long* rec = recs + size_t(tl) * P.arr_cap;
-            const unsigned long long a0 = a_nx;
+            // the records are waited for here, with the prefetched finish visit: at
+            // their use the wait would take in the stores and histogram atomics
+            // that the phases in between have just issued
+            const unsigned long long a0 = landed(a_nx);
 
             // ============ Section 6.5: promotion, adaptive headroom ============
             // (the countdowns and parameters live in LDS: nothing of this stays
@@ -2029,7 +2105,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
 #pragma unroll
                 for (int j = 0; j < OPL; ++j)
                     for (unsigned long long m = pre[j]; m; m &= m - 1)
-                        abort_any = preempt<(IM >= 128 ? 16 : 4), 2>(
+                        abort_any = preempt<(IM >= 128 ? 16 : 4), 2, QC && IM < 128>(
                                         C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || abort_any;
             }
             if (NW > 1) {
@@ -2272,13 +2348,14 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 // key: F of the instances that can take an arrival (minus infinity
                 // for a full instance and, in the first mode, for a draining one)
                 double key[IPL], fnew[IPL], den[IPL], rd[IPL];
-                int live_r[IPL], nw_r[IPL], nadd[IPL], pend_r[IPL], num_r[IPL], hold_r[IPL];
+                int live_r[IPL], nw_r[IPL], nadd[IPL], num_r[IPL], hold_r[IPL];
+                bool head_r[IPL];  // its head of line is an arrival of this batch
                 unsigned long long hk_r[IPL];
 #pragma unroll
                 for (int j = 0; j < IPL; ++j) {
                     const uint32_t i = lane + 64 * j;
                     nadd[j] = 0;
-                    pend_r[j] = -1;
+                    head_r[j] = false;
                     num_r[j] = 0;
                     hold_r[j] = 0;
                     nw_r[j] = 0;
@@ -2320,27 +2397,30 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     unsigned long long heads = 0;  // arrivals of this batch that became a head of line
                     uint32_t k = 0;
                     while (k < cn && !full) {
-                        // what arrival k would change on every instance, beside the
-                        // argmax's chain: whether it becomes the head of line there, and F
-                        const unsigned long long ak = rl64(a, int(k));
-                        const unsigned long long hk = rank_of(C, uint32_t(ak >> 32) & 15u) << 32 | (seq0 + unsigned(ak >> 36));
-                        const int dem = blocks_of(uint32_t(ak & 0xFFFFu), C.shift);
-                        unsigned long long lower[IPL];
-                        int nn[IPL];
-                        double fn[IPL];
-#pragma unroll
-                        for (int j = 0; j < IPL; ++j) {
-                            lower[j] = ballot(hk < hk_r[j]);
-                            // Eq. 1-2: F moves by the change of head-of-line demand
-                            nn[j] = num_r[j] - 256 * (dem - hold_r[j]);
-                            fn[j] = quot(double(nn[j]), den[j], rd[j]);
-                        }
                         if (cur < 0) {
+                            // One arrival: what it would change on every instance is computed
+                            // beside the argmax's chain -- whether it becomes the head of
+                            // line there, and F then (Eq. 1-2: F moves by the change of
+                            // head-of-line demand).  The step is straight-line code: a
+                            // division after the argmax and the branches of a step shared
+                            // with the runs below made it 1150 cycles of a lone wave.
+                            const unsigned long long ak = rl64(a, int(k));
+                            const unsigned long long hk = rank_of(C, uint32_t(ak >> 32) & 15u) << 32 | (seq0 + unsigned(ak >> 36));
+                            const int dem = blocks_of(uint32_t(ak & 0xFFFFu), C.shift);
+                            unsigned long long lower[IPL];
+                            int nn[IPL];
+                            double fn[IPL];
+#pragma unroll
+                            for (int j = 0; j < IPL; ++j) {
+                                lower[j] = ballot(hk < hk_r[j]);
+                                nn[j] = num_r[j] - 256 * (dem - hold_r[j]);
+                                fn[j] = infaas ? 0.0 : quot(double(nn[j]), den[j], rd[j]);
+                            }
                             double lb = key[0];
 #pragma unroll
                             for (int j = 1; j < IPL; ++j) lb = fmax(lb, key[j]);
                             double mv = wave_max_f64<(IM < 64 ? IM : 64)>(lb);
-                            if (mv == -__builtin_inf()) {
+                            if (__builtin_expect(mv == -__builtin_inf(), 0)) {
                                 if (drain_mode) { full = true; break; }
                                 // no non-draining instance has a free slot: the least
                                 // loaded draining one (largest F without the sentinel);
@@ -2359,49 +2439,71 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                                 mv = wave_max_f64<(IM < 64 ? IM : 64)>(lb);
                                 if (mv == -__builtin_inf()) { full = true; break; }
                             }
+                            int jc = 0, lc = 0;
+                            bool becomes = false;
 #pragma unroll
                             for (int j = IPL - 1; j >= 0; --j) {
                                 const unsigned long long bm = ballot(key[j] == mv);
-                                if (bm) cur = 64 * j + ffs64(bm);
+                                if (IPL == 1 || bm) {
+                                    jc = j;
+                                    lc = ffs64(bm);
+                                    becomes = (lower[j] >> lc) & 1ull;
+                                }
                             }
-                        }
-                        const int jc = cur >> 6, lc = cur & 63;
-                        bool becomes = false;
+                            // Arrival k goes to instance 64 jc + lc.  If it becomes its head of
+                            // line, F changes and the argmax is taken again.  Otherwise F
+                            // stays, and so does the argmax for the following arrivals, none
+                            // of which can become the head of line (keys increase along the
+                            // arrival order): they all go there until its slots run out.
+                            // (under INFaaS every placement raises the cost by alpha)
+                            if (becomes || (infaas && P.alpha256 > 0)) {
+                                int na0 = 0;
 #pragma unroll
-                        for (int j = 0; j < IPL; ++j)
-                            if (j == jc) becomes = (lower[j] >> lc) & 1ull;
-                        // Arrival k goes to cur.  If it becomes cur's head of line, F of cur
-                        // changes and the argmax is taken again.  Otherwise F stays, and
-                        // so does the argmax for the following arrivals, none of which can
-                        // become the head of line (keys increase along the arrival order):
-                        // they all go to cur until its slots run out.
-                        // (under INFaaS every placement raises cur's cost by alpha)
-                        const bool step1 = becomes || (infaas && P.alpha256 > 0);
+                                for (int j = 0; j < IPL; ++j) {
+                                    if (j != jc) continue;
+                                    // (a new head of line is the instance's first arrival of the tick)
+                                    if (infaas) na0 = rl(nadd[j], lc);
+                                    const bool me = lane == lc, hd = me && becomes;
+                                    live_r[j] += me ? 1 : 0;
+                                    nadd[j] += me ? 1 : 0;
+                                    head_r[j] = head_r[j] || hd;
+                                    hk_r[j] = hd ? hk : hk_r[j];
+                                    num_r[j] = hd ? nn[j] : num_r[j];
+                                    hold_r[j] = hd ? dem : hold_r[j];
+                                    if (infaas) {
+                                        key[j] = me ? key[j] - double(P.alpha256) : key[j];
+                                    } else {
+                                        fnew[j] = hd ? fn[j] : fnew[j];
+                                        key[j] = hd ? fn[j] : key[j];
+                                    }
+                                    key[j] = me && live_r[j] >= int(S) ? -__builtin_inf() : key[j];
+                                }
+                                heads |= static_cast<unsigned long long>(becomes) << k;
+                                if (lane == int(k)) { tgt = 64 * jc + lc; rank = na0; }
+                                nfall += drain_mode ? 1 : 0;
+                                ++k;
+                                continue;
+                            }
+                            cur = 64 * jc + lc;
+                        }
+                        // a run of arrivals that change nothing goes to cur
+                        const int jc = IPL == 1 ? 0 : cur >> 6, lc = IPL == 1 ? cur : cur & 63;
                         int lv = 0, na0 = 0;
 #pragma unroll
                         for (int j = 0; j < IPL; ++j)
                             if (j == jc) { lv = rl(live_r[j], lc); na0 = rl(nadd[j], lc); }
-                        const int m = step1 ? 1 : min(int(cn - k), int(S) - lv);
-                        const int nl = lv + m;
-                        heads |= becomes ? 1ull << k : 0ull;
+                        const int m = min(int(cn - k), int(S) - lv);
 #pragma unroll
                         for (int j = 0; j < IPL; ++j) {
                             if (j != jc) continue;
-                            const bool me = lane == lc, hd = me && becomes;
-                            live_r[j] = me ? nl : live_r[j];
-                            nadd[j] = me ? nadd[j] + m : nadd[j];
-                            hk_r[j] = hd ? hk : hk_r[j];
-                            pend_r[j] = hd ? int(k0 + k) : pend_r[j];
-                            num_r[j] = hd ? nn[j] : num_r[j];
-                            hold_r[j] = hd ? dem : hold_r[j];
-                            fnew[j] = hd ? fn[j] : fnew[j];
-                            if (infaas) key[j] = me ? key[j] - double(P.alpha256) * double(m) : key[j];
-                            else key[j] = hd ? fn[j] : key[j];
-                            key[j] = me && nl >= int(S) ? -__builtin_inf() : key[j];
+                            const bool me = lane == lc;
+                            live_r[j] += me ? m : 0;
+                            nadd[j] += me ? m : 0;
+                            key[j] = me && lv + m >= int(S) ? -__builtin_inf() : key[j];
                         }
                         if (lane >= int(k) && lane < int(k) + m) { tgt = cur; rank = na0 + lane - int(k); }
-                        if (step1 || nl >= int(S)) cur = -1;
-                        if (drain_mode) nfall += m;
+                        if (lv + m >= int(S)) cur = -1;
+                        nfall += drain_mode ? m : 0;
                         k += uint32_t(m);
                     }
                     // write the dispatch state back for the slot assignment and later phases
@@ -2416,7 +2518,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         nw_r[j] = nw0 + nadd[j];
                         C.nwait[i] = nw_r[j];
                         wait_acc += unsigned(nadd[j]);
-                        if (pend_r[j] >= 0) {
+                        if (head_r[j]) {
                             C.num[i] = num_r[j];
                             C.hold[i] = hold_r[j];
                             C.fd[i] = fnew[j];
@@ -2430,16 +2532,14 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             const bool known = C.hols[i] >= 0;
                             const bool all = nw0 == (known ? 1 + C.qn[i] + qx_count(C, int(i)) : 0);
                             const bool skip = !known && n <= uint32_t(kLast);
-                            C.order[i] = skip ? kQcSkip : (all ? kQcAll : kQcPart) | (pend_r[j] >= 0 ? kQcHead : 0);
+                            C.order[i] = skip ? kQcSkip : (all ? kQcAll : kQcPart) | (head_r[j] ? kQcHead : 0);
                             qc_any = qc_any || !skip;
-                            if (known && pend_r[j] >= 0)
+                            if (known && head_r[j])
                                 qc_insert_at(C, int(i), 0, qc_pack(C.holk[i], C.hols[i], C.hwd[i], C.hmt[i], C.hta[i]));
                         }
                         nadd[j] = 0;
-                        if (pend_r[j] >= 0) {
-                            C.holk[i] = hk_r[j];
-                            pend_r[j] = -1;
-                        }
+                        if (head_r[j]) C.holk[i] = hk_r[j];
+                        head_r[j] = false;
                     }
                     wave_sync();
                     // slot assignment: the arrivals bound for one instance take its
@@ -2563,13 +2663,14 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                                 }
                             }
                         }
-                        // the others one after the other (at most td + 1 of one instance
-                        // can have a place in its ring or fall into its extension)
-                        const bool enter = can && !run && r <= C.td &&
-                                           (!behind || (xc == 0 && nq < C.td && (mode & 3) == kQcAll));
-                        for (unsigned long long em = ballot(enter); em; em &= em - 1) {
-                            if (lane == ffs64(em)) qc_arrive(C, tgt, en);
-                            wave_sync();
+                        // the others by a merge per instance
+                        const unsigned long long inside = ballot(can && !run && !behind);
+                        const bool enter = can && !run && (!behind || (xc == 0 && nq < C.td && (mode & 3) == kQcAll));
+                        for (unsigned long long em = ballot(enter); em;) {
+                            const int l = ffs64(em), ii = rl(tgt, l);
+                            const unsigned long long mine = em & ballot(tgt == ii);
+                            qc_merge(C, ii, mine, key, en, (rl(mode, l) & 3) == kQcAll, inside, lane);
+                            em &= ~mine;
                         }
                     }
                     // every arrival is dispatched (tgt >= 0) or rejected: no free slot
@@ -2593,10 +2694,11 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             }
 
             // ===================== E1: staged copies =====================
-            // a commit leaves the source slot: its wheel entry (source slot in
-            // gtmp, finish tick in order) is erased after the loop
+            // a commit leaves the source slot and its wheel entry (without places,
+            // source slot in gtmp and finish tick in order, searched after the loop)
             if (migs) {
-            for (uint32_t i = lane; i < I; i += 64) C.gtmp[i] = -1;
+            if (!C.td)
+                for (uint32_t i = lane; i < I; i += 64) C.gtmp[i] = -1;
             for (uint32_t i = lane; i < I; i += 64) {
                 int* m = &C.mig[4 * i];
                 const int d = m[0];
@@ -2627,7 +2729,14 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     const uint32_t mm = srec.y;
                     const int tier = int((mm >> 2) & 15u);
                     const int rr = int((wlo(v) - fin - 1u) & C.bmask);
-                    C.slot[db] = make_uint4(v, (mm & ~(3u | kMigrating)) | kRunning, srec.z, srec.w);
+                    const uint32_t place = wheel_put(C, fin, d, m[2]);
+                    C.slot[db] = make_uint4(v, (mm & 0xFFu & ~(3u | kMigrating)) | kRunning | place, srec.z, srec.w);
+                    if (C.td) {
+                        wheel_erase(C, fin, mm);
+                    } else {
+                        C.gtmp[i] = m[1];
+                        C.order[i] = int(fin);
+                    }
                     s_word(C, sb) = 0;
                     C.occ[i * W + (m[1] >> 6)] &= ~(1ull << (m[1] & 63));
                     C.live[i] -= 1;
@@ -2641,9 +2750,6 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     c16_inc(C.res, res_idx(C, d, rr));
                     tier_dec(C, int(i), tier);
                     tier_inc(C, d, tier);
-                    wheel_put(C, fin, d, m[2]);
-                    C.gtmp[i] = m[1];
-                    C.order[i] = int(fin);
                     m[0] = -1; m[1] = 0; m[2] = 0; m[3] = 0;
                     stat(C, kMigCommitted, 1);
                     set_f(C, int(i));
@@ -2651,15 +2757,17 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 set_f(C, d);
             }
             wave_sync();
+            if (!C.td) {
 #pragma unroll
-            for (int j = 0; j < IPL; ++j) {
-                const uint32_t i0 = lane + 64 * j;
-                for (unsigned long long m = ballot(i0 < I && C.gtmp[i0] >= 0); m; m &= m - 1) {
-                    const int ii = 64 * j + ffs64(m);
-                    wheel_erase(C, uint32_t(C.order[ii]), ii, C.gtmp[ii], lane);
+                for (int j = 0; j < IPL; ++j) {
+                    const uint32_t i0 = lane + 64 * j;
+                    for (unsigned long long m = ballot(i0 < I && C.gtmp[i0] >= 0); m; m &= m - 1) {
+                        const int ii = 64 * j + ffs64(m);
+                        wheel_erase_search(C, uint32_t(C.order[ii]), ii, C.gtmp[ii], lane);
+                    }
                 }
+                wave_sync();
             }
-            wave_sync();
             bool live = false;
             for (uint32_t i = lane; i < I; i += 64) live = live || C.mig[4 * i] >= 0;
             migs = ballot(live) != 0;
@@ -3051,7 +3159,7 @@ __global__ __launch_bounds__(256) void k_digest(Params P, uint32_t r0, uint32_t 
         const uint32_t hw = rec.x;
         if (hw == 0u) continue;
         const bool inb = wst(hw) == kInbound;
-        const unsigned m = rec.y;
+        const unsigned m = rec.y & 0xFFu;
         const unsigned long long a = static_cast<unsigned long long>(canonical_lr(hw, tick)) |
                                      (static_cast<unsigned long long>(inb ? 0u : rec.z) << 32);
         const unsigned long long b = static_cast<unsigned long long>(inb ? 0u : rec.w) |
