@@ -2439,6 +2439,49 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                                 mv = wave_max_f64<(IM < 64 ? IM : 64)>(lb);
                                 if (mv == -__builtin_inf()) { full = true; break; }
                             }
+                            if (INF && IPL == 1 && P.alpha256 > 0) {
+                                // INFaaS: a placement raises its instance's cost by alpha
+                                // whatever the arrival, so the instances less than alpha
+                                // above the cheapest are all taken once, in (cost, index)
+                                // order, before any is taken again: one round places as
+                                // many arrivals as there are such instances.  (An argmax per
+                                // arrival was 12.3K of the INFaaS sweep's 41K cycles a tick.)
+                                const unsigned long long win = ballot(key[0] > mv - double(P.alpha256));
+                                int rk = 0;
+                                for (unsigned long long w = win; w; w &= w - 1) {
+                                    const int l = ffs64(w);
+                                    const double fl = __hiloint2double(rl(__double2hiint(key[0]), l), rl(__double2loint(key[0]), l));
+                                    rk += (fl > key[0]) | ((fl == key[0]) & (l < lane)) ? 1 : 0;
+                                }
+                                const int m = min(int(cn - k), __popcll(win));
+                                const bool pick = ((win >> lane) & 1ull) && rk < m;
+                                const unsigned long long pm = ballot(pick);
+                                // the instance of rank r goes to lane k + r, the others elsewhere
+                                int dest = __popcll(~pm & lanemask_lt());
+                                dest += dest < int(k) ? 0 : m;
+                                dest = pick ? int(k) + rk : dest;
+                                const int ti = __builtin_amdgcn_ds_permute(dest * 4, lane);
+                                const int tn = __builtin_amdgcn_ds_permute(dest * 4, nadd[0]);
+                                // and its arrival to the instance
+                                const uint32_t alo = uint32_t(__builtin_amdgcn_ds_bpermute(dest * 4, int(uint32_t(a))));
+                                const uint32_t ahi = uint32_t(__builtin_amdgcn_ds_bpermute(dest * 4, int(uint32_t(a >> 32))));
+                                const unsigned long long hi = rank_of(C, ahi & 15u) << 32 | (seq0 + (ahi >> 4));
+                                const bool hd = pick && hi < hk_r[0];
+                                const unsigned long long hm = ballot(hd);
+                                live_r[0] += pick ? 1 : 0;
+                                nadd[0] += pick ? 1 : 0;
+                                head_r[0] = head_r[0] || hd;
+                                hk_r[0] = hd ? hi : hk_r[0];
+                                hold_r[0] = hd ? blocks_of(alo & 0xFFFFu, C.shift) : hold_r[0];
+                                key[0] = pick ? key[0] - double(P.alpha256) : key[0];
+                                key[0] = pick && live_r[0] >= int(S) ? -__builtin_inf() : key[0];
+                                const bool mine = lane >= int(k) && lane < int(k) + m;
+                                if (mine) { tgt = ti; rank = tn; }
+                                heads |= ballot(mine && ((hm >> (ti & 63)) & 1ull));
+                                nfall += drain_mode ? m : 0;
+                                k += uint32_t(m);
+                                continue;
+                            }
                             int jc = 0, lc = 0;
                             bool becomes = false;
 #pragma unroll

@@ -47,6 +47,9 @@ WIDE_BURSTS = dict(kind="gamma_poisson", mean=120.0, cv=3.0)
     (_cfg(5, 192, 400, BURSTS, K=1), (1, 7)),
     (_cfg(16, 128, 300, BURSTS, blind=1), (3, 7)),
     (_cfg(16, 128, 300, POISSON, infaas=True), (1, 7)),
+    # INFaaS rounds: bursts of several batches, instances that fill up
+    (_cfg(5, 64, 300, BURSTS, infaas=True), (0, 7)),
+    (_cfg(64, 64, 200, dict(kind="gamma_poisson", mean=90.0, cv=2.0), infaas=True), (0, 3)),
     # the eight-wave kernels: piles beyond the ring go on in the extension,
     # preempted and migrated requests enter it in the middle
     (_cfg(65, 256, 420, WIDE_BURSTS), (1, 7, 15)),
