@@ -32,8 +32,10 @@ __device__ inline void philox4x64_10(unsigned long long x[4], unsigned long long
     constexpr unsigned long long W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const unsigned long long lo0 = M0 * x[0], hi0 = __umul64hi(M0, x[0]);
-        const unsigned long long lo1 = M1 * x[2], hi1 = __umul64hi(M1, x[2]);
+        // both halves of a 64 x 64 product at once
+        const unsigned __int128 p0 = static_cast<unsigned __int128>(M0) * x[0], p1 = static_cast<unsigned __int128>(M1) * x[2];
+        const unsigned long long lo0 = static_cast<unsigned long long>(p0), hi0 = static_cast<unsigned long long>(p0 >> 64);
+        const unsigned long long lo1 = static_cast<unsigned long long>(p1), hi1 = static_cast<unsigned long long>(p1 >> 64);
         const unsigned long long n0 = hi1 ^ x[1] ^ k0, n2 = hi0 ^ x[3] ^ k1;
         x[0] = n0; x[1] = lo1; x[2] = n2; x[3] = lo0;
         k0 += W0; k1 += W1;
