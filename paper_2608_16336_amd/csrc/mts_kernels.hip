@@ -2623,18 +2623,20 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         // wherever their words lie)
                         int rk = rank, wi = -1;
                         unsigned long long fw = 0;
-                        for (uint32_t w0 = 0; w0 < W && wi < 0; w0 += 4) {
+                        for (uint32_t w0 = 0; w0 < W; w0 += 4) {
                             unsigned long long wd[4];
 #pragma unroll
                             for (int k = 0; k < 4; ++k) wd[k] = w0 + k < W ? C.occ[tgt * W + w0 + k] : kNone;
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const int z = 64 - __popcll(wd[k]);
-                                const bool here = wi < 0 && rk < z;
-                                fw = here ? ~wd[k] : fw;
-                                wi = here ? int(w0 + k) : wi;
-                                rk -= wi < 0 ? z : 0;
-                            }
+                            // empty slots of the first one, two, three and four words
+                            const int c0 = 64 - __popcll(wd[0]), c1 = c0 + 64 - __popcll(wd[1]),
+                                      c2 = c1 + 64 - __popcll(wd[2]), c3 = c2 + 64 - __popcll(wd[3]);
+                            if (rk >= c3) { rk -= c3; continue; }
+                            const bool h = rk >= c1, q = rk >= (h ? c2 : c0);
+                            const unsigned long long lo = h ? wd[2] : wd[0], hi = h ? wd[3] : wd[1];
+                            fw = ~(q ? hi : lo);
+                            rk -= h ? (q ? c2 : c1) : (q ? c0 : 0);
+                            wi = int(w0) + (h ? 2 : 0) + (q ? 1 : 0);
+                            break;
                         }
                         if (wi >= 0) s = wi * 64 + kth_set_bit(fw, rk);
                     }
