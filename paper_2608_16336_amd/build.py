@@ -19,7 +19,7 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
 # (freeness keys are finite or -inf), so its maxima need no NaN quieting
 EXTRA = {"mts_kernels.hip": ["-fno-honor-nans", "-Wno-unused-function", "-Wno-unneeded-internal-declaration"]}
 # the step kernel's instantiations, compiled as this many units of their own
-STEP_PARTS = 8
+STEP_PARTS = 12
 
 
 def _run(cmd):

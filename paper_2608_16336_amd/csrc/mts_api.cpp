@@ -28,6 +28,8 @@ struct mts_ctx {
     uint32_t wcap_max = 0;             // entries per bucket the layout reserves
     uint32_t blocks = 0;               // step-kernel blocks (one wave each); 0 = automatic
     uint32_t qdepth = 0;               // queue-cache entries per instance (chosen at create)
+    bool four_auto = false;            // four waves per replica chosen at create
+    bool four_waves = false;           // and in use (mts_set_launch can ask for one)
     int device = 0;
     hipStream_t last = nullptr;
     std::vector<uint16_t> group_of;
@@ -142,7 +144,7 @@ Layout make_layout(const mts_cfg& c, const Tables& T, uint32_t R, uint32_t chunk
     // cache that mts_create picks
     {
         const size_t lds = lds_bytes(c.n_instances, c.slots_per_instance, c.block_tokens, wsz, c.dispatch_policy,
-                                     I >= 128 ? 15 : 7, c.adapt_epoch != 0 || c.promote_period != 0);
+                                     I >= 128 ? 15 : 7, c.adapt_epoch != 0 || c.promote_period != 0, I > 64 ? 8 : 4);
         const size_t n = lds / 16 + 1;
         L.img_n = size_t(R) * n * 16 <= kImgBudget ? uint32_t(n) : 0;
     }
@@ -187,6 +189,7 @@ Params make_params(const mts_ctx* h)
     p.pen_over = c.infaas_pen_overloaded;
     p.pen_intf = c.infaas_pen_interfered;
     p.qdepth = h->qdepth;
+    p.nw = h->I > 64 ? 8 : h->four_waves && h->qdepth ? 4 : 1;
     p.blind = c.tier_blind;
     p.zero_lowest = c.zero_lowest_tier;
     p.adapt_epoch = c.adapt_epoch;
@@ -240,6 +243,22 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? MTS_OK : MTS_EDEVICE; }
 
 // the step kernel keeps adaptive-headroom or promotion state in LDS
 bool ext_state(const mts_cfg& c) { return c.adapt_epoch != 0 || c.promote_period != 0; }
+
+double table_mean(const Table& t)
+{
+    double m = t.base;
+    for (size_t j = 0; j + 1 < t.q.size(); ++j) m += 1.0 - double(t.q[j]) / 4294967296.0;
+    return m;
+}
+
+// KV blocks that the arrivals would hold on average, were all of them admitted
+// at once, over the cluster's blocks: above 1 the queues grow without end
+double expected_load(const mts_ctx& x)
+{
+    const double out = table_mean(x.tables.output), len = table_mean(x.tables.prompt) + 0.5 * out;
+    const double blocks = len / x.cfg.block_tokens + 0.5;
+    return x.cfg.arrival_mean * out * blocks / (double(x.cfg.kv_blocks) * x.I);
+}
 
 int prepare(const mts_cfg* cfg, mts_ctx& x)
 {
@@ -306,7 +325,7 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
         delete x;
         return MTS_EDEVICE;
     }
-    if (lds_bytes(x->I, x->S, x->cfg.block_tokens, x->wsz, x->cfg.dispatch_policy, 0, ext_state(x->cfg)) > size_t(max_lds)) { delete x; return MTS_EINVAL; }
+    if (lds_bytes(x->I, x->S, x->cfg.block_tokens, x->wsz, x->cfg.dispatch_policy, 0, ext_state(x->cfg), x->I > 64 ? 8 : 1) > size_t(max_lds)) { delete x; return MTS_EINVAL; }
     // queue cache depth: the deepest of 7, 3, 1 (15, 11, 7, 3, 1 for 128 or
     // more instances, whose long burst queues it spares rescans of 2048
     // slots) that keeps the step kernel's blocks per CU, or that leaves every
@@ -328,9 +347,22 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
         for (uint32_t d : {15u, 11u, 7u, 3u, 1u}) {
             if (d > 7 && x->I < 128) continue;
             p.qdepth = d;
-            if (lds_bytes(x->I, x->S, x->cfg.block_tokens, x->wsz, x->cfg.dispatch_policy, d, ext_state(x->cfg)) > size_t(max_lds)) continue;
+            if (lds_bytes(x->I, x->S, x->cfg.block_tokens, x->wsz, x->cfg.dispatch_policy, d, ext_state(x->cfg), p.nw) > size_t(max_lds)) continue;
             const int nb = step_blocks_per_cu(p);
             if (nb >= base || (nb > 1 && uint64_t(nb - 1) * uint64_t(cus) >= x->R)) { x->qdepth = d; break; }
+        }
+        // four waves per replica for overloaded clusters of 16 or more
+        // instances, when every replica still stays resident: preemptions and
+        // rescans of different instances then run side by side (960 replicas of
+        // the overloaded sweep: 29.9 -> 21.6 ms per 500 ticks; 1024 of gauss10
+        // with extensions: 5.15 -> 4.39 ms per 250).  Below the load limit such
+        // events are rare and the barriers cost more than they give; the four
+        // instances of tiny lose too (6.56 -> 7.36 ms per 1000 ticks).
+        if (x->I >= 16 && x->I <= 64 && x->qdepth) {
+            p.qdepth = x->qdepth;
+            p.nw = 4;
+            x->four_auto = uint64_t(step_blocks_per_cu(p)) * uint64_t(cus) >= x->R && expected_load(*x) > 0.9;
+            x->four_waves = x->four_auto;
         }
     }
 
@@ -415,8 +447,13 @@ int mts_set_launch(mts_handle h, uint32_t threads, uint32_t blocks)
 {
     if (!h) return MTS_EINVAL;
     // the block is the replica's waves: its size is fixed by the instance count
-    if (threads != 0 && int(threads) != step_threads(make_params(h))) return MTS_EINVAL;
+    // (64 asks for one wave where create chose four)
+    Params p = make_params(h);
+    const bool one = h->four_auto && threads == 64;
+    p.nw = h->four_auto && h->qdepth ? 4 : p.nw;
+    if (threads != 0 && !one && int(threads) != step_threads(p)) return MTS_EINVAL;
     if (blocks > h->R) return MTS_EINVAL;
+    h->four_waves = h->four_auto && !one;
     h->blocks = blocks;
     return MTS_OK;
 }
@@ -443,7 +480,7 @@ int mts_set_queue_cache(mts_handle h, uint32_t depth)
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device) != hipSuccess)
         return MTS_EDEVICE;
-    if (lds_bytes(h->I, h->S, h->cfg.block_tokens, h->wsz, h->cfg.dispatch_policy, depth, ext_state(h->cfg)) > size_t(max_lds))
+    if (lds_bytes(h->I, h->S, h->cfg.block_tokens, h->wsz, h->cfg.dispatch_policy, depth, ext_state(h->cfg), h->I > 64 ? 8 : 4) > size_t(max_lds))
         return MTS_EINVAL;
     hipError_t e = hipStreamSynchronize(h->last);
     if (e != hipSuccess) return MTS_EDEVICE;

@@ -102,6 +102,7 @@ struct Params {
     long long alpha256, beta, gamma256;  // INFaaS weights (alpha and gamma times 256)
     uint32_t pen_over, pen_intf;   // INFaaS state penalties in ticks
     uint32_t qdepth;               // queue-cache entries behind each head of line (LDS)
+    uint32_t nw;                   // waves per replica: 8 for 128+ instances, else 1 or 4 (4 with a queue cache only)
     uint32_t blind;                // 1: tiers order nothing (tier-blind scheduling)
     uint32_t zero_lowest;          // 1: the lowest tier carries no headroom
     // adaptive headroom (epoch 0: static) and promotion (period 0: none)
@@ -140,7 +141,7 @@ struct Params {
 
 // LDS bytes of one wave (one replica) of the step kernel
 // (ext: the adaptive-headroom or promotion state is kept in LDS)
-size_t lds_bytes(uint32_t I, uint32_t S, uint32_t RB, uint32_t wsz, uint32_t policy, uint32_t qdepth, bool ext);
+size_t lds_bytes(uint32_t I, uint32_t S, uint32_t RB, uint32_t wsz, uint32_t policy, uint32_t qdepth, bool ext, uint32_t nw);
 
 // kernel launches (mts_kernels.hip, mts_arrivals.hip); return hipError_t as int
 int launch_init(const Params& p, hipStream_t stream);

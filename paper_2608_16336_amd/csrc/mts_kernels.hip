@@ -66,10 +66,10 @@ struct LdsLayout {
     uint32_t stats, occ, holk, fd, ht, ints, res, tcnt, mig, last, vic, wc, wov, inf, qt, qn, xn, ext, blk, rsel, total;
 };
 
-// Waves per replica: the kernels for 128 or more instances run a workgroup of
-// eight waves per replica (the per-instance phases are spread over the waves,
-// the serial ones stay on wave 0); the others one wave.
-__host__ __device__ constexpr int waves_for(uint32_t IM) { return IM >= 128 ? 8 : 1; }
+// Waves per replica (NW): eight in the kernels for 128 or more instances (the
+// per-instance phases are spread over the waves, the serial ones stay on wave
+// 0); one or, for overloaded clusters that leave the chip room, four in the
+// others.
 
 __host__ __device__ inline uint32_t al8(uint32_t x) { return (x + 7u) & ~7u; }
 
@@ -83,8 +83,9 @@ __host__ __device__ constexpr uint32_t imax_for(uint32_t I)
 }
 
 __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_t W, uint32_t RB, uint32_t wsz,
-                                                uint32_t policy, uint32_t qdepth, bool ext)
+                                                uint32_t policy, uint32_t qdepth, bool ext, uint32_t nw)
 {
+    const bool wide = IM >= 128;
     LdsLayout L;
     uint32_t o = 0;
     L.stats = o; o += kNstat * 8;
@@ -109,8 +110,8 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     o = (o + 15u) & ~15u;
     L.qt = o;    o += IM * qdepth * 16;
     L.qn = o;    o += qdepth ? IM * 8 : 0;
-    // multi-wave kernels: per instance the queue cache extension's head << 16 | count
-    L.xn = o;    o += waves_for(IM) > 1 ? IM * 4 : 0;
+    // kernels for 128+ instances: per instance the queue cache extension's head << 16 | count
+    L.xn = o;    o += wide ? IM * 4 : 0;
     // adaptive headroom / promotion: the ticks left to the next promotion
     // pass and headroom update, and per instance a lower bound on the
     // arrival ticks of its waiting requests (the rest of their state stays
@@ -120,12 +121,12 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     // multi-wave kernels: values the waves combine (the auto-scaling sum, an
     // abort flag, the admission work list's length and next entry)
     o = al8(o);
-    L.blk = o;   o += waves_for(IM) > 1 ? 32 : 0;
-    // multi-wave kernels: per wave 64 (key, slot | demand) pairs, the rescan's
+    L.blk = o;   o += nw > 1 ? 32 : 0;
+    // kernels for 128+ instances: per wave 64 (key, slot | demand) pairs, the rescan's
     // selected requests before they are ranked (the pairing's sorted blocks
     // of 64 (key, index) pairs use the same bytes later in the tick)
     o = (o + 15u) & ~15u;
-    L.rsel = o;  o += waves_for(IM) > 1 ? waves_for(IM) * 64 * 8 : 0;
+    L.rsel = o;  o += wide ? nw * 64 * 8 : 0;
     L.total = (o + 15u) & ~15u;
     return L;
 }
@@ -214,10 +215,10 @@ __device__ __forceinline__ unsigned long long* ext_hsnap(const Params& P)
     return reinterpret_cast<unsigned long long*>(reinterpret_cast<const unsigned long long*>(P.ext + kXHsnap)[0]);
 }
 
-template <int IM, bool INF, bool EXT, bool QC>
+template <int IM, bool INF, bool EXT, bool QC, int NW>
 __device__ inline Ctx carve(char* base, const Params& P)
 {
-    const LdsLayout Y = lds_layout(IM, P.I, P.W, P.RB, P.wsz, P.policy, P.qdepth, EXT);
+    const LdsLayout Y = lds_layout(IM, P.I, P.W, P.RB, P.wsz, P.policy, P.qdepth, EXT, NW);
     Ctx C;
     C.stats = reinterpret_cast<unsigned long long*>(base + Y.stats);
     C.occ = reinterpret_cast<unsigned long long*>(base + Y.occ);
@@ -259,7 +260,7 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.qt = reinterpret_cast<uint4*>(base + Y.qt);
     C.qn = reinterpret_cast<int*>(base + Y.qn);
     C.qh = C.qn + IM;
-    C.xn = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.xn) : nullptr;
+    C.xn = IM >= 128 ? reinterpret_cast<int*>(base + Y.xn) : nullptr;
     C.qx = nullptr;  // per replica, set with the slot records
     C.xd = int(P.qxd);
     if (INF) {
@@ -271,13 +272,13 @@ __device__ inline Ctx carve(char* base, const Params& P)
         C.fsum = nullptr; C.svc = nullptr; C.fcnt = nullptr; C.pen = nullptr;
     }
     C.ext = EXT ? reinterpret_cast<unsigned char*>(base + Y.ext) : nullptr;
-    C.bsum = waves_for(IM) > 1 ? reinterpret_cast<long long*>(base + Y.blk) : nullptr;
-    C.bflag = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.blk + 8) : nullptr;
-    C.wln = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.blk + 12) : nullptr;
-    C.wlnext = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.blk + 16) : nullptr;
-    C.e2go = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.blk + 20) : nullptr;
-    C.e2n2 = waves_for(IM) > 1 ? reinterpret_cast<int*>(base + Y.blk + 24) : nullptr;
-    C.rsel = waves_for(IM) > 1 ? reinterpret_cast<uint2*>(base + Y.rsel) + 64 * (threadIdx.x >> 6) : nullptr;
+    C.bsum = NW > 1 ? reinterpret_cast<long long*>(base + Y.blk) : nullptr;
+    C.bflag = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 8) : nullptr;
+    C.wln = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 12) : nullptr;
+    C.wlnext = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 16) : nullptr;
+    C.e2go = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 20) : nullptr;
+    C.e2n2 = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 24) : nullptr;
+    C.rsel = IM >= 128 ? reinterpret_cast<uint2*>(base + Y.rsel) + 64 * (threadIdx.x >> 6) : nullptr;
     C.I = P.I; C.S = P.S; C.W = P.W; C.RB = P.RB;
     C.shift = P.blk_shift;
     C.bmask = (1u << P.blk_shift) - 1u;
@@ -1707,10 +1708,11 @@ __device__ inline void admit_all(const Ctx& C, int i, uint32_t t, int lane)
 // be old enough and the instance is not read.  lb = 0 means unknown (a
 // launch starts so, as does an instance holding a request that arrived
 // after t, possible only after the clock was moved back).
-__device__ inline void promote_waiting(const Ctx& C, const Params& P, uint32_t t, int lane)
+template <int NW>
+__device__ inline void promote_waiting(const Ctx& C, const Params& P, uint32_t t, int lane, int wid)
 {
     const uint32_t qmin = P.ext[kXPromoMin];
-    for (uint32_t i = 0; i < C.I; ++i) {
+    for (uint32_t i = uint32_t(wid); i < C.I; i += NW) {
         if (C.nwait[i] == 0) continue;
         const uint32_t lb = wlb(C)[i];
         if (lb != 0 && t - lb < qmin) continue;
@@ -1720,21 +1722,29 @@ __device__ inline void promote_waiting(const Ctx& C, const Params& P, uint32_t t
         bool any = false, late = false, head = false;
         uint32_t lo = 0xFFFFFFFFu;
         unsigned long long kmin = kNone;
-        for (int c = 0; c < nch; ++c) {
-            const int s = c * 64 + lane;
-            const uint4 rec = C.slot[b + s];
-            if (wst(rec.x) != 1u) continue;
-            const uint32_t m = rec.y, tier = (m >> 2) & 15u, ta = rec.w;
-            lo = ta < lo ? ta : lo;
-            late = late || ta > t;
-            if (tier == 0) continue;
-            const uint32_t q = P.ext[kXAge + tier];
-            if (q != 0 && t - ta >= q) {
-                s_meta(C, b + s) = m - 4u;  // tier field at bits 2..5
-                any = true;
-                head = head || s == h;
-                const unsigned long long k = (rank_of(C, tier - 1u) << 32) | rec.z;
-                kmin = k < kmin ? k : kmin;
+        // four chunks of 64 slots per memory round trip (one at a time took the
+        // passes of the overloaded gauss10 workload 10.7K cycles a tick)
+        for (int c0 = 0; c0 < nch; c0 += 4) {
+            uint4 rr[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) rr[g] = c0 + g < nch ? C.slot[b + (c0 + g) * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const uint4 rec = rr[g];
+                if (wst(rec.x) != 1u) continue;
+                const int s = (c0 + g) * 64 + lane;
+                const uint32_t m = rec.y, tier = (m >> 2) & 15u, ta = rec.w;
+                lo = ta < lo ? ta : lo;
+                late = late || ta > t;
+                if (tier == 0) continue;
+                const uint32_t q = P.ext[kXAge + tier];
+                if (q != 0 && t - ta >= q) {
+                    s_meta(C, b + s) = m - 4u;  // tier field at bits 2..5
+                    any = true;
+                    head = head || s == h;
+                    const unsigned long long k = (rank_of(C, tier - 1u) << 32) | rec.z;
+                    kmin = k < kmin ? k : kmin;
+                }
             }
         }
         lo = wmin32(lo);
@@ -1802,16 +1812,19 @@ __device__ __forceinline__ void block_sync()
 }
 
 // Image of a replica's LDS between launches: a header {tick it stands at,
-// kImgMagic, queue-cache depth | wheel capacity << 8, LDS bytes} and the bytes.
+// kImgMagic, queue-cache depth | waves << 8 | wheel capacity << 16, LDS bytes}
+// and the bytes.
 // Both are uniform over the block.
 constexpr uint32_t kImgMagic = 0x4C445331u;
+template <uint32_t NT>
+__device__ __forceinline__ uint32_t img_layout(const Params& P) { return P.qdepth | (NT / 64u) << 8 | P.wcap << 16; }
 template <uint32_t NT>
 __device__ inline bool image_read(const Params& P, uint32_t r, uint32_t t, char* lds, uint32_t tid)
 {
     if (!P.img) return false;
     const uint4* m = P.img + size_t(r) * P.img_n;
     const uint4 h = *uniform_ptr(m);
-    if (h.x != t || h.y != kImgMagic || h.z != (P.qdepth | (P.wcap << 8)) || h.w != P.img_lds) return false;
+    if (h.x != t || h.y != kImgMagic || h.z != (img_layout<NT>(P)) || h.w != P.img_lds) return false;
     uint4* l = reinterpret_cast<uint4*>(lds);
     const uint32_t n = P.img_lds / 16u;
     for (uint32_t j = tid; j < n; j += 4 * NT) {
@@ -1834,7 +1847,7 @@ __device__ inline void image_write(const Params& P, uint32_t r, uint32_t t, cons
     const uint4* l = reinterpret_cast<const uint4*>(lds);
     const uint32_t n = P.img_lds / 16u;
     for (uint32_t j = tid; j < n; j += NT) m[1 + j] = l[j];
-    if (tid == 0) m[0] = make_uint4(t, kImgMagic, P.qdepth | (P.wcap << 8), P.img_lds);
+    if (tid == 0) m[0] = make_uint4(t, kImgMagic, img_layout<NT>(P), P.img_lds);
 }
 
 // v, with the load that produces it complete
@@ -1845,17 +1858,17 @@ __device__ __forceinline__ unsigned long long landed(unsigned long long v)
     return (static_cast<unsigned long long>(hi) << 32) | lo;
 }
 
-template <int IM, bool INF, bool EXT, bool QC>
-__global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(Params P, unsigned long long t0, uint32_t nt)
+template <int IM, bool INF, bool EXT, bool QC, int NW>
+__global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, unsigned long long t0, uint32_t nt)
 {
     // IPL: instances per lane when one wave covers every instance (the serial
     // phases, run by wave 0); OPL: instances per lane of the instances a wave
     // owns in the per-instance phases, instance (64 j + lane) NW + wid
-    constexpr int NW = waves_for(IM);
+    constexpr bool WIDE = IM >= 128;
     constexpr int IPL = (IM + 63) / 64;
     constexpr int OPL = (IM + 64 * NW - 1) / (64 * NW);
     extern __shared__ __align__(16) char lds_raw[];
-    Ctx C = carve<IM, INF, EXT, QC>(lds_raw, P);
+    Ctx C = carve<IM, INF, EXT, QC, NW>(lds_raw, P);
     const int lane = lane_id();
     const int wid = NW > 1 ? int(threadIdx.x >> 6) : 0;
     const uint32_t tid = threadIdx.x;
@@ -2056,10 +2069,8 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             if (EXT) {
                 const int pl = xleft(C)[0], al = xleft(C)[1];
                 const int per = int(P.ext[kXPromoPeriod]), ep = int(P.ext[kXAdaptEpoch]);
-                if (wid == 0) {
-                    if (per && pl == 0) promote_waiting(C, P, t, lane);
-                    if (ep && al == 0) adapt_headroom(C, P, r, lane);
-                }
+                if (per && pl == 0) promote_waiting<NW>(C, P, t, lane, wid);
+                if (wid == 0 && ep && al == 0) adapt_headroom(C, P, r, lane);
                 block_sync<NW>();
                 if (ep && al == 0) {
                     if (wid == 0) headroom_table(C, ext_hqr(P) + size_t(r) * kTiers, lane);
@@ -2196,7 +2207,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
             // instance to the end: a few long queues no longer load one wave.
             // Admissions on different instances touch only their own state and
             // shared counters, so the order does not matter.
-            if (NW > 1) {
+            if (WIDE) {
 #pragma unroll
                 for (int j = 0; j < OPL; ++j) {
                     const uint32_t i = (uint32_t(lane) + 64u * j) * NW + uint32_t(wid);
@@ -2216,8 +2227,9 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 // may have admitted on
                 block_sync<NW>();
             } else {
-                // lane i holds instance i; its summary is read once per round
-                const int i = lane;
+                // lane l of wave w holds instance l NW + w; its summary is read once per
+                // round
+                const int i = lane * NW + wid;
                 const bool own = uint32_t(i) < I;
                 for (;;) {
                     int h = kNoHol, hd = 0, fr = 0, nw = 0, fs = 0, qn = 0;
@@ -2232,12 +2244,18 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     bool any = false;
                     const unsigned long long um = ballot(h == kHolUnknown);
                     if (um) {
-                        for (unsigned long long m = um; m; m &= m - 1) any = rescan_admit<4, 2>(C, ffs64(m), t, lane) || any;
+                        for (unsigned long long m = um; m; m &= m - 1)
+                            any = rescan_admit<4, 2>(C, ffs64(m) * NW + wid, t, lane) || any;
                         look();
                     }
                     const bool fits = h >= 0 && hd <= fr;
                     // queues that hold the previous tick's arrivals only
-                    if (ballot(fits && fs)) admit_fresh_all(C, t, lane);
+                    const unsigned long long fm = ballot(fits && fs);
+                    if (NW == 1) {
+                        if (fm) admit_fresh_all(C, t, lane);
+                    } else {
+                        for (unsigned long long m = fm; m; m &= m - 1) admit_fresh(C, ffs64(m) * NW + wid, t, lane);
+                    }
                     const bool rest = fits && !fs;
                     if (ballot(rest)) {
                         const bool batch = rest && nw >= 2 && nw <= 64 && !(C.td && qn > 0);
@@ -2252,10 +2270,11 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                             any = any || C.hols[i] == kHolUnknown;
                         }
                         wave_sync();
-                        for (unsigned long long m = ballot(batch); m; m &= m - 1) admit_batch<4>(C, ffs64(m), t, lane);
+                        for (unsigned long long m = ballot(batch); m; m &= m - 1) admit_batch<4>(C, ffs64(m) * NW + wid, t, lane);
                     }
                     if (!ballot(any)) break;
                 }
+                if (NW > 1) wave_sync();
             }
             // auto-scaling signal (Section 3.6): the cluster average of the
             // normal-priority freeness F_normal = (free - head-of-line demand) /
@@ -2858,7 +2877,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                         avm[j] = ballot(i < I && !(migs && (C.flags[i] & kFlagBusy)));
                         n2 += __popcll(avm[j]);
                     }
-                    if (NW > 1) {
+                    if (WIDE) {
                         // the keys for the workgroup's count, in the freeness array
                         // (set again in phase C before its next use): F as an
                         // order-preserving 64-bit key; an instance in a migration
@@ -2884,11 +2903,11 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                     }
                 }
             }
-            if (NW > 1 && lane == 0) { *C.e2go = e2 ? 1 : 0; *C.e2n2 = n2; }
+            if (WIDE && lane == 0) { *C.e2go = e2 ? 1 : 0; *C.e2n2 = n2; }
             wave_sync();
             }  // wave 0
-            block_sync<NW>();
-            if (NW > 1 && *C.e2go) {
+            if (WIDE) block_sync<NW>();
+            if (WIDE && *C.e2go) {
                 // L in the eight-wave kernels: each instance's rank in (F, index)
                 // order, in two steps: waves 0..3 each sort a block of 64
                 // instances by counting (into the rescans' selection buffers,
@@ -2941,7 +2960,7 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
                 block_sync<NW>();
             }
             if (wid == 0) {
-                if (NW > 1) { e2 = *C.e2go != 0; n2 = *C.e2n2; }
+                if (WIDE) { e2 = *C.e2go != 0; n2 = *C.e2n2; }
                 if (e2) {
                     const int npairs = min(int(P.mig_max_pairs), n2 / 2);
                     // Pairs (L[k], L[n2 - 1 - k]) use disjoint instances and one
@@ -3085,9 +3104,10 @@ __global__ __launch_bounds__(64 * waves_for(IM), IM <= 64 ? 4 : 2) void k_step(P
 
 }  // namespace
 
-// The instantiations of the step kernel are compiled in eight translation
-// units (this file with MTS_STEP_PART = 0..7): bit 0 the INFaaS policy, bit 1
-// the Section 6.5 extensions, bit 2 the kernels for 128 or more instances.
+// The instantiations of the step kernel are compiled in twelve translation
+// units (this file with MTS_STEP_PART = 0..11): bit 0 the INFaaS policy, bit 1
+// the Section 6.5 extensions; 0..3 the one-wave kernels, 4..7 those for 128 or
+// more instances, 8..11 the four-wave kernels (always with a queue cache).
 // Each gives the kernel for IM instances with (qc) or without a queue cache.
 #ifdef MTS_STEP_PART
 #define MTS_STEP_FN2(p) step_part_##p
@@ -3098,16 +3118,21 @@ const void* step_of(uint32_t IM)
 {
     constexpr bool INF = (MTS_STEP_PART & 1) != 0, EXT = (MTS_STEP_PART & 2) != 0;
 #if MTS_STEP_PART & 4
-    return IM == 128 ? reinterpret_cast<const void*>(&k_step<128, INF, EXT, QC>)
-                     : reinterpret_cast<const void*>(&k_step<256, INF, EXT, QC>);
+    return IM == 128 ? reinterpret_cast<const void*>(&k_step<128, INF, EXT, QC, 8>)
+                     : reinterpret_cast<const void*>(&k_step<256, INF, EXT, QC, 8>);
 #else
-    return IM == 16   ? reinterpret_cast<const void*>(&k_step<16, INF, EXT, QC>)
-           : IM == 32 ? reinterpret_cast<const void*>(&k_step<32, INF, EXT, QC>)
-                      : reinterpret_cast<const void*>(&k_step<64, INF, EXT, QC>);
+    constexpr int NW = MTS_STEP_PART & 8 ? 4 : 1;
+    return IM == 16   ? reinterpret_cast<const void*>(&k_step<16, INF, EXT, QC, NW>)
+           : IM == 32 ? reinterpret_cast<const void*>(&k_step<32, INF, EXT, QC, NW>)
+                      : reinterpret_cast<const void*>(&k_step<64, INF, EXT, QC, NW>);
 #endif
 }
 }  // namespace
+#if MTS_STEP_PART & 8
+const void* MTS_STEP_FN(MTS_STEP_PART)(uint32_t IM, bool) { return step_of<true>(IM); }
+#else
 const void* MTS_STEP_FN(MTS_STEP_PART)(uint32_t IM, bool qc) { return qc ? step_of<true>(IM) : step_of<false>(IM); }
+#endif
 
 #else
 
@@ -3119,6 +3144,10 @@ const void* step_part_4(uint32_t, bool);
 const void* step_part_5(uint32_t, bool);
 const void* step_part_6(uint32_t, bool);
 const void* step_part_7(uint32_t, bool);
+const void* step_part_8(uint32_t, bool);
+const void* step_part_9(uint32_t, bool);
+const void* step_part_10(uint32_t, bool);
+const void* step_part_11(uint32_t, bool);
 
 namespace {
 
@@ -3231,9 +3260,9 @@ __global__ __launch_bounds__(256) void k_digest(Params P, uint32_t r0, uint32_t 
 
 }  // namespace
 
-size_t lds_bytes(uint32_t I, uint32_t S, uint32_t RB, uint32_t wsz, uint32_t policy, uint32_t qdepth, bool ext)
+size_t lds_bytes(uint32_t I, uint32_t S, uint32_t RB, uint32_t wsz, uint32_t policy, uint32_t qdepth, bool ext, uint32_t nw)
 {
-    return lds_layout(imax_for(I), I, S / 64, RB, wsz, policy, qdepth, ext).total;
+    return lds_layout(imax_for(I), I, S / 64, RB, wsz, policy, qdepth, ext, nw).total;
 }
 
 int launch_init(const Params& p, hipStream_t stream)
@@ -3252,16 +3281,17 @@ bool ext_on(const Params& p) { return p.adapt_epoch != 0 || p.promo_period != 0;
 const void* step_fn(const Params& p)
 {
     using Part = const void* (*)(uint32_t, bool);
-    static constexpr Part parts[8] = {step_part_0, step_part_1, step_part_2, step_part_3,
-                                      step_part_4, step_part_5, step_part_6, step_part_7};
+    static constexpr Part parts[12] = {step_part_0, step_part_1, step_part_2,  step_part_3,
+                                       step_part_4, step_part_5, step_part_6,  step_part_7,
+                                       step_part_8, step_part_9, step_part_10, step_part_11};
     const uint32_t IM = imax_for(p.I);
-    const int k = (p.policy == MTS_POLICY_INFAAS ? 1 : 0) | (ext_on(p) ? 2 : 0) | (IM >= 128 ? 4 : 0);
+    const int k = (p.policy == MTS_POLICY_INFAAS ? 1 : 0) | (ext_on(p) ? 2 : 0) | (IM >= 128 ? 4 : p.nw > 1 ? 8 : 0);
     return parts[k](IM, p.qdepth != 0);
 }
 
 size_t step_lds(const Params& p)
 {
-    const size_t lds = lds_bytes(p.I, p.S, p.RB, p.wsz, p.policy, p.qdepth, ext_on(p));
+    const size_t lds = lds_bytes(p.I, p.S, p.RB, p.wsz, p.policy, p.qdepth, ext_on(p), p.nw);
     if (lds > 64 * 1024) {
         // raise the dynamic LDS limit; a real failure shows up at the launch
         (void)hipFuncSetAttribute(step_fn(p), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
@@ -3272,7 +3302,7 @@ size_t step_lds(const Params& p)
 
 }  // namespace
 
-int step_threads(const Params& p) { return 64 * waves_for(imax_for(p.I)); }
+int step_threads(const Params& p) { return int(64 * p.nw); }
 
 int step_blocks_per_cu(const Params& p)
 {

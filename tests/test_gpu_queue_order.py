@@ -10,7 +10,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
-from workloads import preset  # noqa: E402
+from workloads import preset, with_extensions  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +18,7 @@ if not torch.cuda.is_available():  # collected on CPU-only hosts, never run ther
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from paper_2608_16336_amd import Scheduler  # noqa: E402
+from paper_2608_16336_amd.mts import MtsError  # noqa: E402
 
 
 def _cfg(I, S, M, arrival, K=10, blind=0, interval=1, out=40.0, infaas=False):
@@ -82,3 +83,40 @@ def test_depth_is_kept_where_every_replica_stays_resident():
         grp["n_replicas"] = 32
     g = Scheduler(cfg)
     assert g.queue_cache > 0
+
+
+@pytest.mark.parametrize("cfg", [
+    _cfg(16, 128, 300, dict(kind="poisson", mean=9.0)),
+    _cfg(33, 192, 300, dict(kind="gamma_poisson", mean=20.0, cv=2.0), K=4, interval=3),
+    _cfg(64, 64, 160, dict(kind="poisson", mean=24.0), blind=1),
+    _cfg(17, 64, 200, dict(kind="poisson", mean=9.0), infaas=True),
+    with_extensions(_cfg(20, 128, 200, dict(kind="poisson", mean=9.0))),
+], ids=["I16", "I33", "I64_blind", "I17_infaas", "I20_ext"])
+def test_four_waves_per_replica_equal_one(cfg):
+    # overloaded clusters run four waves per replica; 64 threads ask for one
+    o = oracle.Oracle(cfg)
+    o.step(200)
+    want = o.export()
+    assert want["stats"].reshape(2, -1)[:, :80].reshape(2, 10, 8)[:, :, 5].sum() > 0  # preemptions
+    for threads in (0, 64, 256):
+        g = Scheduler(cfg)
+        g.set_launch(threads, 0)
+        assert g.launch()[0] == (64 if threads == 64 else 256)
+        g.step(150)
+        g.set_launch(0, 1)  # back to the automatic size, both replicas in one block
+        g.step(50)
+        got = g.export()
+        for k in want:
+            assert np.array_equal(got[k], want[k]), "%d threads, field %s" % (threads, k)
+    g.queue_cache = 0  # the four-wave kernels need a queue cache
+    assert g.launch()[0] == 64
+    with pytest.raises(MtsError):
+        g.set_launch(128, 0)
+
+
+def test_one_wave_where_the_load_leaves_no_queue():
+    assert Scheduler(preset("enterprise")).launch()[0] == 64
+    g = Scheduler(preset("tiny"))
+    assert g.launch()[0] == 64
+    with pytest.raises(MtsError):
+        g.set_launch(256, 0)
