@@ -56,6 +56,9 @@ constexpr int kInts = 18;
 constexpr int kLast = 64;
 // requests preempted in the current tick, listed for the prefetched finish visit
 constexpr int kVic = 16;
+// kernels for 128+ instances: up to this many pairs are picked one by one
+// (about 450 cycles each; the whole order takes 11K)
+constexpr int kPickPairs = 16;
 // Section 6.5 extensions: words of the device table (u32; the addresses of
 // the per-replica headroom and snapshot arrays as u64 at the end)
 enum { kXSlo = 0, kXAge = 10, kXPromoMin = 20, kXPromoPeriod, kXAdaptEpoch, kXAdaptUp, kXAdaptDown, kXAdaptMax,
@@ -179,7 +182,8 @@ struct Ctx {
     int* wln;
     int* wlnext;
     int* e2go;                 // pairing runs this tick (set by wave 0)
-    int* e2n2;                 // instances that can pair
+    int* e2n2;                 // staged copies to start
+    int* kcnt;                 // entries that stay in the visited finish bucket
     uint2* rsel;               // this wave's 64 entries of the rescan selection buffer
     // HBM: timing wheel of this replica, slot arrays, latency histograms
     uint32_t* wheel;           // [wsz][wcap] instance << 16 | slot
@@ -278,6 +282,7 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.wlnext = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 16) : nullptr;
     C.e2go = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 20) : nullptr;
     C.e2n2 = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 24) : nullptr;
+    C.kcnt = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 28) : nullptr;
     C.rsel = IM >= 128 ? reinterpret_cast<uint2*>(base + Y.rsel) + 64 * (threadIdx.x >> 6) : nullptr;
     C.I = P.I; C.S = P.S; C.W = P.W; C.RB = P.RB;
     C.shift = P.blk_shift;
@@ -1040,10 +1045,12 @@ __device__ inline void finish_scan(const Ctx& C, int i, uint32_t t, int lane, bo
 // One batch of up to 64 entries of bucket t mod wsz (lanes with inb set),
 // each with its slot's word, meta and arrival tick: entries with fin = t
 // finish, those with a later fin stay in the bucket (compacted in place from
-// position kept on; returns the new kept count), tombstones and entries whose
+// position kept on, or from the one that counter gives when several waves
+// visit the bucket; returns the new kept count), tombstones and entries whose
 // slot changed since are dropped.
 __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint32_t* ent, uint32_t kept, bool inb,
-                                        uint32_t e, uint32_t v, uint32_t m, uint32_t ta, bool& abort_any)
+                                        uint32_t e, uint32_t v, uint32_t m, uint32_t ta, bool& abort_any,
+                                        int* counter = nullptr)
 {
     const uint32_t bk = t & C.wmask;
     const int i = int(e >> 16), s = int(e & 0xFFFFu);
@@ -1055,6 +1062,11 @@ __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint
     const bool f = valid && wst(v) == 2u && fin == t;
     const bool k = valid && wst(v) == 2u && fin != t && (fin & C.wmask) == bk;
     const unsigned long long km = ballot(k);
+    if (counter && km) {
+        int b = 0;
+        if (lane == 0) b = atomicAdd(counter, __popcll(km));
+        kept = uint32_t(rl(b, 0));
+    }
     if (k) {
         // a later finish that shares the bucket: its entry moves to its new place
         // (m may predate a migration's start: the flag comes from the record)
@@ -1090,6 +1102,37 @@ __device__ inline uint32_t finish_batch(const Ctx& C, uint32_t t, int lane, uint
     abort_any = abort_any || ballot(ab) != 0;
     wave_sync();
     return kept;
+}
+
+// A bucket of more than one batch, by all NW waves: batch b of 64 entries is
+// wave b mod NW's.  Every entry and its slot is read before any entry moves
+// (two memory round trips for the whole bucket where one wave after the other
+// batch took two each: 8.6K cycles of the wide workload's tick).  *kcnt is 0
+// before; the caller sets the bucket's count to it after a barrier.
+template <int NW>
+__device__ inline void finish_wide(const Ctx& C, uint32_t t, int lane, int wid, uint32_t n, bool& abort_any)
+{
+    // kMaxSlots caps the entries of a bucket
+    constexpr int NB = int(kMaxSlots) / (64 * NW);
+    uint32_t* ent = C.wheel + size_t(t & C.wmask) * C.wcap;
+    uint32_t e[NB], v[NB], m[NB], ta[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const uint32_t k = uint32_t(b * NW + wid) * 64u + uint32_t(lane);
+        e[b] = k < n ? ent[k] : kTomb;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const uint32_t i = e[b] >> 16, s = e[b] & 0xFFFFu;
+        const uint4 rec = i < C.I && s < C.S ? C.slot[size_t(i) * C.S + s] : make_uint4(0u, 0u, 0u, 0u);
+        v[b] = rec.x; m[b] = rec.y; ta[b] = rec.w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (uint32_t(b * NW + wid) * 64u >= n) break;
+        finish_batch(C, t, lane, ent, 0, true, e[b], v[b], m[b], ta[b], abort_any, C.kcnt);
+    }
 }
 
 __device__ __forceinline__ void wheel_set_count(const Ctx& C, uint32_t b, uint32_t n, int lane)
@@ -2119,16 +2162,37 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                         abort_any = preempt<(IM >= 128 ? 16 : 4), 2, QC && IM < 128>(
                                         C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || abort_any;
             }
+            // a bucket of more than 64 entries is visited by every wave (the count
+            // and the overflow flag are read here, where no wave writes them:
+            // all waves take the same branch)
+            bool by_all = false;
+            uint32_t nb_all = 0;
+            if (WIDE) {
+                const uint32_t bk = t & C.wmask;
+                nb_all = (C.wc[bk >> 1] >> ((bk & 1u) * 16u)) & 0xFFFFu;
+                by_all = nb_all > 64u && !((C.wov[bk >> 5] >> (bk & 31u)) & 1u);
+            }
             if (NW > 1) {
                 if (abort_any && lane == 0) *C.bflag = 1;
                 if (tid == 0) {
                     *C.bsum = 0;  // the auto-scaling sum of this tick (phase C)
                     *C.wln = 0;   // the admission work list (phase B)
                     *C.wlnext = 0;
+                    *C.kcnt = 0;
                 }
                 block_sync<NW>();
                 if (wid == 0) {
                     preempting = *C.nvic != 0;
+                    abort_any = *C.bflag != 0;
+                }
+            }
+            if (by_all) {
+                bool ab = false;
+                finish_wide<NW>(C, t, lane, wid, nb_all, ab);
+                if (ab && lane == 0) *C.bflag = 1;
+                block_sync<NW>();
+                if (wid == 0) {
+                    wheel_set_count(C, t & C.wmask, uint32_t(*C.kcnt), lane);
                     abort_any = *C.bflag != 0;
                 }
             }
@@ -2152,7 +2216,9 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 const uint32_t bk = t & C.wmask;
                 const uint32_t nb = (C.wc[bk >> 1] >> ((bk & 1u) * 16u)) & 0xFFFFu;
                 const bool ov = (C.wov[bk >> 5] >> (bk & 31u)) & 1u;
-                if (pf_n != kNoPf && !pf_lost && !ov && nb == pf_n) {
+                if (by_all) {
+                    // (visited above)
+                } else if (pf_n != kNoPf && !pf_lost && !ov && nb == pf_n) {
                     uint32_t* ent = C.wheel + size_t(bk) * C.wcap;
                     const uint32_t kept = finish_batch(C, t, lane, ent, 0, uint32_t(lane) < pf_n, pf_e, pf_v, pf_m, pf_a,
                                                        abort_any);
@@ -2351,7 +2417,8 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             // the dispatch and the migrations (phases D and E): wave 0 (pairing:
             // whether it runs this tick and how many instances can pair)
             bool e2 = false;
-            int n2 = 0;
+            int nstaged = 0;
+            int n2 = 0, npairs = 0;
             if (wid == 0) {
             // ===================== D: tier-ordered dispatch =====================
             // an instance with an empty queue now holds, after this dispatch, only
@@ -2841,21 +2908,28 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             const bool mig_tick = mig_left == 0;
             mig_left = mig_tick ? P.mig_interval - 1u : mig_left - 1u;
             // pairing in three parts: which instances can pair and their keys
-            // (wave 0), their order (wave 0 by counting ranks; in the
-            // eight-wave kernels every thread counts), the pairs (wave 0)
+            // (wave 0), their order (wave 0 by counting ranks; in the kernels for
+            // 128+ instances only as many of the lowest and highest as can pair,
+            // or the whole order by every thread), the pairs (wave 0, the staged
+            // copies' candidates by all waves)
+            npairs = 0;
+            bool sort = false;
             if (!infaas && mig_tick) {
                 // F and the draining flag of each lane's instances
                 double ef[IPL];
+                bool ng[IPL];
                 bool neg = false;
 #pragma unroll
                 for (int j = 0; j < IPL; ++j) {
                     const uint32_t i = lane + 64 * j;
                     ef[j] = 0.0;
+                    ng[j] = false;
                     if (i < I) {
                         const double f = C.fd[i];
                         const int dr = C.drn[i];
                         ef[j] = dr ? -__builtin_inf() : f;
-                        neg = neg || dr || f < 0.0;
+                        ng[j] = dr || f < 0.0;
+                        neg = neg || ng[j];
                     }
                 }
                 if (ballot(neg)) {
@@ -2876,8 +2950,50 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                         const uint32_t i = lane + 64 * j;
                         avm[j] = ballot(i < I && !(migs && (C.flags[i] & kFlagBusy)));
                         n2 += __popcll(avm[j]);
+                        npairs += __popcll(avm[j] & ballot(ng[j]));
                     }
-                    if (WIDE) {
+                    // a source past those with F < 0 (or draining) ends the round
+                    npairs = min(min(int(P.mig_max_pairs), n2 / 2), npairs);
+                    if (WIDE && npairs <= kPickPairs) {
+                        // L's first and last npairs entries: the smallest and the
+                        // largest (F, index) left, one pair after the other
+                        double lo[IPL], hi[IPL];
+#pragma unroll
+                        for (int j = 0; j < IPL; ++j) {
+                            const bool av = (avm[j] >> lane) & 1ull;
+                            lo[j] = av ? -ef[j] : -__builtin_inf();
+                            hi[j] = av ? ef[j] : -__builtin_inf();
+                            // a draining instance comes first: -ef is plus infinity
+                        }
+                        for (int k = 0; k < npairs; ++k) {
+                            double a = lo[0], b = hi[0];
+#pragma unroll
+                            for (int j = 1; j < IPL; ++j) { a = fmax(a, lo[j]); b = fmax(b, hi[j]); }
+                            a = wave_max_f64<64>(a);
+                            b = wave_max_f64<64>(b);
+                            // only draining instances are left as destinations: the round ends
+                            if (b == -__builtin_inf()) { npairs = k; break; }
+                            int is = 0, id = 0;
+#pragma unroll
+                            for (int j = IPL - 1; j >= 0; --j) {
+                                const unsigned long long m = ballot(lo[j] == a);
+                                if (m) is = 64 * j + ffs64(m);
+                            }
+#pragma unroll
+                            for (int j = 0; j < IPL; ++j) {
+                                const unsigned long long m = ballot(hi[j] == b);
+                                if (m) id = 64 * j + 63 - __clzll(static_cast<long long>(m));
+                            }
+#pragma unroll
+                            for (int j = 0; j < IPL; ++j) {
+                                const int i = lane + 64 * j;
+                                lo[j] = i == is ? -__builtin_inf() : lo[j];
+                                hi[j] = i == id ? -__builtin_inf() : hi[j];
+                            }
+                            if (lane == 0) { C.order[k] = is; C.order[n2 - 1 - k] = id; }
+                        }
+                    } else if (WIDE) {
+                        sort = true;
                         // the keys for the workgroup's count, in the freeness array
                         // (set again in phase C before its next use): F as an
                         // order-preserving 64-bit key; an instance in a migration
@@ -2903,7 +3019,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                     }
                 }
             }
-            if (WIDE && lane == 0) { *C.e2go = e2 ? 1 : 0; *C.e2n2 = n2; }
+            if (WIDE && lane == 0) *C.e2go = sort ? 1 : 0;
             wave_sync();
             }  // wave 0
             if (WIDE) block_sync<NW>();
@@ -2960,14 +3076,13 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 block_sync<NW>();
             }
             if (wid == 0) {
-                if (WIDE) { e2 = *C.e2go != 0; n2 = *C.e2n2; }
+                int nst = 0;  // staged copies to start
                 if (e2) {
-                    const int npairs = min(int(P.mig_max_pairs), n2 / 2);
                     // Pairs (L[k], L[n2 - 1 - k]) use disjoint instances and one
                     // snapshot of F, so the stopping pair is found for all pairs at
                     // once (lane k tests pair k), the queued moves of the pairs
-                    // before it run in parallel, and only the staged copies, which
-                    // scan a source's slots with the whole wave, go one at a time.
+                    // before it run in parallel, and so do the staged copies once
+                    // every wave has scanned its part of the sources' slots.
                     for (int k0 = 0; k0 < npairs; k0 += 64) {
                         const int k = k0 + lane;
                         const bool in = k < npairs;
@@ -3026,58 +3141,78 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                                 qx_insert(C, rl(dst, l), make_uint4(rlu(dq.x, l), rlu(dq.y, l), rlu(dq.z, l), rlu(dq.w, l)), lane);
                             }
                         }
-                        // staged copies: running candidate of largest tier, then fewest
-                        // blocks, then newest
-                        for (unsigned long long pm = ballot(act && h < 0); pm; pm &= pm - 1) {
-                            const int l = ffs64(pm);
-                            const int psrc = rl(src, l), pdst = rl(dst, l), pds = rl(ds, l);
-                            const size_t sbase = size_t(psrc) * S;
-                            const int nch = live_chunks(C, psrc, lane);
-                            unsigned long long bk = 0;
-                            int bs = 0;
-                            // GC chunks of 64 slots per memory round trip
-                            constexpr int GC = IM >= 128 ? 16 : 4;
-                            for (int c0 = 0; c0 < nch; c0 += GC) {
-                                uint32_t v[GC], m[GC], q[GC];
-#pragma unroll
-                                for (int g = 0; g < GC; ++g) {
-                                    const bool in = c0 + g < nch;
-                                    const size_t sb = sbase + (c0 + g) * 64 + lane;
-                                    const uint4 rr = in ? C.slot[sb] : make_uint4(0u, 0u, 0u, 0u);
-                                    v[g] = rr.x; m[g] = rr.y; q[g] = rr.z;
-                                }
-#pragma unroll
-                                for (int g = 0; g < GC; ++g) {
-                                    if (wst(v[g]) == 2u && !(m[g] & kMigrating)) {
-                                        const uint32_t fin = fin_of(v[g], t);
-                                        const unsigned long long kk =
-                                            ((rank_of(C, (m[g] >> 2) & 15u) + 1ull) << 48) |
-                                            (static_cast<unsigned long long>(65535 - blocks_of(wlo(v[g]) - (fin - t), C.shift)) << 32) |
-                                            q[g];
-                                        if (kk > bk) { bk = kk; bs = (c0 + g) * 64 + lane; }
-                                    }
-                                }
-                            }
-                            const unsigned long long mx = wmax64(bk);
-                            if (mx == 0) continue;  // nothing to move (an empty draining source)
-                            const int cs = rl(bs, ffs64(ballot(bk == mx)));
-                            if (lane == 0) {
-                                const size_t dsb = size_t(pdst) * S + pds;
-                                s_set_wm(C, dsb, kInbW, kInbound);
-                                C.occ[pdst * W + (pds >> 6)] |= 1ull << (pds & 63);
-                                C.live[pdst] += 1;
-                                s_meta(C, sbase + cs) |= kMigrating;
-                                int* m = &C.mig[4 * psrc];
-                                m[0] = pdst; m[1] = cs; m[2] = pds; m[3] = 0;
-                                stat(C, kMigStarted, 1);
-                            }
-                            migs = true;
-                            wave_sync();
+                        // staged copies are listed: source, destination, its slot
+                        const unsigned long long pm = ballot(act && h < 0);
+                        if (act && h < 0) {
+                            const int x = nst + __popcll(pm & lanemask_lt());
+                            C.gtmp[x] = src | (dst << 8) | (ds << 16);
+                            reinterpret_cast<unsigned long long*>(C.fd)[x] = 0ull;
                         }
+                        nst += __popcll(pm);
                         if (sm) break;
                     }
                 }
+                if (NW > 1 && lane == 0) *C.e2n2 = nst;
+                migs = migs || nst > 0;
                 wave_sync();
+                nstaged = nst;
+            }
+            if (NW > 1) {
+                block_sync<NW>();
+                nstaged = *C.e2n2;
+            }
+            if (nstaged) {
+                // the running candidate of largest tier, then fewest blocks, then
+                // newest, its slot in the key's low bits (tier rank 4 bits, blocks
+                // 16, seq 32, slot 12); wave w reads chunks w, w + NW, ...  (One wave
+                // scanning 2048 slots took 8K cycles of the wide workload's tick.)
+                unsigned long long* best = reinterpret_cast<unsigned long long*>(C.fd);
+                for (int x = 0; x < nstaged; ++x) {
+                    const int psrc = C.gtmp[x] & 0xFF;
+                    const size_t sbase = size_t(psrc) * S;
+                    if (C.B[psrc] == 0) continue;  // nothing runs (a drained source)
+                    const int nch = live_chunks(C, psrc, lane);
+                    unsigned long long bk = 0;
+                    for (int c0 = wid; c0 < nch; c0 += 4 * NW) {
+                        uint32_t v[4], m[4], q[4];
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const int c = c0 + g * NW;
+                            const uint4 rr = c < nch ? C.slot[sbase + c * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
+                            v[g] = rr.x; m[g] = rr.y; q[g] = rr.z;
+                        }
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            if (wst(v[g]) == 2u && !(m[g] & kMigrating)) {
+                                const uint32_t fin = fin_of(v[g], t);
+                                const uint32_t nb = uint32_t(65535 - blocks_of(wlo(v[g]) - (fin - t), C.shift));
+                                const unsigned long long kk =
+                                    (((rank_of(C, (m[g] >> 2) & 15u) + 1ull) << 48 | static_cast<unsigned long long>(nb) << 32 | q[g]) << 12) |
+                                    uint32_t((c0 + g * NW) * 64 + lane);
+                                bk = kk > bk ? kk : bk;
+                            }
+                        }
+                    }
+                    const unsigned long long mx = wmax64(bk);
+                    if (lane == 0 && mx) atomicMax(&best[x], mx);
+                }
+                block_sync<NW>();
+                if (wid == 0) {
+                    for (int x = lane; x < nstaged; x += 64) {
+                        const unsigned long long mx = best[x];
+                        if (mx == 0) continue;  // nothing to move (an empty draining source)
+                        const int e = C.gtmp[x], psrc = e & 0xFF, pdst = (e >> 8) & 0xFF, pds = e >> 16;
+                        const int cs = int(mx & 0xFFFu);
+                        s_set_wm(C, size_t(pdst) * S + pds, kInbW, kInbound);
+                        C.occ[pdst * W + (pds >> 6)] |= 1ull << (pds & 63);
+                        C.live[pdst] += 1;
+                        atomicOr(&s_meta(C, size_t(psrc) * S + cs), kMigrating);
+                        int* m = &C.mig[4 * psrc];
+                        m[0] = pdst; m[1] = cs; m[2] = pds; m[3] = 0;
+                        stat(C, kMigStarted, 1);
+                    }
+                    wave_sync();
+                }
             }
             block_sync<NW>();
         }
