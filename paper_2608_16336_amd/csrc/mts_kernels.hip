@@ -126,8 +126,9 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     o = al8(o);
     L.blk = o;   o += nw > 1 ? 32 : 0;
     // kernels for 128+ instances: per wave 64 (key, slot | demand) pairs, the rescan's
-    // selected requests before they are ranked (the pairing's sorted blocks
-    // of 64 (key, index) pairs use the same bytes later in the tick)
+    // selected requests before they are ranked (the dispatch's deferred
+    // bursts and the pairing's sorted blocks of 64 (key, index) pairs use the
+    // same bytes later in the tick)
     o = (o + 15u) & ~15u;
     L.rsel = o;  o += wide ? nw * 64 * 8 : 0;
     L.total = (o + 15u) & ~15u;
@@ -1191,10 +1192,11 @@ __device__ inline void finish_tick(const Ctx& C, uint32_t t, int lane, bool& abo
 // extension (xc0 entries from xh0 on) as far as it fits the wave
 // (admit_cached): the new extension is then a suffix of the stored one (the
 // cache never holds more than qdepth), so only its head moves; when the whole
-// list is admitted, its first entry becomes the head of line.
+// list is admitted, its first entry becomes the head of line (go_on: the
+// caller admits from there on, the head of line stays unknown).
 __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, int w, unsigned long long key,
                                     uint32_t word, uint32_t meta, uint32_t ta, int slot, bool complete = true,
-                                    int xn0 = -1, int xh0 = 0, int xc0 = 0)
+                                    int xn0 = -1, int xh0 = 0, int xc0 = 0, bool go_on = false)
 {
     const size_t b = size_t(i) * C.S;
     const int dem = lane < w ? blocks_of(wlo(word), C.shift) : 0;
@@ -1247,7 +1249,7 @@ __device__ inline void admit_ranked(const Ctx& C, int i, uint32_t t, int lane, i
                 const int xc = xc0 - used;
                 const int xh = xh0 + used;
                 C.xn[i] = xc > 0 ? ((xh >= C.xd ? xh - C.xd : xh) << 16) | xc : 0;
-                if (na == w && xc > 0) hol_pop(C, i);
+                if (na == w && xc > 0 && !go_on) hol_pop(C, i);
             }
         }
     }
@@ -1580,8 +1582,35 @@ __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
         ta = e.z;
         slot = int(e.w & 0xFFFu);
     }
-    const bool complete = C.nwait[i] == w;
-    admit_ranked(C, i, t, lane, w, key, word, meta, ta, slot, complete, C.xn ? n : -1, xh, xc);
+    if (!C.xn) {
+        admit_ranked(C, i, t, lane, w, key, word, meta, ta, slot, C.nwait[i] == w);
+        return;
+    }
+    // While whole windows fit, the next 64 entries of the extension are on
+    // their way when a window is admitted: one memory round trip per window, and
+    // none for the head of line in between.
+    int nr = n, x0 = xh, xr = xc, wn = w;
+    for (;;) {
+        const int at = x0 + (wn - 1 - nr);  // of the entries behind the window
+        const int x1 = at >= C.xd ? at - C.xd : at, rest = xr - (wn - 1 - nr);
+        const int dem = lane < wn ? blocks_of(wlo(word), C.shift) : 0;
+        const bool all = rl(wscan(dem, lane), 63) <= C.freeb[i] && rest > 0;
+        uint4 nx = make_uint4(0u, 0u, 0u, 0u);
+        if (all && lane < rest) nx = *qx_at(C, i, x1, lane);
+        admit_ranked(C, i, t, lane, wn, key, word, meta, ta, slot, C.nwait[i] == wn, nr, x0, xr, all);
+        if (!all) return;
+        // (the window's first entry stands for the head of line)
+        wn = min(64, rest);
+        nr = 0;
+        x0 = x1 + 1 == C.xd ? 0 : x1 + 1;
+        xr = rest - 1;
+        const uint32_t tier = (nx.w >> 12) & 15u;
+        key = lane < wn ? qc_key(C, nx) : kNone;
+        word = nx.y;
+        meta = kWaiting | (tier << 2) | (((nx.w >> 16) & 1u) << 6);
+        ta = nx.z;
+        slot = int(nx.w & 0xFFFu);
+    }
 }
 
 // Admission of instance i whose waiting requests all arrived in the previous
@@ -1893,6 +1922,130 @@ __device__ inline void image_write(const Params& P, uint32_t r, uint32_t t, cons
     if (tid == 0) m[0] = make_uint4(t, kImgMagic, img_layout<NT>(P), P.img_lds);
 }
 
+// A staged copy's request: the running candidate of source i of largest tier,
+// then fewest blocks, then newest, its slot in the key's low bits (tier rank 4
+// bits, blocks 16, seq 32, slot 12); 0: nothing to move (an empty draining
+// source).  Wave wid of NW reads chunks wid, wid + NW, ... and returns its own
+// best.  (One wave scanning 2048 slots took 8K cycles of the wide workload's
+// tick; the one-wave kernels scan a source as its pair is made.)
+template <int NW>
+__device__ inline unsigned long long staged_best(const Ctx& C, int i, uint32_t t, int lane, int wid)
+{
+    if (C.B[i] == 0) return 0ull;
+    const size_t b = size_t(i) * C.S;
+    const int nch = live_chunks(C, i, lane);
+    unsigned long long bk = 0;
+    for (int c0 = wid; c0 < nch; c0 += 4 * NW) {
+        uint32_t v[4], m[4], q[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int c = c0 + g * NW;
+            const uint4 rr = c < nch ? C.slot[b + c * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
+            v[g] = rr.x; m[g] = rr.y; q[g] = rr.z;
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if (wst(v[g]) == 2u && !(m[g] & kMigrating)) {
+                const uint32_t fin = fin_of(v[g], t);
+                const uint32_t nb = uint32_t(65535 - blocks_of(wlo(v[g]) - (fin - t), C.shift));
+                const unsigned long long kk =
+                    (((rank_of(C, (m[g] >> 2) & 15u) + 1ull) << 48 | static_cast<unsigned long long>(nb) << 32 | q[g]) << 12) |
+                    uint32_t((c0 + g * NW) * 64 + lane);
+                bk = kk > bk ? kk : bk;
+            }
+        }
+    }
+    return wmax64(bk);
+}
+
+// The staged copy of the request of key mx (staged_best) from instance src to
+// slot ds of dst starts; one lane.
+__device__ inline void staged_start(const Ctx& C, int src, int dst, int ds, unsigned long long mx)
+{
+    const int cs = int(mx & 0xFFFu);
+    s_set_wm(C, size_t(dst) * C.S + ds, kInbW, kInbound);
+    C.occ[dst * C.W + (ds >> 6)] |= 1ull << (ds & 63);
+    C.live[dst] += 1;
+    atomicOr(&s_meta(C, size_t(src) * C.S + cs), kMigrating);
+    int* m = &C.mig[4 * src];
+    m[0] = dst; m[1] = cs; m[2] = ds; m[3] = 0;
+    stat(C, kMigStarted, 1);
+}
+
+// Bursts' rests kept for placement by all waves; more are placed as they come.
+constexpr int kMaxRuns = 8;
+// Places the m arrivals from index k1 on of this tick (records rec) that all go
+// to one instance, behind its head of line, on its m lowest empty slots (run
+// a = {instance, k1, m, sequence number of arrival 0}, b = {append to the kept
+// queue order, ring entries, extension's head << 16 | count before}).  Waves
+// take batches of 64 in turn.  One wave placed a burst at some 2K cycles a
+// batch of 64: 18 of the 26K cycles that the dispatch of the wide workload's
+// bursts took of a tick.  (This and the windows of admit_cached: 17.98 -> 15.70
+// ms per call there.)
+template <int NW>
+__device__ inline void place_run(const Ctx& C, const unsigned long long* rec, uint32_t t, uint4 a, uint4 b, int lane, int wid)
+{
+    const int i = int(a.x), m = int(a.z);
+    const unsigned long long* ra = rec + a.y;
+    const int nq = int(b.y), xc = int(b.z & 0xFFFFu), xh = int(b.z >> 16);
+    // empty slots up to and including each occupancy word, one word per lane
+    const unsigned long long wd = lane < int(C.W) ? C.occ[i * C.W + lane] : kNone;
+    const int fw = 64 - int(__popcll(wd));
+    const int pre = wscan(fw, lane);
+    const uint32_t wlo32 = uint32_t(~wd), whi32 = uint32_t(~wd >> 32);
+    for (int k0 = wid * 64; k0 < m; k0 += 64 * NW) {
+        const int k = k0 + lane;
+        const bool in = k < m;
+        const unsigned long long ar = in ? ra[k] : 0ull;
+        // the word that holds the k-th empty slot: the first whose count exceeds k
+        int w = 0;
+#pragma unroll
+        for (int step = 32; step; step >>= 1) {
+            const int v = __shfl(pre, w + step - 1);
+            w += v <= k ? step : 0;
+        }
+        const int before = __shfl(pre, w > 0 ? w - 1 : 0);
+        const uint32_t f0 = uint32_t(__shfl(int(wlo32), w & 63)), f1 = uint32_t(__shfl(int(whi32), w & 63));
+        const bool ok = in && w < int(C.W);
+        const int s = w * 64 + kth_set_bit(static_cast<unsigned long long>(f1) << 32 | f0, k - (w > 0 ? before : 0));
+        const int tier = int((ar >> 32) & 15u);
+        const uint32_t seq = a.w + unsigned(ar >> 36);
+        if (ok) {
+            const uint32_t word = kWaitW | (uint32_t((ar >> 16) & 0xFFFFu) << 16) | uint32_t(ar & 0xFFFFu);
+            C.slot[size_t(i) * C.S + s] = make_uint4(word, kWaiting | (uint32_t(tier) << 2), seq, t);
+            if (b.x) {
+                const uint4 en = make_uint4(seq, word, t, uint32_t(s) | (uint32_t(tier) << 12));
+                const int at = xc > 0 ? C.td : nq + k;  // place behind the head while the ring has room
+                const int e = xc > 0 ? xc + k : nq + k - C.td;
+                if (at < C.td) C.qt[qc_at(C, i, at)] = en;
+                else if (e < C.xd) *qx_at(C, i, xh, e) = en;
+            }
+            stat(C, tier * 8 + kArrived, 1);
+            stat(C, tier * 8 + kDispatched, 1);
+        } else if (in) {  // occupancy and live count disagree: flag, drop the arrival
+            stat(C, kInvariant, 1);
+            stat(C, tier * 8 + kArrived, 1);
+            stat(C, tier * 8 + kRejected, 1);
+        }
+    }
+    __syncthreads();
+    if (wid == 0) {
+        // the m lowest empty slots are taken
+        const int take = min(fw, m - (pre - fw));
+        if (lane < int(C.W) && take > 0) {
+            const int p = kth_set_bit(~wd, take - 1);
+            C.occ[i * C.W + lane] = wd | (p == 63 ? kNone : (2ull << p) - 1ull);
+        }
+        if (b.x && lane == 0) {
+            const int r = xc > 0 ? 0 : min(m, C.td - nq);  // entered the ring
+            C.qn[i] = nq + r;
+            const int ne = min(C.xd, xc + m - r);
+            C.xn[i] = ne > 0 ? (xh << 16) | ne : 0;
+        }
+    }
+    __syncthreads();
+}
+
 // v, with the load that produces it complete
 __device__ __forceinline__ unsigned long long landed(unsigned long long v)
 {
@@ -2186,14 +2339,16 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                     abort_any = *C.bflag != 0;
                 }
             }
-            if (by_all) {
-                bool ab = false;
-                finish_wide<NW>(C, t, lane, wid, nb_all, ab);
-                if (ab && lane == 0) *C.bflag = 1;
-                block_sync<NW>();
-                if (wid == 0) {
-                    wheel_set_count(C, t & C.wmask, uint32_t(*C.kcnt), lane);
-                    abort_any = *C.bflag != 0;
+            if constexpr (WIDE) {
+                if (by_all) {
+                    bool ab = false;
+                    finish_wide<NW>(C, t, lane, wid, nb_all, ab);
+                    if (ab && lane == 0) *C.bflag = 1;
+                    block_sync<NW>();
+                    if (wid == 0) {
+                        wheel_set_count(C, t & C.wmask, uint32_t(*C.kcnt), lane);
+                        abort_any = *C.bflag != 0;
+                    }
                 }
             }
             // a preempted request is waiting now: its prefetched entries (for this
@@ -2417,7 +2572,8 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             // the dispatch and the migrations (phases D and E): wave 0 (pairing:
             // whether it runs this tick and how many instances can pair)
             bool e2 = false;
-            int nstaged = 0;
+            int nruns = 0;  // bursts' rests to place
+            uint4* runs = reinterpret_cast<uint4*>(WIDE ? C.rsel - 64 * wid : nullptr);
             int n2 = 0, npairs = 0;
             if (wid == 0) {
             // ===================== D: tier-ordered dispatch =====================
@@ -2756,6 +2912,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                             C.hta[tgt] = t;
                         }
                     }
+                    bool beyond = true;  // this lane's arrival is larger than every cached entry
                     if (C.td && ballot(qc_any)) {
                         // the arrivals behind a head of line enter its queue cache
                         wave_sync();
@@ -2794,6 +2951,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                                 }
                             }
                         }
+                        beyond = behind;
                         // the others by a merge per instance
                         const unsigned long long inside = ballot(can && !run && !behind);
                         const bool enter = can && !run && (!behind || (xc == 0 && nq < C.td && (mode & 3) == kQcAll));
@@ -2811,10 +2969,53 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                     if (tgt >= 0) stat(C, tier * 8 + kDispatched, 1);
                     else if (tgt == -1 && lane < int(cn)) stat(C, tier * 8 + kRejected, 1);
                     wave_sync();
+                    // The rest of a burst that goes on to the same instance is placed by
+                    // all waves after this loop (place_run); here only the counts move
+                    // on.  Its arrivals follow the kept queue order (append) or lie
+                    // beyond it; else they take the batches above one by one.
+                    if (WIDE && cur >= 0 && k0 + 64 < n && nruns < kMaxRuns) {
+                        const int jc = cur >> 6, lc = cur & 63;
+                        const bool append = C.td && (C.order[cur] & kQcRun);
+                        if (!C.td || append || (ballot(beyond) >> 63)) {
+                            int lv = 0;
+#pragma unroll
+                            for (int j = 0; j < IPL; ++j)
+                                if (j == jc) lv = rl(live_r[j], lc);
+                            const int m = min(int(n - k0 - 64), int(S) - lv);
+                            if (lane == 0) {
+                                runs[2 * nruns] = make_uint4(uint32_t(cur), k0 + 64u, uint32_t(m), seq0);
+                                runs[2 * nruns + 1] = make_uint4(append ? 1u : 0u, append ? uint32_t(C.qn[cur]) : 0u, append ? uint32_t(C.xn[cur]) : 0u, 0u);
+                                C.live[cur] += m;
+                                C.nwait[cur] += m;
+                            }
+#pragma unroll
+                            for (int j = 0; j < IPL; ++j) {
+                                const bool me = j == jc && lane == lc;
+                                live_r[j] += me ? m : 0;
+                                nw_r[j] += me ? m : 0;
+                                key[j] = me && live_r[j] >= int(S) ? -__builtin_inf() : key[j];
+                            }
+                            wait_acc += lane == 0 ? unsigned(m) : 0u;
+                            nfall += drain_mode ? m : 0;
+                            cur = -1;
+                            ++nruns;
+                            k0 += uint32_t(m);
+                            if (k0 + 64 < n) a_bt = k0 + 64 + lane < n ? rec[k0 + 64 + lane] : 0ull;
+                            wave_sync();
+                        }
+                    }
                 }
                 if (lane == 0 && nfall) stat(C, kDrainFallback, unsigned(nfall));
             }
-
+            if (WIDE && lane == 0) *C.kcnt = nruns;
+            if (WIDE) wave_sync();
+            }  // wave 0
+            if constexpr (WIDE) {
+                block_sync<NW>();
+                nruns = *C.kcnt;
+                for (int x = 0; x < nruns; ++x) place_run<NW>(C, rec, t, runs[2 * x], runs[2 * x + 1], lane, wid);
+            }
+            if (wid == 0) {
             if (tl + 1 < nt) {
                 if (((tl + 1u) & 63u) == 0) {
                     const uint32_t* cn = uniform_ptr(cnts + tl + 1u);
@@ -3141,77 +3342,53 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                                 qx_insert(C, rl(dst, l), make_uint4(rlu(dq.x, l), rlu(dq.y, l), rlu(dq.z, l), rlu(dq.w, l)), lane);
                             }
                         }
-                        // staged copies are listed: source, destination, its slot
                         const unsigned long long pm = ballot(act && h < 0);
-                        if (act && h < 0) {
-                            const int x = nst + __popcll(pm & lanemask_lt());
-                            C.gtmp[x] = src | (dst << 8) | (ds << 16);
-                            reinterpret_cast<unsigned long long*>(C.fd)[x] = 0ull;
+                        if constexpr (NW > 1) {
+                            // staged copies are listed: source, destination, its slot
+                            if (act && h < 0) {
+                                const int x = nst + __popcll(pm & lanemask_lt());
+                                C.gtmp[x] = src | (dst << 8) | (ds << 16);
+                                reinterpret_cast<unsigned long long*>(C.fd)[x] = 0ull;
+                            }
+                            nst += __popcll(pm);
+                        } else {
+                            for (unsigned long long w = pm; w; w &= w - 1) {
+                                const int l = ffs64(w);
+                                const int psrc = rl(src, l);
+                                const unsigned long long mx = staged_best<1>(C, psrc, t, lane, 0);
+                                if (mx == 0) continue;
+                                const int pdst = rl(dst, l), pds = rl(ds, l);
+                                if (lane == 0) staged_start(C, psrc, pdst, pds, mx);
+                                migs = true;
+                                wave_sync();
+                            }
                         }
-                        nst += __popcll(pm);
                         if (sm) break;
                     }
                 }
-                if (NW > 1 && lane == 0) *C.e2n2 = nst;
-                migs = migs || nst > 0;
-                wave_sync();
-                nstaged = nst;
-            }
-            if (NW > 1) {
-                block_sync<NW>();
-                nstaged = *C.e2n2;
-            }
-            if (nstaged) {
-                // the running candidate of largest tier, then fewest blocks, then
-                // newest, its slot in the key's low bits (tier rank 4 bits, blocks
-                // 16, seq 32, slot 12); wave w reads chunks w, w + NW, ...  (One wave
-                // scanning 2048 slots took 8K cycles of the wide workload's tick.)
-                unsigned long long* best = reinterpret_cast<unsigned long long*>(C.fd);
-                for (int x = 0; x < nstaged; ++x) {
-                    const int psrc = C.gtmp[x] & 0xFF;
-                    const size_t sbase = size_t(psrc) * S;
-                    if (C.B[psrc] == 0) continue;  // nothing runs (a drained source)
-                    const int nch = live_chunks(C, psrc, lane);
-                    unsigned long long bk = 0;
-                    for (int c0 = wid; c0 < nch; c0 += 4 * NW) {
-                        uint32_t v[4], m[4], q[4];
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            const int c = c0 + g * NW;
-                            const uint4 rr = c < nch ? C.slot[sbase + c * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
-                            v[g] = rr.x; m[g] = rr.y; q[g] = rr.z;
-                        }
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            if (wst(v[g]) == 2u && !(m[g] & kMigrating)) {
-                                const uint32_t fin = fin_of(v[g], t);
-                                const uint32_t nb = uint32_t(65535 - blocks_of(wlo(v[g]) - (fin - t), C.shift));
-                                const unsigned long long kk =
-                                    (((rank_of(C, (m[g] >> 2) & 15u) + 1ull) << 48 | static_cast<unsigned long long>(nb) << 32 | q[g]) << 12) |
-                                    uint32_t((c0 + g * NW) * 64 + lane);
-                                bk = kk > bk ? kk : bk;
-                            }
-                        }
-                    }
-                    const unsigned long long mx = wmax64(bk);
-                    if (lane == 0 && mx) atomicMax(&best[x], mx);
+                if (NW > 1) {
+                    if (lane == 0) *C.e2n2 = nst;
+                    migs = migs || nst > 0;
                 }
+                wave_sync();
+            }
+            if constexpr (NW > 1) {
                 block_sync<NW>();
-                if (wid == 0) {
-                    for (int x = lane; x < nstaged; x += 64) {
-                        const unsigned long long mx = best[x];
-                        if (mx == 0) continue;  // nothing to move (an empty draining source)
-                        const int e = C.gtmp[x], psrc = e & 0xFF, pdst = (e >> 8) & 0xFF, pds = e >> 16;
-                        const int cs = int(mx & 0xFFFu);
-                        s_set_wm(C, size_t(pdst) * S + pds, kInbW, kInbound);
-                        C.occ[pdst * W + (pds >> 6)] |= 1ull << (pds & 63);
-                        C.live[pdst] += 1;
-                        atomicOr(&s_meta(C, size_t(psrc) * S + cs), kMigrating);
-                        int* m = &C.mig[4 * psrc];
-                        m[0] = pdst; m[1] = cs; m[2] = pds; m[3] = 0;
-                        stat(C, kMigStarted, 1);
+                const int nstaged = *C.e2n2;
+                if (nstaged) {
+                    unsigned long long* best = reinterpret_cast<unsigned long long*>(C.fd);
+                    for (int x = 0; x < nstaged; ++x) {
+                        const unsigned long long mx = staged_best<NW>(C, C.gtmp[x] & 0xFF, t, lane, wid);
+                        if (lane == 0 && mx) atomicMax(&best[x], mx);
                     }
-                    wave_sync();
+                    block_sync<NW>();
+                    if (wid == 0) {
+                        for (int x = lane; x < nstaged; x += 64) {
+                            const int e = C.gtmp[x];
+                            if (best[x]) staged_start(C, e & 0xFF, (e >> 8) & 0xFF, e >> 16, best[x]);
+                        }
+                        wave_sync();
+                    }
                 }
             }
             block_sync<NW>();

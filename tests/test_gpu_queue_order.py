@@ -120,3 +120,30 @@ def test_one_wave_where_the_load_leaves_no_queue():
     assert g.launch()[0] == 64
     with pytest.raises(MtsError):
         g.set_launch(256, 0)
+
+
+@pytest.mark.parametrize("cfg,depth", [
+    # runs that end inside a word of slots, fill instances one after the other,
+    # are more than the list of deferred runs holds, or fill the cluster
+    (_cfg(65, 128, 300, dict(kind="gamma_poisson", mean=400.0, cv=3.0), out=20.0), 0),
+    (_cfg(65, 128, 300, dict(kind="gamma_poisson", mean=400.0, cv=3.0), out=20.0), 7),
+    (_cfg(129, 512, 700, dict(kind="gamma_poisson", mean=300.0, cv=4.0), K=1), 3),
+    (_cfg(96, 192, 500, dict(kind="gamma_poisson", mean=300.0, cv=3.0), blind=1), 7),
+    (_cfg(100, 256, 500, dict(kind="gamma_poisson", mean=200.0, cv=4.0), infaas=True), 7),
+    (with_extensions(_cfg(70, 320, 500, dict(kind="gamma_poisson", mean=200.0, cv=4.0))), 7),
+], ids=["depth0", "fills", "one_tier", "blind", "infaas", "ext"])
+def test_long_bursts_placed_by_all_waves(cfg, depth):
+    g, orc = Scheduler(cfg), oracle.Oracle(cfg)
+    g.queue_cache = depth
+    flags = np.zeros(2 * cfg["n_instances"], np.uint8)
+    for ticks, drained in ((40, ()), (50, (0, 5, 64)), (50, (0, 64))):
+        for i in range(cfg["n_instances"]):
+            orc.set_drain(0, i, i in drained)
+            flags[i] = i in drained
+        g.set_draining(flags)
+        g.step(ticks)
+        orc.step(ticks)
+        got, want = g.export(), orc.export()
+        for k in want:
+            assert np.array_equal(got[k], want[k]), "depth %d field %s" % (depth, k)
+        assert g.stats()["raw"][86] == 0
