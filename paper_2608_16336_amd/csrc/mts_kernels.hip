@@ -122,9 +122,9 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     o = al8(o);
     L.ext = o;   o += ext ? 8 + IM * 4 : 0;
     // multi-wave kernels: values the waves combine (the auto-scaling sum, an
-    // abort flag, the admission work list's length and next entry)
+    // abort flag, the work lists' lengths and next entries)
     o = al8(o);
-    L.blk = o;   o += nw > 1 ? 32 : 0;
+    L.blk = o;   o += nw > 1 ? 40 : 0;
     // kernels for 128+ instances: per wave 64 (key, slot | demand) pairs, the rescan's
     // selected requests before they are ranked (the dispatch's deferred
     // bursts and the pairing's sorted blocks of 64 (key, index) pairs use the
@@ -185,6 +185,8 @@ struct Ctx {
     int* e2go;                 // pairing runs this tick (set by wave 0)
     int* e2n2;                 // staged copies to start
     int* kcnt;                 // entries that stay in the visited finish bucket
+    int *gln, *glnext;         // four-wave kernels: the preempting instances' list
+                               // (in order[] too), its next entry
     uint2* rsel;               // this wave's 64 entries of the rescan selection buffer
     // HBM: timing wheel of this replica, slot arrays, latency histograms
     uint32_t* wheel;           // [wsz][wcap] instance << 16 | slot
@@ -284,6 +286,8 @@ __device__ inline Ctx carve(char* base, const Params& P)
     C.e2go = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 20) : nullptr;
     C.e2n2 = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 24) : nullptr;
     C.kcnt = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 28) : nullptr;
+    C.gln = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 32) : nullptr;
+    C.glnext = NW > 1 ? reinterpret_cast<int*>(base + Y.blk + 36) : nullptr;
     C.rsel = IM >= 128 ? reinterpret_cast<uint2*>(base + Y.rsel) + 64 * (threadIdx.x >> 6) : nullptr;
     C.I = P.I; C.S = P.S; C.W = P.W; C.RB = P.RB;
     C.shift = P.blk_shift;
@@ -1562,11 +1566,12 @@ __device__ inline void admit_batch(const Ctx& C, int i, uint32_t t, int lane)
 // it, which are the smallest keys of its queue in order: the longest fitting
 // prefix is admitted at once (admit_ranked).  When all of them fit and more
 // wait, the head of line is unknown afterwards.
+template <bool XT>
 __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
 {
     const int n = C.qn[i];
-    // (kernels for 128+ instances) the extension follows the ring
-    const int xv = C.xn ? C.xn[i] : 0, xc = xv & 0xFFFF, xh = xv >> 16;
+    // (XT, the kernels for 128+ instances) the extension follows the ring
+    const int xv = XT ? C.xn[i] : 0, xc = xv & 0xFFFF, xh = xv >> 16;
     const int w = min(64, n + xc + 1);
     unsigned long long key = kNone;
     uint32_t word = 0, meta = 0, ta = 0;
@@ -1574,7 +1579,7 @@ __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
     if (lane == 0) {
         key = C.holk[i]; word = C.hwd[i]; meta = C.hmt[i]; ta = C.hta[i]; slot = C.hols[i];
     } else if (lane < w) {
-        const uint4 e = lane <= n ? C.qt[qc_at(C, i, lane - 1)] : *qx_at(C, i, xh, lane - n - 1);
+        const uint4 e = !XT || lane <= n ? C.qt[qc_at(C, i, lane - 1)] : *qx_at(C, i, xh, lane - n - 1);
         const uint32_t tier = (e.w >> 12) & 15u;
         key = qc_key(C, e);
         word = e.y;
@@ -1582,10 +1587,9 @@ __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
         ta = e.z;
         slot = int(e.w & 0xFFFu);
     }
-    if (!C.xn) {
+    if constexpr (!XT) {
         admit_ranked(C, i, t, lane, w, key, word, meta, ta, slot, C.nwait[i] == w);
-        return;
-    }
+    } else {
     // While whole windows fit, the next 64 entries of the extension are on
     // their way when a window is admitted: one memory round trip per window, and
     // none for the head of line in between.
@@ -1610,6 +1614,7 @@ __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
         meta = kWaiting | (tier << 2) | (((nx.w >> 16) & 1u) << 6);
         ta = nx.z;
         slot = int(nx.w & 0xFFFu);
+    }
     }
 }
 
@@ -1738,15 +1743,15 @@ __device__ inline void admit_head(const Ctx& C, int i, uint32_t t)
 // is unknown, the previous tick's placements, a gather of a short queue, a
 // cached run, or one head of line -- until the head of line does not fit or
 // nothing waits.  Every step admits at least one request, or finds the head
-// of line, so the loop ends.  (The kernels for 128+ instances hand instances
-// to waves dynamically with it.)
-template <int GR, int MK>
+// of line, so the loop ends.  (The multi-wave kernels hand instances to waves
+// dynamically with it.)
+template <int GR, int MK, bool SEL>
 __device__ inline void admit_all(const Ctx& C, int i, uint32_t t, int lane)
 {
     for (;;) {
         const int h = C.hols[i];
         if (h == kHolUnknown) {
-            rescan_admit<GR, MK, true>(C, i, t, lane);
+            rescan_admit<GR, MK, SEL>(C, i, t, lane);
             continue;
         }
         if (h < 0 || C.hold[i] > C.freeb[i]) break;
@@ -1757,7 +1762,7 @@ __device__ inline void admit_all(const Ctx& C, int i, uint32_t t, int lane)
         } else if (nw >= 2 && nw <= 64 && !cached) {
             admit_batch<GR>(C, i, t, lane);
         } else if (cached) {
-            admit_cached(C, i, t, lane);
+            admit_cached<SEL>(C, i, t, lane);
         } else {
             if (lane == 0) admit_head(C, i, t);
             wave_sync();
@@ -1881,6 +1886,14 @@ __device__ __forceinline__ void block_sync()
 {
     if (NW > 1) __syncthreads();
     else wave_sync();
+}
+
+// the wave's next entry of a work list, by its cursor; uniform
+__device__ __forceinline__ int next_of(int* cursor, int lane)
+{
+    int k = 0;
+    if (lane == 0) k = atomicAdd(cursor, 1);
+    return rl(k, 0);
 }
 
 // Image of a replica's LDS between launches: a header {tick it stands at,
@@ -2215,6 +2228,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             if (!warm)
                 for (uint32_t i = tid; i < P.I; i += NT) wlb(C)[i] = 0u;
         }
+        if (NW > 1 && tid == 0) { *C.gln = 0; *C.glnext = 0; }
         if (wid == 0) headroom_table(C, hq, lane);
         unsigned next_seq = P.next_seq[r];
         uint32_t run_acc = 0, wait_acc = 0;  // per lane, at most 1024 ticks x 4 x 2048
@@ -2303,11 +2317,36 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 }
                 pre[j] = ballot(np);
                 preempting = preempting || pre[j] != 0;
+                if (NW > 1 && !WIDE && np) C.order[atomicAdd(C.gln, 1)] = int(i);
             }
             // migrations to abort: set by preemption and finish, kept in a register
             // (multi-wave kernels: another wave's preemption sets the block flag)
             bool abort_any = false;
-            if (preempting) {
+            if constexpr (NW > 1 && !WIDE) {
+                // Four waves: the preempting instances are listed and the waves take
+                // them one at a time, as in admission below.  With each wave on the
+                // instances it owns, the others waited for the one with most of
+                // them: 15K of the overloaded study's 97K cycles a tick.
+                if (tid == 0) {
+                    *C.bsum = 0;  // the auto-scaling sum of this tick (phase C)
+                    *C.wln = 0;   // the admission work list (phase B)
+                    *C.wlnext = 0;
+                }
+                block_sync<NW>();
+                const int ng = *C.gln;
+                if (ng) {
+                    for (int k = next_of(C.glnext, lane); k < ng; k = next_of(C.glnext, lane))
+                        abort_any = preempt<4, 2, QC>(C, C.order[k], t, lane) || abort_any;
+                    if (abort_any && lane == 0) *C.bflag = 1;
+                    block_sync<NW>();
+                }
+                if (wid == 0) {
+                    // (every wave has read the list's length where it is not 0)
+                    if (lane == 0) { *C.gln = 0; *C.glnext = 0; }
+                    preempting = *C.nvic != 0;
+                    abort_any = *C.bflag != 0;
+                }
+            } else if (preempting) {
                 wave_sync();
 #pragma unroll
                 for (int j = 0; j < OPL; ++j)
@@ -2325,7 +2364,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 nb_all = (C.wc[bk >> 1] >> ((bk & 1u) * 16u)) & 0xFFFFu;
                 by_all = nb_all > 64u && !((C.wov[bk >> 5] >> (bk & 31u)) & 1u);
             }
-            if (NW > 1) {
+            if (WIDE) {
                 if (abort_any && lane == 0) *C.bflag = 1;
                 if (tid == 0) {
                     *C.bsum = 0;  // the auto-scaling sum of this tick (phase C)
@@ -2437,20 +2476,45 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 }
                 block_sync<NW>();
                 const int nl = *C.wln;
-                for (;;) {
-                    int k = 0;
-                    if (lane == 0) k = atomicAdd(C.wlnext, 1);
-                    k = rl(k, 0);
-                    if (k >= nl) break;
-                    admit_all<16, 3>(C, C.order[k], t, lane);
-                }
+                for (int k = next_of(C.wlnext, lane); k < nl; k = next_of(C.wlnext, lane))
+                    admit_all<16, 3, true>(C, C.order[k], t, lane);
                 // phase C reads the instances each wave owns, which any wave
                 // may have admitted on
                 block_sync<NW>();
-            } else {
-                // lane l of wave w holds instance l NW + w; its summary is read once per
-                // round
+            } else if constexpr (NW > 1) {
+                // Four waves: each lane admits the known heads of line of its
+                // instance that fit one by one; what takes a whole wave -- a
+                // rescan, the previous tick's arrivals, a gather -- is listed and
+                // taken as above.  (Each wave on its own instances left the others
+                // waiting for 16K of the overloaded study's 97K cycles a tick;
+                // this and the preemptions' list: 23.33 -> 21.08 ms per 500 ticks.
+                // Eight chunks of slots a round trip instead of four: 22.65, for
+                // 77 spilled registers instead of 48.)
                 const int i = lane * NW + wid;
+                if (uint32_t(i) < I) {
+                    const int h = C.hols[i], hd = C.hold[i], fr = C.freeb[i], nw = C.nwait[i], fs = C.frs[i], qn = C.qn[i];
+                    bool need = h == kHolUnknown;
+                    if (h >= 0 && hd <= fr) {
+                        need = fs || (nw >= 2 && nw <= 64 && qn == 0);
+                        if (!need) {
+                            do {
+                                admit_head(C, i, t);
+                            } while (C.hols[i] >= 0 && C.hold[i] <= C.freeb[i]);
+                            need = C.hols[i] == kHolUnknown;
+                        }
+                    }
+                    if (need) C.order[atomicAdd(C.wln, 1)] = i;
+                }
+                block_sync<NW>();
+                const int nl = *C.wln;
+                if (nl) {
+                    for (int k = next_of(C.wlnext, lane); k < nl; k = next_of(C.wlnext, lane))
+                        admit_all<4, 2, false>(C, C.order[k], t, lane);
+                    block_sync<NW>();
+                }
+            } else {
+                // lane l holds instance l; its summary is read once per round
+                const int i = lane;
                 const bool own = uint32_t(i) < I;
                 for (;;) {
                     int h = kNoHol, hd = 0, fr = 0, nw = 0, fs = 0, qn = 0;
@@ -2466,17 +2530,13 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                     const unsigned long long um = ballot(h == kHolUnknown);
                     if (um) {
                         for (unsigned long long m = um; m; m &= m - 1)
-                            any = rescan_admit<4, 2>(C, ffs64(m) * NW + wid, t, lane) || any;
+                            any = rescan_admit<4, 2>(C, ffs64(m), t, lane) || any;
                         look();
                     }
                     const bool fits = h >= 0 && hd <= fr;
                     // queues that hold the previous tick's arrivals only
                     const unsigned long long fm = ballot(fits && fs);
-                    if (NW == 1) {
-                        if (fm) admit_fresh_all(C, t, lane);
-                    } else {
-                        for (unsigned long long m = fm; m; m &= m - 1) admit_fresh(C, ffs64(m) * NW + wid, t, lane);
-                    }
+                    if (fm) admit_fresh_all(C, t, lane);
                     const bool rest = fits && !fs;
                     if (ballot(rest)) {
                         const bool batch = rest && nw >= 2 && nw <= 64 && !(C.td && qn > 0);
@@ -2491,11 +2551,10 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                             any = any || C.hols[i] == kHolUnknown;
                         }
                         wave_sync();
-                        for (unsigned long long m = ballot(batch); m; m &= m - 1) admit_batch<4>(C, ffs64(m) * NW + wid, t, lane);
+                        for (unsigned long long m = ballot(batch); m; m &= m - 1) admit_batch<4>(C, ffs64(m), t, lane);
                     }
                     if (!ballot(any)) break;
                 }
-                if (NW > 1) wave_sync();
             }
             // auto-scaling signal (Section 3.6): the cluster average of the
             // normal-priority freeness F_normal = (free - head-of-line demand) /
