@@ -875,6 +875,12 @@ template <int GR, int MK, bool kArr>
 __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
 {
     const size_t b = size_t(i) * C.S;
+    // (MK: a call takes one victim nearly always, since a victim frees tens of
+    // blocks and a tick's growth is a few; a second key per lane only spares the
+    // second scan of a call with more.  One key instead of two: overloaded study
+    // 21.08 -> 20.70 ms, gauss10 14.84 -> 14.56, with extensions 4.39 -> 4.26,
+    // INFaaS sweep 6.59 -> 6.44, tiny run 6.45 -> 6.34; wide, whose bursts take
+    // more victims a call, 15.20 -> 15.66, keeps two.)
     // (kArr: a victim's arrival tick comes with the scan; 16 chunks a round trip
     // leave it no registers, and without a queue cache its spills cost the
     // INFaaS sweep 4 %)
@@ -2336,7 +2342,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 const int ng = *C.gln;
                 if (ng) {
                     for (int k = next_of(C.glnext, lane); k < ng; k = next_of(C.glnext, lane))
-                        abort_any = preempt<4, 2, QC>(C, C.order[k], t, lane) || abort_any;
+                        abort_any = preempt<4, 1, QC>(C, C.order[k], t, lane) || abort_any;
                     if (abort_any && lane == 0) *C.bflag = 1;
                     block_sync<NW>();
                 }
@@ -2351,7 +2357,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
 #pragma unroll
                 for (int j = 0; j < OPL; ++j)
                     for (unsigned long long m = pre[j]; m; m &= m - 1)
-                        abort_any = preempt<(IM >= 128 ? 16 : 4), 2, QC && IM < 128>(
+                        abort_any = preempt<(IM >= 128 ? 16 : 4), (IM >= 128 ? 2 : 1), QC && IM < 128>(
                                         C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || abort_any;
             }
             // a bucket of more than 64 entries is visited by every wave (the count
