@@ -2641,6 +2641,20 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             uint4* runs = reinterpret_cast<uint4*>(WIDE ? C.rsel - 64 * wid : nullptr);
             int n2 = 0, npairs = 0;
             if (wid == 0) {
+            // the next tick's records: a read of 2K cycles on the sweep, whose
+            // records fit no cache, waited for at the top of the tick (issued after
+            // the dispatch: 1.5K of 16.8K cycles there, sweep 8.87 ms per 1000
+            // ticks, here 8.64; ahead of the freeness phase, across which they cost
+            // registers, 8.93)
+            if (tl + 1 < nt) {
+                if (((tl + 1u) & 63u) == 0) {
+                    const uint32_t* cn = uniform_ptr(cnts + tl + 1u);
+                    cnt64 = tl + 1u + lane < nt ? cn[lane] : 0u;
+                }
+                const unsigned long long* rn = uniform_ptr(rec + P.arr_cap);
+                a_nx = uint32_t(lane) < lim ? rn[lane] : 0ull;
+            }
+
             // ===================== D: tier-ordered dispatch =====================
             // an instance with an empty queue now holds, after this dispatch, only
             // this tick's arrivals; they are recorded in LDS when they fit one wave
@@ -3081,15 +3095,6 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 for (int x = 0; x < nruns; ++x) place_run<NW>(C, rec, t, runs[2 * x], runs[2 * x + 1], lane, wid);
             }
             if (wid == 0) {
-            if (tl + 1 < nt) {
-                if (((tl + 1u) & 63u) == 0) {
-                    const uint32_t* cn = uniform_ptr(cnts + tl + 1u);
-                    cnt64 = tl + 1u + lane < nt ? cn[lane] : 0u;
-                }
-                const unsigned long long* rn = uniform_ptr(rec + P.arr_cap);
-                a_nx = uint32_t(lane) < lim ? rn[lane] : 0ull;
-            }
-
             // ===================== E1: staged copies =====================
             // a commit leaves the source slot and its wheel entry (without places,
             // source slot in gtmp and finish tick in order, searched after the loop)
