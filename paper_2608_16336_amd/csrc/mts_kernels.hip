@@ -2645,15 +2645,18 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             // records fit no cache, waited for at the top of the tick (issued after
             // the dispatch: 1.5K of 16.8K cycles there, sweep 8.87 ms per 1000
             // ticks, here 8.64; ahead of the freeness phase, across which they cost
-            // registers, 8.93)
-            if (tl + 1 < nt) {
+            // registers, 8.93).  Four waves, whose tick is longer, load them after it
+            // (gauss10 with extensions 4.26 ms per 250 ticks, before it 4.34)
+            auto load_next = [&] {
+                if (tl + 1 >= nt) return;
                 if (((tl + 1u) & 63u) == 0) {
                     const uint32_t* cn = uniform_ptr(cnts + tl + 1u);
                     cnt64 = tl + 1u + lane < nt ? cn[lane] : 0u;
                 }
                 const unsigned long long* rn = uniform_ptr(rec + P.arr_cap);
                 a_nx = uint32_t(lane) < lim ? rn[lane] : 0ull;
-            }
+            };
+            if (NW == 1 || WIDE) load_next();
 
             // ===================== D: tier-ordered dispatch =====================
             // an instance with an empty queue now holds, after this dispatch, only
@@ -3086,6 +3089,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 }
                 if (lane == 0 && nfall) stat(C, kDrainFallback, unsigned(nfall));
             }
+            if (NW > 1 && !WIDE) load_next();
             if (WIDE && lane == 0) *C.kcnt = nruns;
             if (WIDE) wave_sync();
             }  // wave 0
