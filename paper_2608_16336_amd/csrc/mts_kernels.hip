@@ -869,48 +869,6 @@ __device__ inline void wheel_erase_search(const Ctx& C, uint32_t fin, int i, int
     }
 }
 
-// The victim of instance i in slot vs (word v, meta m, arrival tick vta, key mx)
-// returns to the queue (recompute semantics: len, rem and seq kept, its blocks
-// freed; the caller counts them).  One wave.
-__device__ inline void preempt_take(const Ctx& C, int i, int vs, uint32_t v, uint32_t m, uint32_t vta, unsigned long long mx,
-                                    uint32_t t, int lane)
-{
-    const size_t b = size_t(i) * C.S;
-    const uint32_t lenf = wlo(v), fin = fin_of(v, t);
-    const uint32_t remb = fin - t + 1u, lenb = lenf - remb;
-    const uint32_t vw = kWaitW | (remb << 16) | lenb;
-    const uint32_t vmeta = (m & 0xFFu & ~(3u | kMigrating)) | kWaiting;
-    const int vt = int((m >> 2) & 15u);
-    const int vr = int((lenf - fin - 1u) & C.bmask);
-    if (lane == 0) {
-        s_set_wm(C, b + vs, vw, vmeta);
-        if (C.td) wheel_erase(C, fin, m);
-    }
-    if (!C.td) wheel_erase_search(C, fin, i, vs, lane);
-    bool deep = false;
-    if (lane == 0) {
-        C.held[i] -= blocks_of(lenb, C.shift);
-        C.B[i] -= 1;
-        C.nwait[i] += 1;
-        C.frs[i] = 0;
-        if (C.fsum) C.flags[i] |= kFlagIntf;  // (INFaaS state)
-        // (several waves may preempt at once; a count above kVic means
-        // the list missed some)
-        const int nv = atomicAdd(C.nvic, 1);
-        if (nv < kVic) C.vic[nv] = (uint32_t(i) << 16) | uint32_t(vs);
-        c16_dec(C.res, res_idx(C, i, vr));
-        tier_dec(C, i, vt);
-        stat(C, vt * 8 + kPreempted, 1);
-        if (m & kMigrating) C.flags[i] |= kFlagAbort;
-        const unsigned long long key = (rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx);
-        deep = hol_insert(C, i, key, vs, vw, vmeta, vta);
-        if (C.ext) wlb(C)[i] = vta < wlb(C)[i] ? vta : wlb(C)[i];
-    }
-    wave_sync();
-    if (C.xn && ballot(deep))
-        qx_insert(C, i, qc_pack((rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx), vs, vw, vmeta, vta), lane);
-}
-
 // memory pressure: preempt the largest (tier, seq) running request until the
 // growth of this tick fits (Section 2.2; recompute semantics)
 template <int GR, int MK, bool kArr>
@@ -921,10 +879,11 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
     // blocks and a tick's growth is a few; a second key per lane only spares the
     // second scan of a call with more.  One key instead of two: overloaded study
     // 21.08 -> 20.70 ms, gauss10 14.84 -> 14.56, with extensions 4.39 -> 4.26,
-    // INFaaS sweep 6.59 -> 6.44, tiny run 6.45 -> 6.34.)
-    // (kArr: a victim's arrival tick comes with the scan; without a queue cache
-    // its spills cost the INFaaS sweep 4 %.  Eight chunks a round trip there:
-    // INFaaS sweep 6.45 -> 6.75 ms, spills too.)
+    // INFaaS sweep 6.59 -> 6.44, tiny run 6.45 -> 6.34; wide, whose bursts take
+    // more victims a call, 15.20 -> 15.66, keeps two.)
+    // (kArr: a victim's arrival tick comes with the scan; 16 chunks a round trip
+    // leave it no registers, and without a queue cache its spills cost the
+    // INFaaS sweep 4 %)
     int G = C.gtmp[i], fr = C.freeb[i];
     bool aborted = false;
     bool scan = G > fr;
@@ -989,86 +948,53 @@ __device__ inline bool preempt(const Ctx& C, int i, uint32_t t, int lane)
             k[MK - 1] = win ? 0ull : k[MK - 1];
             taken += win ? 1 : 0;
             const bool unknown = ballot(win && more && taken >= MK) != 0;
-            const uint32_t lenf = wlo(v), lenb = lenf - (fin_of(v, t) - t + 1u);
-            fr += blocks_of(lenb, C.shift);
-            G -= (lenb & C.bmask) == 0;
-            aborted = aborted || (m & kMigrating) != 0;
-            preempt_take(C, i, vs, v, m, vta, mx, t, lane);
+            // the victim returns to the queue (recompute semantics: len, rem and
+            // seq kept, its blocks freed)
+            const uint32_t lenf = wlo(v), fin = fin_of(v, t);
+            const uint32_t remb = fin - t + 1u, lenb = lenf - remb;
+            const uint32_t vw = kWaitW | (remb << 16) | lenb;
+            const uint32_t vmeta = (m & 0xFFu & ~(3u | kMigrating)) | kWaiting;
+            const int vb = blocks_of(lenb, C.shift);
+            const int vg = (lenb & C.bmask) == 0;
+            const int vt = int((m >> 2) & 15u);
+            const int vr = int((lenf - fin - 1u) & C.bmask);
+            const bool vm = (m & kMigrating) != 0;
+            if (lane == 0) {
+                s_set_wm(C, b + vs, vw, vmeta);
+                if (C.td) wheel_erase(C, fin, m);
+            }
+            if (!C.td) wheel_erase_search(C, fin, i, vs, lane);
+            fr += vb;
+            G -= vg;
+            aborted = aborted || vm;
+            bool deep = false;
+            if (lane == 0) {
+                C.held[i] -= vb;
+                C.B[i] -= 1;
+                C.nwait[i] += 1;
+                C.frs[i] = 0;
+                if (C.fsum) C.flags[i] |= kFlagIntf;  // (INFaaS state)
+                // (several waves may preempt at once; a count above kVic means
+                // the list missed some)
+                const int nv = atomicAdd(C.nvic, 1);
+                if (nv < kVic) C.vic[nv] = (uint32_t(i) << 16) | uint32_t(vs);
+                c16_dec(C.res, res_idx(C, i, vr));
+                tier_dec(C, i, vt);
+                stat(C, vt * 8 + kPreempted, 1);
+                if (vm) C.flags[i] |= kFlagAbort;
+                const unsigned long long key = (rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx);
+                deep = hol_insert(C, i, key, vs, vw, vmeta, vta);
+                if (C.ext) wlb(C)[i] = vta < wlb(C)[i] ? vta : wlb(C)[i];
+            }
+            wave_sync();
+            if (C.xn && ballot(deep))
+                qx_insert(C, i, qc_pack((rank_of(C, uint32_t(vt)) << 32) | static_cast<unsigned>(mx), vs, vw, vmeta, vta), lane);
             if (unknown) { scan = G > fr; break; }  // the winner's next key is unknown: read again
         }
     }
     // this tick's growth, now that it fits
     if (lane == 0) { C.freeb[i] = fr - G; C.held[i] += G; }
     wave_sync();
-    return aborted;
-}
-
-// The same by every wave of the replica (kernels for 128+ instances): each
-// keeps its part of the instance's slots in registers, so the slots are read
-// once whatever the number of victims.  A round's victim is the largest of the
-// waves' largest keys, exchanged in the rescans' buffers, which are free at this
-// point of the tick; two sets of entries in turn (par), so that one barrier a
-// round is enough.  Wave 0 takes the victim while the others go on.  (One wave
-// per instance took 14K cycles a call, and with 2.8 victims a tick the waves
-// waited 20K of the wide workload's 90K cycles for the last one.)
-template <int NW>
-__device__ inline bool preempt_wide(const Ctx& C, int i, uint32_t t, int lane, int wid, uint32_t& par)
-{
-    constexpr int CH = int(kMaxSlots) / 64 / NW;  // chunks of 64 slots per wave
-    const size_t b = size_t(i) * C.S;
-    int G = C.gtmp[i], fr = C.freeb[i];
-    const int nch = live_chunks(C, i, lane);
-    uint32_t v[CH], m[CH], a[CH];
-    unsigned long long k[CH];
-#pragma unroll
-    for (int g = 0; g < CH; ++g) {
-        const int c = g * NW + wid;
-        const uint4 rr = c < nch ? C.slot[b + c * 64 + lane] : make_uint4(0u, 0u, 0u, 0u);
-        v[g] = rr.x; m[g] = rr.y; a[g] = rr.w;
-        k[g] = wst(rr.x) == 2u ? ((rank_of(C, (rr.y >> 2) & 15u) + 1ull) << 32) | rr.z : 0ull;
-    }
-    bool aborted = false;
-    while (G > fr) {
-        unsigned long long bk = k[0];
-        uint32_t bv = v[0], bm = m[0], ba = a[0];
-        int bs = wid * 64 + lane;
-#pragma unroll
-        for (int g = 1; g < CH; ++g) {
-            const bool gt = k[g] > bk;
-            bk = gt ? k[g] : bk;
-            bv = gt ? v[g] : bv;
-            bm = gt ? m[g] : bm;
-            ba = gt ? a[g] : ba;
-            bs = gt ? (g * NW + wid) * 64 + lane : bs;
-        }
-        const unsigned long long mx = wmax64(bk);
-        uint4* e = reinterpret_cast<uint4*>(C.rsel - 64 * wid) + 2 * NW * (par & 1u);
-        ++par;
-        if (lane == ffs64(ballot(bk == mx))) {
-            e[2 * wid] = make_uint4(uint32_t(mx), uint32_t(mx >> 32), bv, bm);
-            e[2 * wid + 1] = make_uint4(uint32_t(bs), ba, 0u, 0u);
-        }
-        __syncthreads();
-        const uint4 e0 = e[2 * (lane & (NW - 1))], e1 = e[2 * (lane & (NW - 1)) + 1];
-        const unsigned long long ek = static_cast<unsigned long long>(e0.y) << 32 | e0.x;
-        const unsigned long long top = wmax64(ek);
-        if (top == 0) break;  // nothing runs
-        const int wl = ffs64(ballot(ek == top));
-        const int vs = int(rlu(e1.x, wl));
-        const uint32_t vv = rlu(e0.z, wl), vm = rlu(e0.w, wl), vta = rlu(e1.y, wl);
-#pragma unroll
-        for (int g = 0; g < CH; ++g) k[g] = k[g] == top ? 0ull : k[g];
-        const uint32_t lenb = wlo(vv) - (fin_of(vv, t) - t + 1u);
-        fr += blocks_of(lenb, C.shift);
-        G -= (lenb & C.bmask) == 0;
-        aborted = aborted || (vm & kMigrating) != 0;
-        if (wid == 0) preempt_take(C, i, vs, vv, vm, vta, top, t, lane);
-    }
-    // this tick's growth, now that it fits
-    if (wid == 0) {
-        if (lane == 0) { C.freeb[i] = fr - G; C.held[i] += G; }
-        wave_sync();
-    }
     return aborted;
 }
 
@@ -2065,11 +1991,6 @@ __device__ inline void staged_start(const Ctx& C, int src, int dst, int ds, unsi
     stat(C, kMigStarted, 1);
 }
 
-// Up to this many preempting instances are taken one after the other by all
-// eight waves, more of them one by each wave (wide, against 15.33 ms per 300
-// ticks with every wave on its own instances: always together 15.78, up to two
-// 14.95, up to four 14.85)
-constexpr int kTogether = 4;
 // Bursts' rests kept for placement by all waves; more are placed as they come.
 constexpr int kMaxRuns = 8;
 // Places the m arrivals from index k1 on of this tick (records rec) that all go
@@ -2402,48 +2323,26 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                 }
                 pre[j] = ballot(np);
                 preempting = preempting || pre[j] != 0;
-                if (NW > 1 && np) C.order[atomicAdd(C.gln, 1)] = int(i);
-            }
-            // a bucket of more than 64 entries is visited by every wave (the count
-            // and the overflow flag are read here, where no wave writes them before
-            // the next barrier: all waves take the same branch)
-            bool by_all = false;
-            uint32_t nb_all = 0;
-            if (WIDE) {
-                const uint32_t bk = t & C.wmask;
-                nb_all = (C.wc[bk >> 1] >> ((bk & 1u) * 16u)) & 0xFFFFu;
-                by_all = nb_all > 64u && !((C.wov[bk >> 5] >> (bk & 31u)) & 1u);
+                if (NW > 1 && !WIDE && np) C.order[atomicAdd(C.gln, 1)] = int(i);
             }
             // migrations to abort: set by preemption and finish, kept in a register
             // (multi-wave kernels: another wave's preemption sets the block flag)
             bool abort_any = false;
-            if constexpr (NW > 1) {
-                // The preempting instances are listed.  Four waves take them one at a
-                // time, as in admission below; eight work on each together.  With
-                // each wave on the instances it owns, the others waited for the one
-                // with most of them: 15K of the overloaded study's 97K cycles a tick.
+            if constexpr (NW > 1 && !WIDE) {
+                // Four waves: the preempting instances are listed and the waves take
+                // them one at a time, as in admission below.  With each wave on the
+                // instances it owns, the others waited for the one with most of
+                // them: 15K of the overloaded study's 97K cycles a tick.
                 if (tid == 0) {
                     *C.bsum = 0;  // the auto-scaling sum of this tick (phase C)
                     *C.wln = 0;   // the admission work list (phase B)
                     *C.wlnext = 0;
-                    if (WIDE) *C.kcnt = 0;
                 }
                 block_sync<NW>();
                 const int ng = *C.gln;
                 if (ng) {
-                    if constexpr (WIDE) {
-                        uint32_t par = 0;
-                        if (ng <= kTogether) {
-                            for (int k = 0; k < ng; ++k)
-                                abort_any = preempt_wide<NW>(C, C.order[k], t, lane, wid, par) || abort_any;
-                        } else {
-                            for (int k = next_of(C.glnext, lane); k < ng; k = next_of(C.glnext, lane))
-                                abort_any = preempt<16, 2, false>(C, C.order[k], t, lane) || abort_any;
-                        }
-                    } else {
-                        for (int k = next_of(C.glnext, lane); k < ng; k = next_of(C.glnext, lane))
-                            abort_any = preempt<4, 1, QC>(C, C.order[k], t, lane) || abort_any;
-                    }
+                    for (int k = next_of(C.glnext, lane); k < ng; k = next_of(C.glnext, lane))
+                        abort_any = preempt<4, 1, QC>(C, C.order[k], t, lane) || abort_any;
                     if (abort_any && lane == 0) *C.bflag = 1;
                     block_sync<NW>();
                 }
@@ -2458,7 +2357,32 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
 #pragma unroll
                 for (int j = 0; j < OPL; ++j)
                     for (unsigned long long m = pre[j]; m; m &= m - 1)
-                        abort_any = preempt<4, 1, QC>(C, int(64u * j + ffs64(m)), t, lane) || abort_any;
+                        abort_any = preempt<(IM >= 128 ? 16 : 4), (IM >= 128 ? 2 : 1), QC && IM < 128>(
+                                        C, int((64u * j + ffs64(m)) * NW + uint32_t(wid)), t, lane) || abort_any;
+            }
+            // a bucket of more than 64 entries is visited by every wave (the count
+            // and the overflow flag are read here, where no wave writes them:
+            // all waves take the same branch)
+            bool by_all = false;
+            uint32_t nb_all = 0;
+            if (WIDE) {
+                const uint32_t bk = t & C.wmask;
+                nb_all = (C.wc[bk >> 1] >> ((bk & 1u) * 16u)) & 0xFFFFu;
+                by_all = nb_all > 64u && !((C.wov[bk >> 5] >> (bk & 31u)) & 1u);
+            }
+            if (WIDE) {
+                if (abort_any && lane == 0) *C.bflag = 1;
+                if (tid == 0) {
+                    *C.bsum = 0;  // the auto-scaling sum of this tick (phase C)
+                    *C.wln = 0;   // the admission work list (phase B)
+                    *C.wlnext = 0;
+                    *C.kcnt = 0;
+                }
+                block_sync<NW>();
+                if (wid == 0) {
+                    preempting = *C.nvic != 0;
+                    abort_any = *C.bflag != 0;
+                }
             }
             if constexpr (WIDE) {
                 if (by_all) {
