@@ -43,7 +43,7 @@ VALU_PEAK_GINST = 256 * 2.4
 #   read, write   HBM bytes per launch from TCC_EA0_RDREQ_{32B,64B,128B} and
 #                 TCC_EA0_WRREQ{,_64B} (requests times their sizes)
 PROFILED = {
-    'e7eb6393498a72f8': {"valu_per_rt": 869.2, "lane_util": 0.3756, "read": 9133853824, "write": 7667387645},
+    '887cdeecf26652ba': {"valu_per_rt": 657.1, "lane_util": 0.5343, "read": 8284276998, "write": 7501849078},
 }
 
 
