@@ -371,6 +371,15 @@ int mts_get_launch(mts_handle h, uint32_t* threads, uint32_t* blocks);
 int mts_set_queue_cache(mts_handle h, uint32_t depth);
 int mts_get_queue_cache(mts_handle h, uint32_t* depth);
 
+/* Entries per instance of the queue cache's continuation in the state buffer
+ * (a test hook): the depth in use and the reserved one, both 0 for 64 or fewer
+ * instances, which have none.  mts_set_queue_extension lowers it (64 .. the
+ * reserved depth, else MTS_EINVAL) from the next mts_step on, so that tests
+ * reach a full one on small states; results never depend on it.  Either
+ * pointer may be NULL. */
+int mts_set_queue_extension(mts_handle h, uint32_t depth);
+int mts_get_queue_extension(mts_handle h, uint32_t* depth, uint32_t* depth_max);
+
 /* Finish wheel of the step kernel (a test hook): every running request is
  * filed under its finish tick in a per-replica wheel of buckets holding up to
  * `cap` entries each; a bucket that fills is rebuilt at its visit by an exact

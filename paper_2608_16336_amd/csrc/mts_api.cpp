@@ -28,6 +28,8 @@ struct mts_ctx {
     uint32_t wcap_max = 0;             // entries per bucket the layout reserves
     uint32_t blocks = 0;               // step-kernel blocks (one wave each); 0 = automatic
     uint32_t qdepth = 0;               // queue-cache entries per instance (chosen at create)
+    uint32_t qxd = 0;                  // entries of its extension in use (more than 64 instances)
+    uint32_t qxd_max = 0;              // and those the layout reserves
     bool four_auto = false;            // four waves per replica chosen at create
     bool four_waves = false;           // and in use (mts_set_launch can ask for one)
     int device = 0;
@@ -225,7 +227,7 @@ Params make_params(const mts_ctx* h)
     p.arr_rec = reinterpret_cast<unsigned long long*>(d + L.arr_rec);
     p.wheel = reinterpret_cast<uint32_t*>(d + L.wheel);
     p.qx = h->I > 64 ? reinterpret_cast<uint4*>(d + L.qx) : nullptr;
-    p.qxd = qx_depth(h->R, h->I, h->S);
+    p.qxd = h->qxd;
     p.img = L.img_n ? reinterpret_cast<uint4*>(d + L.img) : nullptr;
     p.img_n = L.img_n;
     return p;
@@ -277,6 +279,8 @@ int prepare(const mts_cfg* cfg, mts_ctx& x)
     x.chunk = chunk_for(x.R, x.arr_cap);
     wheel_size(x.cfg, x.tables, x.wsz, x.wcap);
     x.wcap_max = x.wcap;
+    x.qxd_max = x.I > 64 ? qx_depth(x.R, x.I, x.S) : 0;
+    x.qxd = x.qxd_max;
     x.lay = make_layout(x.cfg, x.tables, x.R, x.chunk, x.arr_cap, x.wsz, x.wcap);
     return MTS_OK;
 }
@@ -492,6 +496,26 @@ int mts_get_queue_cache(mts_handle h, uint32_t* depth)
 {
     if (!h || !depth) return MTS_EINVAL;
     *depth = h->qdepth;
+    return MTS_OK;
+}
+
+int mts_set_queue_extension(mts_handle h, uint32_t depth)
+{
+    // a rescan writes its whole selection behind the ring without looking at
+    // the depth: never less than that
+    if (!h || depth < kQxLeast || depth > h->qxd_max) return MTS_EINVAL;
+    // the depth is part of the launch image's key: the next launch starts
+    // without an extension
+    if (hipStreamSynchronize(h->last) != hipSuccess) return MTS_EDEVICE;
+    h->qxd = depth;
+    return MTS_OK;
+}
+
+int mts_get_queue_extension(mts_handle h, uint32_t* depth, uint32_t* depth_max)
+{
+    if (!h) return MTS_EINVAL;
+    if (depth) *depth = h->qxd;
+    if (depth_max) *depth_max = h->qxd_max;
     return MTS_OK;
 }
 

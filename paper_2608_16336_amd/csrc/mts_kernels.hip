@@ -1903,12 +1903,14 @@ __device__ __forceinline__ int next_of(int* cursor, int lane)
 }
 
 // Image of a replica's LDS between launches: a header {tick it stands at,
-// kImgMagic, queue-cache depth | waves << 8 | wheel capacity << 16, LDS bytes}
-// and the bytes.
+// kImgMagic, layout, LDS bytes} and the bytes.  The layout holds what the LDS
+// and the memory it points into are laid out by and the host can change:
+// queue-cache depth | waves << 4 | wheel capacity << 8 | extension depth << 20.
 // Both are uniform over the block.
 constexpr uint32_t kImgMagic = 0x4C445331u;
+static_assert(kMaxSlots < 1u << 12, "a wheel capacity and an extension depth (both at most kMaxSlots) fit 12 bits");
 template <uint32_t NT>
-__device__ __forceinline__ uint32_t img_layout(const Params& P) { return P.qdepth | (NT / 64u) << 8 | P.wcap << 16; }
+__device__ __forceinline__ uint32_t img_layout(const Params& P) { return P.qdepth | (NT / 64u) << 4 | P.wcap << 8 | P.qxd << 20; }
 template <uint32_t NT>
 __device__ inline bool image_read(const Params& P, uint32_t r, uint32_t t, char* lds, uint32_t tid)
 {

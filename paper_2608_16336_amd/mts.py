@@ -89,7 +89,8 @@ EXPORTED = ("mts_state_bytes", "mts_create", "mts_step", "mts_stats", "mts_diges
             "mts_export_state", "mts_import_state", "mts_get_table", "mts_get_headroom",
             "mts_tick", "mts_set_tick", "mts_set_launch", "mts_get_launch", "mts_set_timing",
             "mts_get_timing", "mts_set_draining", "mts_set_queue_cache", "mts_get_queue_cache",
-            "mts_set_wheel_cap", "mts_get_wheel", "mts_step_noalloc", "mts_destroy", "mts_strerror")
+            "mts_set_queue_extension", "mts_get_queue_extension", "mts_set_wheel_cap", "mts_get_wheel",
+            "mts_step_noalloc", "mts_destroy", "mts_strerror")
 
 _lib = None
 
@@ -124,6 +125,8 @@ def load_library(path=LIB_PATH):
     L.mts_set_draining.argtypes = [vp, u32, u32, vp]
     L.mts_set_queue_cache.argtypes = [vp, u32]
     L.mts_get_queue_cache.argtypes = [vp, ctypes.POINTER(u32)]
+    L.mts_set_queue_extension.argtypes = [vp, u32]
+    L.mts_get_queue_extension.argtypes = [vp, ctypes.POINTER(u32), ctypes.POINTER(u32)]
     L.mts_set_wheel_cap.argtypes = [vp, u32]
     L.mts_get_wheel.argtypes = [vp, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(u64)]
     L.mts_get_timing.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double),
@@ -135,7 +138,8 @@ def load_library(path=LIB_PATH):
     for f in ("mts_state_bytes", "mts_create", "mts_step", "mts_step_noalloc", "mts_stats", "mts_digest", "mts_export_state",
               "mts_import_state", "mts_get_table", "mts_get_headroom", "mts_set_launch", "mts_get_launch",
               "mts_set_timing", "mts_get_timing", "mts_set_draining", "mts_set_queue_cache",
-              "mts_get_queue_cache", "mts_set_wheel_cap", "mts_get_wheel"):
+              "mts_get_queue_cache", "mts_set_queue_extension", "mts_get_queue_extension", "mts_set_wheel_cap",
+              "mts_get_wheel"):
         getattr(L, f).restype = ci
     _lib = L
     return L
@@ -344,6 +348,16 @@ class Scheduler:
     @queue_cache.setter
     def queue_cache(self, depth):
         _check("mts_set_queue_cache", load_library().mts_set_queue_cache(self._h, depth))
+
+    def set_queue_extension(self, depth):
+        """Entries per instance of the queue cache's extension from the next step on (test hook)."""
+        _check("mts_set_queue_extension", load_library().mts_set_queue_extension(self._h, depth))
+
+    def queue_extension(self):
+        """(depth in use, reserved depth) of the queue cache's extension."""
+        d, m = ctypes.c_uint32(0), ctypes.c_uint32(0)
+        _check("mts_get_queue_extension", load_library().mts_get_queue_extension(self._h, ctypes.byref(d), ctypes.byref(m)))
+        return d.value, m.value
 
     def set_wheel_cap(self, cap):
         """Entries per finish-wheel bucket from the next step on (test hook)."""
