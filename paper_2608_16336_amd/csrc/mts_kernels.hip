@@ -2898,13 +2898,15 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
                             // the old head to the front of the cache; the others enter it
                             // once their slots are known (an empty queue's arrivals are
                             // served by the list of this tick's placements)
-                            const bool known = C.hols[i] >= 0;
-                            const bool all = nw0 == (known ? 1 + C.qn[i] + qx_count(C, int(i)) : 0);
+                            const bool known = C.hols[i] >= 0, push = known && head_r[j];
+                            if (push)
+                                qc_insert_at(C, int(i), 0, qc_pack(C.holk[i], C.hols[i], C.hwd[i], C.hmt[i], C.hta[i]));
+                            // (what is listed, after the push: it may drop the ring's last
+                            // entry, or a full extension as a whole)
+                            const bool all = nw0 + (push ? 1 : 0) == (known ? 1 + C.qn[i] + qx_count(C, int(i)) : 0);
                             const bool skip = !known && n <= uint32_t(kLast);
                             C.order[i] = skip ? kQcSkip : (all ? kQcAll : kQcPart) | (head_r[j] ? kQcHead : 0);
                             qc_any = qc_any || !skip;
-                            if (known && head_r[j])
-                                qc_insert_at(C, int(i), 0, qc_pack(C.holk[i], C.hols[i], C.hwd[i], C.hmt[i], C.hta[i]));
                         }
                         nadd[j] = 0;
                         if (head_r[j]) C.holk[i] = hk_r[j];

@@ -53,3 +53,39 @@ def test_the_depth_in_use_is_lowered_and_raised_between_steps():
     assert g.queue_extension() == (0, 0)
     with pytest.raises(MtsError):
         g.set_queue_extension(64)
+
+
+@pytest.mark.parametrize("ring,ticks", [(1, 61), (7, 65), (15, 68)])
+def test_an_arrival_that_becomes_the_head_may_push_the_extension_out(ring, ticks):
+    # One instance takes every arrival (the others drain) and its queue grows
+    # through the length at which head, ring and full extension list all of it.
+    # There an arrival that becomes the head of line drops the extension, and
+    # the arrivals after it in the same batch follow requests that are no longer
+    # listed: they must not be taken for the next ones.  300 replicas stop a few
+    # requests around that length; then the others take arrivals again, and
+    # migrations and admissions empty the queue in its order.
+    R, I, S = 300, 65, 128
+    cfg = _cfg(I, S, 600, dict(kind="poisson", mean=2.0), R=R, K=2, out=60.0)
+    cfg["groups"][0]["tiers"] = dict(kind="explicit", probs=[0.05, 0.95])
+    g, o = Scheduler(cfg), oracle.Oracle(cfg)
+    g.queue_cache = ring
+    g.set_queue_extension(64)
+
+    def drain(flags):
+        g.set_draining(flags)
+        for r in range(R):
+            for i in range(I):
+                o.set_drain(r, i, bool(flags[r, i]))
+
+    flags = np.ones((R, I), np.uint8)
+    flags[:, 7] = 0
+    drain(flags)
+    g.step(ticks)
+    o.step(ticks)
+    waiting = ((g.export()["meta"].reshape(R, I, S)[:, 7] & 3) == 1).sum(1)
+    assert waiting.min() < 66 + ring < waiting.max()
+    drain(np.zeros((R, I), np.uint8))
+    g.step(40)
+    o.step(40)
+    _same(g, o, "ring %d" % ring)
+    assert g.stats()["raw"][86] == 0
