@@ -8,7 +8,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
-from workloads import preset  # noqa: E402
+from workloads import preset, with_extensions  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -17,6 +17,9 @@ if not torch.cuda.is_available():  # collected on CPU-only hosts, never run ther
 
 from paper_2608_16336_amd import Scheduler  # noqa: E402
 from paper_2608_16336_amd.mts import MtsError  # noqa: E402
+
+
+INFAAS = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
 
 
 def _cfg(I, S, M, arrival, R=2, K=10, interval=1, out=40.0, **kw):
@@ -89,3 +92,39 @@ def test_an_arrival_that_becomes_the_head_may_push_the_extension_out(ring, ticks
     o.step(40)
     _same(g, o, "ring %d" % ring)
     assert g.stats()["raw"][86] == 0
+
+
+BURSTS = dict(kind="gamma_poisson", mean=120.0, cv=3.0)
+LONG_BURSTS = dict(kind="gamma_poisson", mean=300.0, cv=4.0)
+
+
+@pytest.mark.parametrize("cfg,ring", [
+    # piles longer than a full extension behind the ring: appends that end
+    # there, insertions in front that push its last entry out
+    (_cfg(65, 256, 420, BURSTS), 1),
+    (_cfg(65, 256, 420, BURSTS), 15),
+    (_cfg(130, 1024, 900, BURSTS, out=120.0), 3),
+    (_cfg(256, 2048, 1500, LONG_BURSTS, interval=2, out=200.0), 11),
+    (_cfg(129, 512, 700, LONG_BURSTS, K=1), 3),
+    (_cfg(96, 192, 500, LONG_BURSTS, tier_blind=1), 7),
+    (_cfg(100, 256, 500, LONG_BURSTS, dispatch=INFAAS), 7),
+    (with_extensions(_cfg(70, 320, 500, LONG_BURSTS)), 7),
+], ids=["I65_ring1", "I65_ring15", "I130", "I256", "one_tier", "blind", "infaas", "ext"])
+@pytest.mark.parametrize("depth", [64, 100])
+def test_a_full_extension_never_changes_a_result(cfg, ring, depth):
+    g, o = Scheduler(cfg), oracle.Oracle(cfg)
+    g.queue_cache = ring
+    g.set_queue_extension(depth)
+    longest = 0
+    for ticks in (40, 40, 39, 41):
+        g.step(ticks)
+        o.step(ticks)
+        _same(g, o, "tick %d" % g.tick)
+        st = g.export()["meta"].reshape(-1, cfg["slots_per_instance"])
+        longest = max(longest, int(((st & 3) == 1).sum(1).max()))
+    assert g.stats()["raw"][86] == 0
+    # some queue was longer than head, ring and extension, and requests entered
+    # queues in the middle: preempted ones, or moved ones
+    raw = o.export()["stats"].reshape(2, -1).sum(0)
+    assert longest > 1 + ring + depth
+    assert raw[5:80:8].sum() > 0 and ("dispatch" in cfg or raw[80] > 0)
