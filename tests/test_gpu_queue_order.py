@@ -71,9 +71,10 @@ def test_kept_queue_order_never_changes_a_result(cfg, depths):
         for k in want:
             assert np.array_equal(got[k], want[k]), "I=%d depth %d field %s" % (cfg["n_instances"], depth, k)
         assert g.stats()["raw"][86] == 0
-    # the workload reaches what it is there for
-    st = want["stats"].reshape(2, -1)[:, :80].reshape(2, 10, 8)
-    assert st[:, :, 5].sum() > 0 or cfg["n_instances"] > 64
+    # the workload reaches what it is there for: preempted and (under Llumnix)
+    # moved requests enter the queues
+    raw = want["stats"].reshape(2, -1).sum(0)
+    assert raw[5:80:8].sum() > 0 and ("dispatch" in cfg or raw[80] > 0)
 
 
 def test_depth_is_kept_where_every_replica_stays_resident():
