@@ -258,8 +258,12 @@ typedef struct mts_state_view {
 
 typedef struct mts_ctx* mts_handle;
 
-/* Validate cfg and report the device bytes mts_create needs.
- * Returns MTS_EINVAL for a configuration outside the limits above. */
+/* Validate cfg and report the device bytes mts_create needs: the clusters'
+ * state and workspaces that only make steps faster -- up to 2 GiB of sampled
+ * arrivals, at most 1 GiB more than 1 KiB per instance of queue order (see
+ * mts_set_queue_cache; more than 64 instances only) and at most 8 GiB of
+ * launch images (each replica's per-instance summaries between two launches,
+ * kept for the first replicas where not all fit).  Returns MTS_EINVAL for a configuration outside the limits above. */
 int mts_state_bytes(const mts_cfg* cfg, size_t* bytes);
 
 /* Validate cfg, build the sampling and headroom tables (host, double
@@ -364,8 +368,8 @@ int mts_get_launch(mts_handle h, uint32_t* threads, uint32_t* blocks);
  * instances; else 0) entries that keeps the step kernel's blocks per compute
  * unit or leaves every replica resident at once with a block per compute unit
  * to spare.  For more than 64 instances the cache continues in the state
- * buffer (one entry per slot of the instance, or 64 where that would take more
- * than 8 GiB).  Results never depend on the depth (a performance setting, also
+ * buffer: one entry per slot of the instance, fewer (at least 64) where that
+ * would take more than 1 GiB in all.  Results never depend on the depth (a performance setting, also
  * a test hook).  mts_set_queue_cache takes effect at the next
  * mts_step; MTS_EINVAL for a depth above 15 or one whose LDS does not fit. */
 int mts_set_queue_cache(mts_handle h, uint32_t depth);

@@ -141,16 +141,16 @@ Layout make_layout(const mts_cfg& c, const Tables& T, uint32_t R, uint32_t chunk
     L.arr_rec = o;  o = up256(o + size_t(R) * chunk * cap * 8);
     L.wheel = o;    o = up256(o + size_t(R) * wsz * wcap * 4);
     // the queue cache's extension, for the kernels of more than 64 instances
-    L.qx = o;       o = up256(o + (I > 64 ? size_t(R) * I * qx_depth(R, I, S) * 16 : 0));
+    L.qx = o;       o = up256(o + (I > 64 ? qx_bytes(R, I, S) : 0));
     // the step kernel's LDS between launches, with room for the deepest queue
     // cache that mts_create picks
     {
         const size_t lds = lds_bytes(c.n_instances, c.slots_per_instance, c.block_tokens, wsz, c.dispatch_policy,
                                      I >= 128 ? 15 : 7, c.adapt_epoch != 0 || c.promote_period != 0, I > 64 ? 8 : 4);
-        const size_t n = lds / 16 + 1;
-        L.img_n = size_t(R) * n * 16 <= kImgBudget ? uint32_t(n) : 0;
+        L.img_n = uint32_t(lds / 16 + 1);
+        L.img_r = uint32_t(std::min<size_t>(R, kImgBudget / (size_t(L.img_n) * 16)));
     }
-    L.img = o;      o = up256(o + size_t(R) * L.img_n * 16);
+    L.img = o;      o = up256(o + size_t(L.img_r) * L.img_n * 16);
     L.total = o;
     return L;
 }
@@ -228,8 +228,9 @@ Params make_params(const mts_ctx* h)
     p.wheel = reinterpret_cast<uint32_t*>(d + L.wheel);
     p.qx = h->I > 64 ? reinterpret_cast<uint4*>(d + L.qx) : nullptr;
     p.qxd = h->qxd;
-    p.img = L.img_n ? reinterpret_cast<uint4*>(d + L.img) : nullptr;
+    p.img = reinterpret_cast<uint4*>(d + L.img);
     p.img_n = L.img_n;
+    p.img_r = L.img_r;
     return p;
 }
 

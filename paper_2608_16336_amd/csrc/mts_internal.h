@@ -67,24 +67,28 @@ struct Layout {
     size_t arr_cnt, arr_rec;                                            // [R][chunk], [R][chunk][cap]
     size_t wheel;                                                       // [R][wsz][wcap]
     size_t qx;                                                          // [R][I][qx_depth] uint4 (I > 64 only)
-    size_t img;                                                         // [R][img_n] uint4, LDS images (img_n 0: none)
-    uint32_t img_n;
+    size_t img;                                                         // [img_r][img_n] uint4, LDS images
+    uint32_t img_n, img_r;
     size_t total;
 };
 
 // The kernels for more than 64 instances keep, behind each instance's queue
 // cache in LDS, further waiting requests in order in HBM: as many as the
-// instance has slots, so that a burst's whole pile stays in order, unless
-// that takes more than kQxBudget bytes in all (then kQxLeast, one rescan's
-// selection).
+// instance has slots, so that a burst's whole pile stays in order, while that
+// takes at most kQxBudget bytes in all; beyond, what the budget gives every
+// instance, at least kQxLeast (one rescan's selection).  The bytes never fall
+// as R grows.
 constexpr uint32_t kQxLeast = 64;
-constexpr size_t kQxBudget = size_t(8) << 30;
-// LDS images of the replicas are kept between launches up to this many bytes
-constexpr size_t kImgBudget = size_t(8) << 30;
-inline uint32_t qx_depth(size_t R, size_t I, size_t S)
+constexpr size_t kQxBudget = size_t(1) << 30;
+inline size_t qx_bytes(size_t R, size_t I, size_t S)
 {
-    return R * I * S * 16 <= kQxBudget ? uint32_t(S) : kQxLeast;
+    const size_t all = R * I * S * 16, least = R * I * kQxLeast * 16;
+    return all <= kQxBudget ? all : least > kQxBudget ? least : kQxBudget;
 }
+inline uint32_t qx_depth(size_t R, size_t I, size_t S) { return uint32_t(qx_bytes(R, I, S) / (R * I * 16)); }
+// LDS images of the first replicas are kept between launches, up to this many
+// bytes (13.9 KB of a sweep replica's 361 KB, 177 KB of a wide one's 17 MB)
+constexpr size_t kImgBudget = size_t(8) << 30;
 
 // Everything a kernel launch needs, passed by value.
 struct Params {
@@ -135,8 +139,8 @@ struct Params {
     uint32_t* wheel;
     uint4* qx;                     // [R][I][qxd] queue cache extension (I > 64; null otherwise)
     uint32_t qxd;                  // its entries per instance
-    uint4* img;                    // [R][img_n] header and LDS of each replica after its last launch (or null)
-    uint32_t img_n, img_lds;       // uint4 per image; LDS bytes of this launch
+    uint4* img;                    // [img_r][img_n] header and LDS of the first replicas after their last launch
+    uint32_t img_n, img_r, img_lds;  // uint4 per image; replicas with one; LDS bytes of this launch
 };
 
 // LDS bytes of one wave (one replica) of the step kernel

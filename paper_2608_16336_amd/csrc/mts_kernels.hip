@@ -1914,7 +1914,7 @@ __device__ __forceinline__ uint32_t img_layout(const Params& P) { return P.qdept
 template <uint32_t NT>
 __device__ inline bool image_read(const Params& P, uint32_t r, uint32_t t, char* lds, uint32_t tid)
 {
-    if (!P.img) return false;
+    if (r >= P.img_r) return false;
     const uint4* m = P.img + size_t(r) * P.img_n;
     const uint4 h = *uniform_ptr(m);
     if (h.x != t || h.y != kImgMagic || h.z != (img_layout<NT>(P)) || h.w != P.img_lds) return false;
@@ -1935,7 +1935,7 @@ __device__ inline bool image_read(const Params& P, uint32_t r, uint32_t t, char*
 template <uint32_t NT>
 __device__ inline void image_write(const Params& P, uint32_t r, uint32_t t, const char* lds, uint32_t tid)
 {
-    if (!P.img) return;
+    if (r >= P.img_r) return;
     uint4* m = P.img + size_t(r) * P.img_n;
     const uint4* l = reinterpret_cast<const uint4*>(lds);
     const uint32_t n = P.img_lds / 16u;
@@ -3568,7 +3568,7 @@ __global__ void k_init(Params P)
     for (size_t j = t0; j < P.R; j += stride) {
         P.next_seq[j] = 0;
         P.digest[j] = 0;
-        if (P.img) P.img[j * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
+        if (j < P.img_r) P.img[j * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
     }
     if (P.hsnap)
         for (size_t j = t0; j < size_t(P.R) * 2 * kTiers; j += stride) P.hsnap[j] = 0;
@@ -3580,9 +3580,8 @@ __global__ void k_init(Params P)
 // ---------------------------------------------------------------------------
 __global__ void k_shift_clock(Params P, uint32_t delta)
 {
-    if (P.img)
-        for (size_t j = size_t(blockIdx.x) * blockDim.x + threadIdx.x; j < P.R; j += size_t(gridDim.x) * blockDim.x)
-            P.img[j * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
+    for (size_t j = size_t(blockIdx.x) * blockDim.x + threadIdx.x; j < P.img_r; j += size_t(gridDim.x) * blockDim.x)
+        P.img[j * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
     const size_t nslots = size_t(P.R) * P.I * P.S;
     const size_t stride = size_t(gridDim.x) * blockDim.x;
     for (size_t s = size_t(blockIdx.x) * blockDim.x + threadIdx.x; s < nslots; s += stride) {
@@ -3717,7 +3716,7 @@ int launch_step(const Params& p, unsigned long long t0, uint32_t nt, uint32_t bl
     const size_t lds = step_lds(p);
     Params q = p;
     q.img_lds = uint32_t(lds);
-    if (lds + 16 > size_t(p.img_n) * 16) q.img = nullptr;  // a depth the image has no room for
+    if (lds + 16 > size_t(p.img_n) * 16) q.img_r = 0;  // a depth the image has no room for
     void* args[] = {&q, &t0, &nt};
     const hipError_t rc = hipLaunchKernel(step_fn(p), dim3(blocks), dim3(uint32_t(step_threads(p))), args, lds, stream);
     if (rc != hipSuccess) { (void)hipGetLastError(); return int(rc); }
@@ -3817,12 +3816,12 @@ int launch_unpack(const Params& p, size_t f0, uint32_t n, uint32_t tick, const u
 __global__ void k_void_images(Params P, uint32_t r0, uint32_t nr)
 {
     const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < nr) P.img[size_t(r0 + j) * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
+    if (j < nr && r0 + j < P.img_r) P.img[size_t(r0 + j) * P.img_n] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 int launch_void_images(const Params& p, uint32_t r0, uint32_t nr, hipStream_t stream)
 {
-    if (!p.img || nr == 0) return 0;
+    if (r0 >= p.img_r || nr == 0) return 0;
     hipLaunchKernelGGL(k_void_images, dim3((nr + 255) / 256), dim3(256), 0, stream, p, r0, nr);
     return int(hipGetLastError());
 }

@@ -142,3 +142,52 @@ def test_checkpoint_larger_than_one_slice_of_the_staging():
     for o in orc:
         o.step(5)
     _same(g, orc, "after the refused import")
+
+
+def test_replicas_beyond_the_images_budget_start_from_their_slots():
+    # 80,000 replicas of wide clusters with few slots and short outputs, 32 GB:
+    # their images would take 9.6 GB, more than the budget of 8 GiB, so the last
+    # ones have none; the others' steps resume from theirs
+    R = 80000
+    c = _cfg("wide", n_instances=129, slots_per_instance=64, kv_blocks=40, block_tokens=64, headroom_base=5.0, mig_max_pairs=64,
+             arrival=dict(kind="gamma_poisson", mean=30.0, cv=2.0), prompt=dict(kind="uniform_int", lo=64, hi=1600),
+             output=dict(kind="geometric", mean=1.5), groups=[dict(n_replicas=R, K=4, tiers=dict(kind="uniform"))])
+    g = Scheduler(c)
+    assert g.nbytes < 48 << 30
+    at = (0, 40000, 71000, 72000, 79998, R - 1)
+    orc = [oracle.Oracle(c, r, 1) for r in at]
+    for n in (3, 1, 5, 2):
+        g.step(n)
+        for o in orc:
+            o.step(n)
+        for r, o in zip(at, orc):
+            a, b = g.export(r, 1), o.export()
+            for k in b:
+                assert np.array_equal(a[k], b[k]), "replica %d field %s" % (r, k)
+    # replicas without an image take a state as well
+    saved = g.export(0, 1)
+    g.import_state(saved, R - 1, 1)
+    orc[-1].import_state(saved)
+    g.step(4)
+    for r, o in zip(at, orc):
+        o.step(4)
+        a, b = g.export(r, 1), o.export()
+        for k in b:
+            assert np.array_equal(a[k], b[k]), "replica %d field %s after the import" % (r, k)
+    assert g.stats()["raw"][86] == 0
+    g.close()
+    torch.cuda.empty_cache()
+
+
+def test_a_cache_deeper_than_the_images_have_room_for():
+    # up to 64 instances the images have room for a ring of 7
+    cfg = _cfg("enterprise", load=1.5)
+    g = Scheduler(cfg)
+    orc = [oracle.Oracle(cfg, r, 1) for r in range(g.R)]
+    for depth, n in ((7, 30), (15, 20), (15, 3), (7, 2), (7, 3), (15, 1), (7, 4)):
+        g.queue_cache = depth
+        g.step(n)
+        for o in orc:
+            o.step(n)
+        _same(g, orc, "depth %d" % depth)
+    assert g.stats()["raw"][86] == 0

@@ -109,3 +109,19 @@ def test_adaptive_limits_accept_what_the_oracle_accepts():
                            margin=256, slo=[1, 1 << 20]), promotion=dict(period=2**32 - 1, age=[2**32 - 1] * 10))
     assert mts.mts_state_bytes(c) > 0
     oracle.Oracle(c).close()
+
+
+def test_state_bytes_grow_with_the_replicas_and_keep_the_workspaces_bounded():
+    c = preset("wide")
+    last = 0
+    for R in range(100, 6001, 100):
+        c["groups"][0]["n_replicas"] = R
+        b = mts.mts_state_bytes(c)
+        assert b > last, R
+        last = b
+        # the slots, the finish wheel (512 buckets of 2 (1 + cv) mean + 24
+        # entries, up to 16 more), histograms and counters; then the workspaces:
+        # sampled arrivals (a tick of 1000 replicas is 40 MB), the queue order
+        # (1 GiB, or 1 KiB per instance if that is more) and the launch images
+        state = R * (256 * 2048 * 16 + 512 * 4 * (2 * 200 * 4 + 24 + 16) + 2 * 10 * 240 * 4 + 64 * 256)
+        assert b <= state + (2 << 30) + max(1 << 30, R * 256 * 1024) + min(8 << 30, R * 180000) + (1 << 20), R
