@@ -90,6 +90,40 @@ inline uint32_t qx_depth(size_t R, size_t I, size_t S) { return uint32_t(qx_byte
 // bytes (13.9 KB of a sweep replica's 361 KB, 177 KB of a wide one's 17 MB)
 constexpr size_t kImgBudget = size_t(8) << 30;
 
+// Slot words (the step kernel's source lists their fields) and the canonical
+// len | rem << 16 and meta of mts_state_view, at tick t, the next to run.
+__host__ __device__ inline uint32_t slot_lr(uint32_t w, uint32_t t)
+{
+    const uint32_t st = w >> 30, lo = w & 0xFFFFu, mid = (w >> 16) & 0x3FFFu;
+    if (st == kWaiting) return lo | (mid << 16);
+    if (st == kRunning) {
+        const uint32_t rem = (mid - t + 1u) & 0x3FFFu;
+        return (lo - rem) | (rem << 16);
+    }
+    return 0;
+}
+// an empty slot or an inbound reservation: seq and arrival tick are zero in the
+// canonical state, whatever the record holds (an empty slot's meta too)
+__host__ __device__ inline bool slot_gone(uint32_t w) { return w == 0 || w >> 30 == kInbound; }
+__host__ __device__ inline uint32_t slot_word(uint32_t m, uint32_t lr, uint32_t t)
+{
+    const uint32_t st = m & 3u, len = lr & 0xFFFFu, rem = lr >> 16;
+    if (st == kInbound) return 3u << 30;
+    if (st == kWaiting) return (1u << 30) | (rem << 16) | len;
+    if (st == kRunning) return (2u << 30) | (((t - 1u + rem) & 0x3FFFu) << 16) | (len + rem);
+    return 0;
+}
+// whether a canonical slot keeps the limits that hold every index the step
+// kernel derives from it in range (K: the replica's tiers)
+__host__ __device__ inline bool slot_ok(uint32_t m, uint32_t lr, uint32_t K)
+{
+    const uint32_t st = m & 3u, len = lr & 0xFFFFu, rem = lr >> 16;
+    if (st == kEmpty) return m == 0;
+    if (st == kInbound) return true;
+    if (((m >> 2) & 15u) >= K || len == 0 || rem == 0 || rem > kMaxOutput) return false;
+    return st != kRunning || len + rem <= 65535u;
+}
+
 // Everything a kernel launch needs, passed by value.
 struct Params {
     uint32_t R, I, S, W;           // W = S / 64 occupancy words per instance

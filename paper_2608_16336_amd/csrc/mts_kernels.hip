@@ -3603,17 +3603,6 @@ __device__ inline unsigned long long mix64(unsigned long long z)
     return z ^ (z >> 31);
 }
 
-// canonical len | rem << 16 of a slot word at tick `tick`
-__device__ inline uint32_t canonical_lr(uint32_t v, uint32_t tick)
-{
-    if (wst(v) == 1u) return wlo(v) | (wmid(v) << 16);
-    if (wst(v) == 2u) {
-        const uint32_t rem = (wmid(v) - tick + 1u) & kFin;
-        return (wlo(v) - rem) | (rem << 16);
-    }
-    return 0;
-}
-
 __global__ __launch_bounds__(256) void k_digest(Params P, uint32_t r0, uint32_t tick)
 {
     __shared__ unsigned long long part[4];
@@ -3630,7 +3619,7 @@ __global__ __launch_bounds__(256) void k_digest(Params P, uint32_t r0, uint32_t 
         if (hw == 0u) continue;
         const bool inb = wst(hw) == kInbound;
         const unsigned m = rec.y & 0xFFu;
-        const unsigned long long a = static_cast<unsigned long long>(canonical_lr(hw, tick)) |
+        const unsigned long long a = static_cast<unsigned long long>(slot_lr(hw, tick)) |
                                      (static_cast<unsigned long long>(inb ? 0u : rec.z) << 32);
         const unsigned long long b = static_cast<unsigned long long>(inb ? 0u : rec.w) |
                                      (static_cast<unsigned long long>(m) << 32);
@@ -3741,32 +3730,24 @@ __global__ __launch_bounds__(256) void k_pack(Params P, size_t f0, uint32_t n, u
     for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
         const uint4 rec = P.slot[f0 + j];
         const uint32_t w = rec.x;
-        // an empty slot's other fields and an inbound reservation's seq and
-        // arrival tick are zero in the canonical state
-        const bool gone = w == 0 || wst(w) == kInbound;
-        if (lr) lr[j] = canonical_lr(w, tick);
+        const bool gone = slot_gone(w);
+        if (lr) lr[j] = slot_lr(w, tick);
         if (meta) meta[j] = w == 0 ? 0 : uint8_t(rec.y);
         if (seq) seq[j] = gone ? 0 : rec.z;
         if (tarr) tarr[j] = gone ? 0 : rec.w;
     }
 }
 
-// sets *bad when a slot breaks a limit that keeps every index the step kernel
-// derives from the state in range
+// sets *bad when a slot is not acceptable (slot_ok)
 __global__ __launch_bounds__(256) void k_check_slots(Params P, size_t f0, uint32_t n, const uint8_t* meta, const uint32_t* lr,
                                                      uint32_t* bad)
 {
     const uint32_t IS = P.I * P.S, stride = gridDim.x * blockDim.x;
     bool b = false;
     for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
-        const uint32_t m = meta[j], st = m & 3u, len = lr[j] & 0xFFFFu, rem = lr[j] >> 16;
-        if (st == kEmpty) {
-            b = b || m != 0;
-        } else if (st != kInbound) {
-            const uint32_t K = P.group_K32[P.group_of[(f0 + j) / IS]];
-            b = b || ((m >> 2) & 15u) >= K || len == 0 || rem == 0 || rem > kMaxOutput;
-            if (st == kRunning) b = b || len + rem > 65535u;
-        }
+        const uint32_t m = meta[j];
+        const uint32_t K = m ? P.group_K32[P.group_of[(f0 + j) / IS]] : 0u;
+        b = b || !slot_ok(m, lr[j], K);
     }
     if (b) atomicOr(bad, 1u);
 }
@@ -3777,12 +3758,8 @@ __global__ __launch_bounds__(256) void k_unpack(Params P, size_t f0, uint32_t n,
 {
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
-        const uint32_t m = meta[j], st = m & 3u, len = lr[j] & 0xFFFFu, rem = lr[j] >> 16;
-        uint32_t w = 0;
-        if (st == kInbound) w = kInbW;
-        else if (st == kWaiting) w = kWaitW | (rem << 16) | len;
-        else if (st == kRunning) w = kRunW | (((tick - 1u + rem) & kFin) << 16) | (len + rem);
-        P.slot[f0 + j] = make_uint4(w, m, seq[j], tarr[j]);
+        const uint32_t m = meta[j];
+        P.slot[f0 + j] = make_uint4(slot_word(m, lr[j], tick), m, seq[j], tarr[j]);
     }
 }
 

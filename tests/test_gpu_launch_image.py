@@ -99,20 +99,22 @@ def test_launches_resume_through_every_change_of_state(cfg):
     assert g.stats()["raw"][86] == 0
 
 
-def test_checkpoint_larger_than_one_slice_of_the_staging():
-    # few sampled arrivals leave a staging area far smaller than the slots, so
-    # the canonical arrays pass in many slices; the last one is partial
-    c = _cfg("tiny", n_instances=61, slots_per_instance=576, mig_max_pairs=30)
+@pytest.mark.parametrize("I,S", [(4, 64), (61, 576), (61, 1088), (201, 2048)])
+def test_checkpoint_larger_than_one_slice_of_the_staging(I, S):
+    # few sampled arrivals leave a staging area smaller than the slots, so the
+    # canonical arrays of the largest state pass in four slices, the last one
+    # partial; the smallest is converted by the host
+    c = _cfg("tiny", n_instances=I, slots_per_instance=S, mig_max_pairs=I // 2)
     c["arrival"]["mean"] = 0.05
     c["groups"] = [dict(c["groups"][0], n_replicas=2)]
     g = Scheduler(c)
     orc = [oracle.Oracle(c, r, 1) for r in range(2)]
     rng = np.random.RandomState(5)
     st = g.export()
-    N = 61 * 576
+    N = I * S
     # requests all over the slots (waiting, lengths and tiers at random)
     for r in range(2):
-        at = rng.choice(N, 3000, replace=False) + r * N
+        at = rng.choice(N, min(N // 2, 3000), replace=False) + r * N
         at[-1] = (r + 1) * N - 1
         at = np.unique(at)
         st["meta"][at] = 1 | (rng.randint(0, 2, len(at)) << 2)
@@ -191,3 +193,26 @@ def test_a_cache_deeper_than_the_images_have_room_for():
             o.step(n)
         _same(g, orc, "depth %d" % depth)
     assert g.stats()["raw"][86] == 0
+
+
+@pytest.mark.parametrize("replicas", [1, 40])
+def test_a_state_loaded_on_one_stream_is_stepped_on_another(replicas):
+    # small states are converted by the host, larger ones on the device: both
+    # loads are complete when the call returns, whatever stream steps next
+    c = _cfg("enterprise", load=1.3)
+    c["groups"][0]["n_replicas"] = replicas
+    g, o = Scheduler(c), oracle.Oracle(c, 0, 1)
+    g.step(30)
+    o.step(30)
+    saved = g.export()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for k in range(6):
+        g.step(8, stream=streams[k % 3])
+        g.import_state(saved)
+        g.tick = 30
+        g.step(4, stream=streams[(k + 1) % 3])
+        torch.cuda.synchronize()
+    o.step(4)
+    a, b = g.export(0, 1), o.export()
+    for f in b:
+        assert np.array_equal(a[f], b[f]), f
