@@ -263,7 +263,8 @@ typedef struct mts_ctx* mts_handle;
  * arrivals, at most 1 GiB more than 1 KiB per instance of queue order (see
  * mts_set_queue_cache; more than 64 instances only) and at most 8 GiB of
  * launch images (each replica's per-instance summaries between two launches,
- * kept for the first replicas where not all fit).  Returns MTS_EINVAL for a configuration outside the limits above. */
+ * kept for the first replicas where not all fit).  Returns MTS_EINVAL for a
+ * configuration outside the limits above. */
 int mts_state_bytes(const mts_cfg* cfg, size_t* bytes);
 
 /* Validate cfg, build the sampling and headroom tables (host, double
@@ -347,12 +348,15 @@ uint64_t mts_tick(mts_handle h);
  * the tick does not fit the 32-bit tick fields. */
 int mts_set_tick(mts_handle h, uint64_t tick);
 
-/* Force the launch shape of the step kernel: threads per block (0, or the
- * block size mts_get_launch reports: one 64-lane wave per replica -- four for
- * overloaded clusters of 16 to 64 instances that leave the device room, where
- * 64 asks for one -- and eight for 128 or more instances) and number of blocks (0:
- * automatic, else at most the replica count; each block runs replicas r,
- * r + blocks, ...). */
+/* Force the launch shape of the step kernel: threads per block and number of
+ * blocks (0: automatic, else at most the replica count; each block runs
+ * replicas r, r + blocks, ...).  A block is one replica's waves: 64 threads, or
+ * 256 for overloaded clusters of 16 to 64 instances that leave the device room
+ * (a choice of mts_create), or 512 for more than 64 instances.  threads is 0
+ * (automatic) or the size that mts_create chose; where that is 256, 64 is taken
+ * as well and steps with one wave per replica until the next mts_set_launch.
+ * Results never depend on the shape: callers who only set the number of blocks
+ * pass 0 threads. */
 int mts_set_launch(mts_handle h, uint32_t threads, uint32_t blocks);
 
 /* Launch shape mts_step uses now: *threads = the block size (64 or 256, or 512
@@ -369,9 +373,10 @@ int mts_get_launch(mts_handle h, uint32_t* threads, uint32_t* blocks);
  * unit or leaves every replica resident at once with a block per compute unit
  * to spare.  For more than 64 instances the cache continues in the state
  * buffer: one entry per slot of the instance, fewer (at least 64) where that
- * would take more than 1 GiB in all.  Results never depend on the depth (a performance setting, also
- * a test hook).  mts_set_queue_cache takes effect at the next
- * mts_step; MTS_EINVAL for a depth above 15 or one whose LDS does not fit. */
+ * would take more than 1 GiB in all.  Results never depend on the depth (a
+ * performance setting, also a test hook).  mts_set_queue_cache takes effect at
+ * the next mts_step; MTS_EINVAL for a depth above 15 or one whose LDS does not
+ * fit. */
 int mts_set_queue_cache(mts_handle h, uint32_t depth);
 int mts_get_queue_cache(mts_handle h, uint32_t* depth);
 

@@ -26,7 +26,7 @@ struct mts_ctx {
     uint32_t chunk = 0;                // ticks per arrival batch
     uint32_t wsz = 0, wcap = 0;        // finish wheel: buckets, entries per bucket
     uint32_t wcap_max = 0;             // entries per bucket the layout reserves
-    uint32_t blocks = 0;               // step-kernel blocks (one wave each); 0 = automatic
+    uint32_t blocks = 0;               // step-kernel blocks; 0 = automatic
     uint32_t qdepth = 0;               // queue-cache entries per instance (chosen at create)
     uint32_t qxd = 0;                  // entries of its extension in use (more than 64 instances)
     uint32_t qxd_max = 0;              // and those the layout reserves
@@ -463,8 +463,8 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
 int mts_set_launch(mts_handle h, uint32_t threads, uint32_t blocks)
 {
     if (!h) return MTS_EINVAL;
-    // the block is the replica's waves: its size is fixed by the instance count
-    // (64 asks for one wave where create chose four)
+    // the block is the replica's waves: its size is fixed at create (64 asks for
+    // one wave where create chose four)
     Params p = make_params(h);
     const bool one = h->four_auto && threads == 64;
     p.nw = h->four_auto && h->qdepth ? 4 : p.nw;
@@ -928,8 +928,8 @@ int mts_set_tick(mts_handle h, uint64_t tick)
 int mts_set_wheel_cap(mts_handle h, uint32_t cap)
 {
     if (!h || cap == 0 || cap > h->wcap_max) return MTS_EINVAL;
-    // every step-kernel launch files the running requests into the wheel
-    // afresh, so the capacity can change between steps
+    // the capacity is part of the launch image's key: the next launch does not
+    // resume from the image but files every running request afresh
     if (hipStreamSynchronize(h->last) != hipSuccess) return MTS_EDEVICE;
     h->wcap = cap;
     return MTS_OK;

@@ -140,7 +140,7 @@ struct Params {
     long long alpha256, beta, gamma256;  // INFaaS weights (alpha and gamma times 256)
     uint32_t pen_over, pen_intf;   // INFaaS state penalties in ticks
     uint32_t qdepth;               // queue-cache entries behind each head of line (LDS)
-    uint32_t nw;                   // waves per replica: 8 for 128+ instances, else 1 or 4 (4 with a queue cache only)
+    uint32_t nw;                   // waves per replica: 8 for more than 64 instances, else 1 or 4 (4 with a queue cache only)
     uint32_t blind;                // 1: tiers order nothing (tier-blind scheduling)
     uint32_t zero_lowest;          // 1: the lowest tier carries no headroom
     // adaptive headroom (epoch 0: static) and promotion (period 0: none)
@@ -177,7 +177,7 @@ struct Params {
     uint32_t img_n, img_r, img_lds;  // uint4 per image; replicas with one; LDS bytes of this launch
 };
 
-// LDS bytes of one wave (one replica) of the step kernel
+// LDS bytes of one replica (one workgroup of nw waves) of the step kernel
 // (ext: the adaptive-headroom or promotion state is kept in LDS)
 size_t lds_bytes(uint32_t I, uint32_t S, uint32_t RB, uint32_t wsz, uint32_t policy, uint32_t qdepth, bool ext, uint32_t nw);
 
@@ -186,7 +186,7 @@ int launch_init(const Params& p, hipStream_t stream);
 int launch_arrivals(const Params& p, unsigned long long t0, uint32_t nt, hipStream_t stream);
 int launch_step(const Params& p, unsigned long long t0, uint32_t nt, uint32_t blocks, hipStream_t stream);
 // resident step-kernel blocks per CU (0 if the runtime cannot tell); threads
-// per block (one wave per replica, or eight for 128 or more instances)
+// per block (p.nw waves per replica)
 int step_blocks_per_cu(const Params& p);
 int step_threads(const Params& p);
 int launch_digest(const Params& p, uint32_t r0, uint32_t nr, uint32_t tick, hipStream_t stream);

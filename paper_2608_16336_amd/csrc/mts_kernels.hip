@@ -2,15 +2,16 @@
 //
 //   k_arrivals  (mts_arrivals.hip) samples every arrival of a chunk of ticks
 //               and sorts each tick's arrivals by tier.
-//   k_step      the scheduling tick, one wave per replica for a whole chunk
-//               of ticks: per-instance summaries live in LDS, per-instance
+//   k_step      the scheduling tick, a workgroup of one, four or eight waves
+//               per replica for a whole chunk of ticks: per-instance summaries live in LDS, per-instance
 //               O(1) work is lane-parallel (lane i <-> instance i), slot
 //               state lives in HBM and is touched only by events.
 //   k_init      empty clusters; k_digest the canonical state digest.
 //
-// Slot record (uint4 per slot): x = slot word, y = meta (a running request's
-// place in its finish bucket from bit 8 on), z = seq, w = arrival tick, so that an event reads or writes one 16-byte record.  Slot word (u32,
-// bits 31..30 = status):
+// Slot record (uint4 per slot): x = slot word, y = meta (in the kernels with a
+// queue cache with a running request's place in its finish bucket from bit 8
+// on), z = seq, w = arrival tick, so that an event reads or writes one 16-byte
+// record.  Slot word (u32, bits 31..30 = status):
 //   waiting   01 | rem (14 bits) | len (16 bits)
 //   running   10 | fin mod 2^14  | final length (16 bits)
 //   inbound   11 | 0 (with meta; seq and arrival tick keep whatever the slot
@@ -49,14 +50,14 @@ __device__ __forceinline__ uint32_t wlo(uint32_t v) { return v & 0xFFFFu; }
 __device__ __forceinline__ uint32_t wmid(uint32_t v) { return (v >> 16) & kFin; }
 
 // ---------------------------------------------------------------------------
-// LDS of one wave (one replica)
+// LDS of one replica
 // ---------------------------------------------------------------------------
 constexpr int kInts = 18;
 // placements of the previous tick's dispatch kept in LDS (at most one wave's worth)
 constexpr int kLast = 64;
 // requests preempted in the current tick, listed for the prefetched finish visit
 constexpr int kVic = 16;
-// kernels for 128+ instances: up to this many pairs are picked one by one
+// kernels for more than 64 instances: up to this many pairs are picked one by one
 // (about 450 cycles each; the whole order takes 11K)
 constexpr int kPickPairs = 16;
 // Section 6.5 extensions: words of the device table (u32; the addresses of
@@ -69,10 +70,10 @@ struct LdsLayout {
     uint32_t stats, occ, holk, fd, ht, ints, res, tcnt, mig, last, vic, wc, wov, inf, qt, qn, xn, ext, blk, rsel, total;
 };
 
-// Waves per replica (NW): eight in the kernels for 128 or more instances (the
-// per-instance phases are spread over the waves, the serial ones stay on wave
-// 0); one or, for overloaded clusters that leave the chip room, four in the
-// others.
+// Waves per replica (NW): eight in the kernels for more than 64 instances
+// (IM 128 and 256; the per-instance phases are spread over the waves, the
+// serial ones stay on wave 0); one or, for overloaded clusters that leave the
+// chip room, four in the others.
 
 __host__ __device__ inline uint32_t al8(uint32_t x) { return (x + 7u) & ~7u; }
 
@@ -113,7 +114,7 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     o = (o + 15u) & ~15u;
     L.qt = o;    o += IM * qdepth * 16;
     L.qn = o;    o += qdepth ? IM * 8 : 0;
-    // kernels for 128+ instances: per instance the queue cache extension's head << 16 | count
+    // kernels for more than 64 instances: per instance the queue cache extension's head << 16 | count
     L.xn = o;    o += wide ? IM * 4 : 0;
     // adaptive headroom / promotion: the ticks left to the next promotion
     // pass and headroom update, and per instance a lower bound on the
@@ -125,7 +126,7 @@ __host__ __device__ inline LdsLayout lds_layout(uint32_t IM, uint32_t I, uint32_
     // abort flag, the work lists' lengths and next entries)
     o = al8(o);
     L.blk = o;   o += nw > 1 ? 40 : 0;
-    // kernels for 128+ instances: per wave 64 (key, slot | demand) pairs, the rescan's
+    // kernels for more than 64 instances: per wave 64 (key, slot | demand) pairs, the rescan's
     // selected requests before they are ranked (the dispatch's deferred
     // bursts and the pairing's sorted blocks of 64 (key, index) pairs use the
     // same bytes later in the tick)
@@ -165,7 +166,7 @@ struct Ctx {
     uint4* qt;                 // [I][td] a ring: entry k at (qh + k) mod td
     int* qn;                   // [I] cached entries
     int* qh;                   // [I] ring position of the first entry
-    // kernels for 128+ instances (null otherwise): behind the ring, further
+    // kernels for more than 64 instances (null otherwise): behind the ring, further
     // waiting requests of the instance in order, a ring of xd entries in HBM
     int* xn;                   // [I] first entry << 16 | count
     uint4* qx;                 // [I][xd] this replica's extensions
@@ -598,7 +599,7 @@ __device__ __forceinline__ void set_hol(const Ctx& C, int i, int slot, unsigned 
 }
 
 // Queue cache.  Invariant: the head of line, the qn[i] cached entries and
-// (kernels for 128+ instances) the extension's entries are the smallest
+// (kernels for more than 64 instances) the extension's entries are the smallest
 // (tier, seq) keys among instance i's waiting requests, in order.  The functions below are per lane (lane-private
 // instance i) and keep it: popping the head promotes the first cached entry
 // (or leaves the head unknown, to be found by a rescan), a new waiting
@@ -1410,7 +1411,7 @@ __device__ inline int rank_select(const Ctx& C, uint32_t (&k)[MK], uint32_t (&sd
 // and the cache behind it).  A second read fetches the fields of the requests
 // taken, and the longest fitting prefix is admitted at once (admit_ranked).
 // The minima are taken on 32-bit keys when the candidates' seqs allow
-// (rank_extract); with SEL (the kernels for 128+ instances) the same prefix
+// (rank_extract); with SEL (the kernels for more than 64 instances) the same prefix
 // is found by selection (rank_select), and when every request taken fits the
 // candidates left up to the exhaustion bound are taken next without reading
 // the slots again.  GR chunks of 64 slots are read per memory round trip.
@@ -1576,7 +1577,7 @@ template <bool XT>
 __device__ inline void admit_cached(const Ctx& C, int i, uint32_t t, int lane)
 {
     const int n = C.qn[i];
-    // (XT, the kernels for 128+ instances) the extension follows the ring
+    // (XT, the kernels for more than 64 instances) the extension follows the ring
     const int xv = XT ? C.xn[i] : 0, xc = xv & 0xFFFF, xh = xv >> 16;
     const int w = min(64, n + xc + 1);
     unsigned long long key = kNone;
@@ -1789,8 +1790,9 @@ __device__ inline void admit_all(const Ctx& C, int i, uint32_t t, int lane)
 // such tick is at most t (requests start to wait at the current tick or
 // keep an older one): when t - lb is below the smallest quota no request can
 // be old enough and the instance is not read.  lb = 0 means unknown (a
-// launch starts so, as does an instance holding a request that arrived
-// after t, possible only after the clock was moved back).
+// launch that reads the slots starts so, as does an instance holding a request
+// that arrived after t, possible only after the clock was moved back; a launch
+// that resumes from the replica's image keeps lb).
 template <int NW>
 __device__ inline void promote_waiting(const Ctx& C, const Params& P, uint32_t t, int lane, int wid)
 {
@@ -2239,7 +2241,11 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
         if (NW > 1 && tid == 0) { *C.gln = 0; *C.glnext = 0; }
         if (wid == 0) headroom_table(C, hq, lane);
         unsigned next_seq = P.next_seq[r];
-        uint32_t run_acc = 0, wait_acc = 0;  // per lane, at most 1024 ticks x 4 x 2048
+        // slot-ticks per lane of a chunk of at most 1024 ticks: a tick adds at most
+        // OPL x 2048 to run_acc, and to wait_acc as many after admission, IPL x 2048
+        // placed by the dispatch and on lane 0 kMaxRuns bursts' rests: below 2^25
+        static_assert(OPL == 1 && IPL <= 4 && kMaxRuns <= 8, "1024 ticks of slot counts fit 32 bits");
+        uint32_t run_acc = 0, wait_acc = 0;
         const unsigned long long* recs = P.arr_rec + size_t(r) * P.chunk * P.arr_cap;
         const uint32_t* cnts = P.arr_cnt + size_t(r) * P.chunk;
         block_sync<NW>();
@@ -3188,7 +3194,7 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
             mig_left = mig_tick ? P.mig_interval - 1u : mig_left - 1u;
             // pairing in three parts: which instances can pair and their keys
             // (wave 0), their order (wave 0 by counting ranks; in the kernels for
-            // 128+ instances only as many of the lowest and highest as can pair,
+            // more than 64 instances only as many of the lowest and highest as can pair,
             // or the whole order by every thread), the pairs (wave 0, the staged
             // copies' candidates by all waves)
             npairs = 0;
@@ -3503,8 +3509,8 @@ __global__ __launch_bounds__(64 * NW, IM <= 64 ? 4 : 2) void k_step(Params P, un
 
 // The instantiations of the step kernel are compiled in twelve translation
 // units (this file with MTS_STEP_PART = 0..11): bit 0 the INFaaS policy, bit 1
-// the Section 6.5 extensions; 0..3 the one-wave kernels, 4..7 those for 128 or
-// more instances, 8..11 the four-wave kernels (always with a queue cache).
+// the Section 6.5 extensions; 0..3 the one-wave kernels, 4..7 those for more
+// than 64 instances, 8..11 the four-wave kernels (always with a queue cache).
 // Each gives the kernel for IM instances with (qc) or without a queue cache.
 #ifdef MTS_STEP_PART
 #define MTS_STEP_FN2(p) step_part_##p
