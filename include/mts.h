@@ -350,11 +350,11 @@ int mts_set_tick(mts_handle h, uint64_t tick);
 
 /* Force the launch shape of the step kernel: threads per block and number of
  * blocks (0: automatic, else at most the replica count; each block runs
- * replicas r, r + blocks, ...).  A block is one replica's waves: 64 threads, or
- * 256 for overloaded clusters of 16 to 64 instances that leave the device room
- * (a choice of mts_create), or 512 for more than 64 instances.  threads is 0
- * (automatic) or the size that mts_create chose; where that is 256, 64 is taken
- * as well and steps with one wave per replica until the next mts_set_launch.
+ * replicas r, r + blocks, ...).  A block is one replica's waves: 512 threads
+ * for more than 64 instances, else 64; overloaded clusters of 16 to 64
+ * instances that leave the device room can also run on 256, and do where
+ * mts_create expects them to preempt often.  threads is 0 (what mts_create
+ * chose) or a size the handle can run on, kept until the next mts_set_launch.
  * Results never depend on the shape: callers who only set the number of blocks
  * pass 0 threads. */
 int mts_set_launch(mts_handle h, uint32_t threads, uint32_t blocks);

@@ -30,8 +30,9 @@ struct mts_ctx {
     uint32_t qdepth = 0;               // queue-cache entries per instance (chosen at create)
     uint32_t qxd = 0;                  // entries of its extension in use (more than 64 instances)
     uint32_t qxd_max = 0;              // and those the layout reserves
-    bool four_auto = false;            // four waves per replica chosen at create
-    bool four_waves = false;           // and in use (mts_set_launch can ask for one)
+    bool four_ok = false;              // four waves per replica allowed,
+    bool four_auto = false;            // chosen at create
+    bool four_waves = false;           // and in use (mts_set_launch can ask for one or four)
     int device = 0;
     hipStream_t last = nullptr;
     std::vector<uint16_t> group_of;
@@ -266,13 +267,28 @@ double table_mean(const Table& t)
     return m;
 }
 
+// KV blocks that a request holds on average while it runs
+double mean_blocks(const mts_ctx& x)
+{
+    const double len = table_mean(x.tables.prompt) + 0.5 * table_mean(x.tables.output);
+    return len / x.cfg.block_tokens + 0.5;
+}
+
 // KV blocks that the arrivals would hold on average, were all of them admitted
 // at once, over the cluster's blocks: above 1 the queues grow without end
 double expected_load(const mts_ctx& x)
 {
-    const double out = table_mean(x.tables.output), len = table_mean(x.tables.prompt) + 0.5 * out;
-    const double blocks = len / x.cfg.block_tokens + 0.5;
-    return x.cfg.arrival_mean * out * blocks / (double(x.cfg.kv_blocks) * x.I);
+    return x.cfg.arrival_mean * table_mean(x.tables.output) * mean_blocks(x) / (double(x.cfg.kv_blocks) * x.I);
+}
+
+// Requests that a full cluster would preempt a tick if nothing but preemption
+// gave its running requests their new blocks: each of them needs one every
+// block_tokens ticks, a victim frees mean_blocks.  (Overloaded clusters preempt
+// about half to all of this.)
+double expected_victims(const mts_ctx& x)
+{
+    const double b = mean_blocks(x);
+    return double(x.cfg.kv_blocks) / b * x.I / x.cfg.block_tokens / b;
 }
 
 int prepare(const mts_cfg* cfg, mts_ctx& x)
@@ -368,17 +384,28 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
             const int nb = step_blocks_per_cu(p);
             if (nb >= base || (nb > 1 && uint64_t(nb - 1) * uint64_t(cus) >= x->R)) { x->qdepth = d; break; }
         }
-        // four waves per replica for overloaded clusters of 16 or more
-        // instances, when every replica still stays resident: preemptions and
-        // rescans of different instances then run side by side (960 replicas of
-        // the overloaded sweep: 29.9 -> 21.6 ms per 500 ticks; 1024 of gauss10
-        // with extensions: 5.15 -> 4.39 ms per 250).  Below the load limit such
-        // events are rare and the barriers cost more than they give; the four
-        // instances of tiny lose too (6.56 -> 7.36 ms per 1000 ticks).
+        // Four waves per replica for overloaded clusters of 16 or more instances
+        // that preempt often, when every replica still stays resident:
+        // preemptions and rescans of different instances then run side by side.
+        // One against four waves, ms per 100 ticks of 1024 replicas at loads of
+        // about 1.1 (and of 2): at the requests of enterprise, 3.5 victims a tick
+        // by expected_victims for 16 instances, 2.63 and 2.19 (2.58 and 2.17),
+        // for 64 8.22 and 5.18 (8.02 and 5.36); at those of gauss10, 0.4 for 16,
+        // 1.75 and 1.90 (1.16 and 1.34), 0.85 for 32 2.55 and 2.52 (1.73 and
+        // 1.84), 1.3 for 48 3.32 and 2.97 (2.25 and 2.28), 1.7 for 64 4.05 and
+        // 3.42 (2.82 and 2.70).  INFaaS rescans less: 1.3 for 48 instances 1.95
+        // and 2.00, 1.5 for 56 2.16 and 2.15, 1.7 for 64 2.33 and 2.28.
+        // Promotion passes bring rescans of their own: 0.1 for 16 instances 1.51
+        // and 1.59 (1.66 and 1.60), 0.2 for 32 2.21 and 2.16 (2.37 and 2.10), 0.4
+        // for 16 2.15 and 2.02 (2.09 and 1.72).  At a load of 0.6, without
+        // preemptions, four waves take 1.2 to 1.5 times as long.  Fewer
+        // replicas, other arrivals and block sizes lie alike.
         if (x->I >= 16 && x->I <= 64 && x->qdepth) {
             p.qdepth = x->qdepth;
             p.nw = 4;
-            x->four_auto = uint64_t(step_blocks_per_cu(p)) * uint64_t(cus) >= x->R && expected_load(*x) > 0.9;
+            x->four_ok = uint64_t(step_blocks_per_cu(p)) * uint64_t(cus) >= x->R && expected_load(*x) > 0.9;
+            const double least = x->cfg.promote_period ? 0.2 : x->cfg.dispatch_policy == MTS_POLICY_INFAAS ? 1.5 : 1.2;
+            x->four_auto = x->four_ok && expected_victims(*x) >= least;
             x->four_waves = x->four_auto;
         }
     }
@@ -463,14 +490,13 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
 int mts_set_launch(mts_handle h, uint32_t threads, uint32_t blocks)
 {
     if (!h) return MTS_EINVAL;
-    // the block is the replica's waves: its size is fixed at create (64 asks for
-    // one wave where create chose four)
+    // the block is the replica's waves: one size per handle, except where the
+    // step can run on one wave or on four
     Params p = make_params(h);
-    const bool one = h->four_auto && threads == 64;
-    p.nw = h->four_auto && h->qdepth ? 4 : p.nw;
-    if (threads != 0 && !one && int(threads) != step_threads(p)) return MTS_EINVAL;
+    const bool four = h->four_ok && h->qdepth;
+    if (threads != 0 && !(four && (threads == 64 || threads == 256)) && int(threads) != step_threads(p)) return MTS_EINVAL;
     if (blocks > h->R) return MTS_EINVAL;
-    h->four_waves = h->four_auto && !one;
+    h->four_waves = threads == 0 ? h->four_auto : h->four_ok && threads == 256;
     h->blocks = blocks;
     return MTS_OK;
 }

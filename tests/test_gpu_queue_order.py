@@ -21,6 +21,9 @@ from paper_2608_16336_amd import Scheduler  # noqa: E402
 from paper_2608_16336_amd.mts import MtsError  # noqa: E402
 
 
+INFAAS = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
+
+
 def _cfg(I, S, M, arrival, K=10, blind=0, interval=1, out=40.0, infaas=False):
     c = preset("tiny")
     c.update(n_instances=I, slots_per_instance=S, kv_blocks=M, headroom_base=M / 8.0, headroom_decay=0.7, mig_interval=interval,
@@ -29,7 +32,7 @@ def _cfg(I, S, M, arrival, K=10, blind=0, interval=1, out=40.0, infaas=False):
     if blind:
         c["tier_blind"] = 1
     if infaas:
-        c["dispatch"] = dict(policy="infaas", alpha=64, beta=1, gamma=1, pen_overloaded=512, pen_interfered=128, ewma_shift=4)
+        c["dispatch"] = dict(INFAAS)
     return c
 
 
@@ -86,15 +89,16 @@ def test_depth_is_kept_where_every_replica_stays_resident():
     assert g.queue_cache > 0
 
 
-@pytest.mark.parametrize("cfg", [
-    _cfg(16, 128, 300, dict(kind="poisson", mean=9.0)),
-    _cfg(33, 192, 300, dict(kind="gamma_poisson", mean=20.0, cv=2.0), K=4, interval=3),
-    _cfg(64, 64, 160, dict(kind="poisson", mean=24.0), blind=1),
-    _cfg(17, 64, 200, dict(kind="poisson", mean=9.0), infaas=True),
-    with_extensions(_cfg(20, 128, 200, dict(kind="poisson", mean=9.0))),
+@pytest.mark.parametrize("cfg,chosen", [
+    (_cfg(16, 128, 300, dict(kind="poisson", mean=9.0)), 64),
+    (_cfg(33, 192, 300, dict(kind="gamma_poisson", mean=20.0, cv=2.0), K=4, interval=3), 256),
+    (_cfg(64, 64, 160, dict(kind="poisson", mean=24.0), blind=1), 256),
+    (_cfg(17, 64, 200, dict(kind="poisson", mean=9.0), infaas=True), 64),
+    (with_extensions(_cfg(20, 128, 200, dict(kind="poisson", mean=9.0))), 256),
 ], ids=["I16", "I33", "I64_blind", "I17_infaas", "I20_ext"])
-def test_four_waves_per_replica_equal_one(cfg):
-    # overloaded clusters run four waves per replica; 64 threads ask for one
+def test_four_waves_per_replica_equal_one(cfg, chosen):
+    # overloaded clusters can run four waves per replica or one (256 or 64
+    # threads), and run four where they are expected to preempt often
     o = oracle.Oracle(cfg)
     o.step(200)
     want = o.export()
@@ -102,9 +106,10 @@ def test_four_waves_per_replica_equal_one(cfg):
     for threads in (0, 64, 256):
         g = Scheduler(cfg)
         g.set_launch(threads, 0)
-        assert g.launch()[0] == (64 if threads == 64 else 256)
+        assert g.launch()[0] == (threads or chosen)
         g.step(150)
         g.set_launch(0, 1)  # back to the automatic size, both replicas in one block
+        assert g.launch()[0] == chosen
         g.step(50)
         got = g.export()
         for k in want:
@@ -113,6 +118,30 @@ def test_four_waves_per_replica_equal_one(cfg):
     assert g.launch()[0] == 64
     with pytest.raises(MtsError):
         g.set_launch(128, 0)
+
+
+@pytest.mark.parametrize("name,I,mean,kw,threads", [
+    # overloaded, but long requests grow slowly and few are preempted: four
+    # waves are slower (1024 replicas, 100 ticks: 1.90 ms against 1.75)
+    ("gauss10", 16, 5.2, {}, 64),
+    ("gauss10", 32, 10.4, {}, 64),
+    ("gauss10", 56, 18.2, {}, 256),
+    ("gauss10", 48, 15.6, dict(dispatch=INFAAS), 64),
+    ("gauss10", 64, 20.8, dict(dispatch=INFAAS), 256),
+    ("enterprise", 16, 11.4, {}, 256),
+    ("sweep", 32, 30.0, {}, 256),
+    # promotion passes bring rescans
+    ("gauss10", 16, 5.2, dict(ext=True), 256),
+])
+def test_four_waves_where_a_cluster_preempts_often(name, I, mean, kw, threads):
+    c = preset(name)
+    c.update(n_instances=I, mig_max_pairs=I // 2, arrival=dict(kind="poisson", mean=mean))
+    if kw.get("ext"):
+        c = with_extensions(c)
+    else:
+        c.update(kw)
+    c["groups"] = [dict(c["groups"][-1], n_replicas=8)]
+    assert Scheduler(c).launch()[0] == threads
 
 
 def test_one_wave_where_the_load_leaves_no_queue():
