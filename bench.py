@@ -43,7 +43,7 @@ VALU_PEAK_GINST = 256 * 2.4
 #   read, write   HBM bytes per launch from TCC_EA0_RDREQ_{32B,64B,128B} and
 #                 TCC_EA0_WRREQ{,_64B} (requests times their sizes)
 PROFILED = {
-    '887cdeecf26652ba': {"valu_per_rt": 657.1, "lane_util": 0.5343, "read": 8284276998, "write": 7501849078},
+    'e62599323363f8b9': {"valu_per_rt": 657.1, "lane_util": 0.5343, "read": 8280912710, "write": 7503924605},
 }
 
 

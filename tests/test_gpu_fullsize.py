@@ -53,7 +53,7 @@ def test_full_size_sampled_replicas(name, ticks, groups_sampled):
     cfg = preset(name)
     g = Scheduler(cfg)
     threads, blocks = g.launch()
-    # one wave per replica; a workgroup of eight for 128 or more instances
+    # one wave per replica; a workgroup of eight for more than 64 instances
     assert threads == (512 if cfg["n_instances"] >= 128 else 64) and 1 <= blocks <= g.R
     g.step(ticks)
     torch.cuda.synchronize()

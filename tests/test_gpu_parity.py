@@ -790,7 +790,7 @@ def test_extension_state_export_import_resumes_exactly():
 def test_large_clusters_pairing_ends(case):
     # Clusters of 65..256 instances, overloaded so that many instances are
     # below zero freeness: pairing reads only the two ends of the (F, index)
-    # order, which the kernels for 128+ instances take by wave minima and
+    # order, which the kernels for more than 64 instances take by wave minima and
     # maxima when they are disjoint (Section 3.5); pair caps from 1 to I/2,
     # thresholds 0 and 3/10, some instances draining.
     rng = random.Random(12000 + case)
