@@ -365,9 +365,12 @@ int mts_create(const mts_cfg* cfg, void* dev_buf, size_t bytes, hipStream_t stre
     // replica resident at once with a block per CU to spare (the cache only
     // saves rescans; replicas that do not fit at once cost more, and with no
     // spare room per CU the dispatcher cannot place every block at once).
-    // Measured on the overloaded sweep with 960 replicas, which the first rule
-    // alone leaves without a cache: 54.9 ms per 500 ticks with depth 0, 36.3
-    // with 7.
+    // Measured on the sweep's clusters where the first rule alone leaves them
+    // without a cache, ms per 200 ticks with depth 0 and 7: 960 replicas at a
+    // load of 0.45 1.09 and 1.16, 0.67 1.76 and 1.78, 0.82 9.14 and 7.48, 0.9
+    // 12.7 and 10.1; under INFaaS at 0.45 3.26 and 3.20, at 0.9 10.8 and 8.25.
+    // (Below a load of about 0.7, where little waits, the cache's insertions and
+    // the finish places cost 3 to 6 %; the depth does not look at the load.)
     {
         Params p = make_params(x);
         p.qdepth = 0;
